@@ -244,6 +244,20 @@ def test_pack_whole_prompt_dataset(lib, name):
     _cmp_pack(lib, pl, None, keep, 4096, 128, policy="best_fit")
 
 
+@pytest.mark.parametrize("n_win", [31, 32, 33, 95, 96, 97])
+@pytest.mark.parametrize("n", [63, 64, 65, 1023, 1024, 1025, 15360, 15361])
+def test_pack_pool_and_stream_edges(lib, n, n_win):
+    """Pools around what one and two registers per lane hold (32, 96) and what falls back to scanning, item counts
+    around a wavefront, the workgroup and the stream lengths that fit in LDS (15 360); rows of very many and of few
+    items, so that the pool is closed up inside a row and between rows; loss positions written by the packing
+    workgroup (capacity up to 16 384) and by the grid-wide kernel. Bit-exact."""
+    rng = np.random.default_rng(n * 100 + n_win)
+    pl, cl = rng.integers(1, 5, size=n).astype(np.int32), rng.integers(1, 20, size=n).astype(np.int32)
+    for cap, policy in ((24, "first_fit"), (900, "first_fit"), (24, "best_fit"), (900, "best_fit")):
+        if policy == "first_fit" or n <= 1025:      # the oracle's best-fit scan is quadratic in the pool
+            _cmp_pack(lib, pl, cl, None, cap, n_win, policy=policy)
+
+
 def test_pack_reports_device_detected_errors(lib):
     # item longer than the window
     got = lib.dppo_pack(np.array([3, 9], np.int32), np.array([2, 8], np.int32), None, 16, 4, device=DEV)
