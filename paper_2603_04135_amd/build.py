@@ -13,7 +13,7 @@ INCLUDE = os.path.join(os.path.dirname(PKG_DIR), "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libdppo_hip.so")
 
-SOURCES = ["api.hip", "select.hip", "pack.hip", "head_kernels.hip", "gemm_plain.hip", "gemm_mfma.hip"]
+SOURCES = ["api.hip", "select.hip", "pack.hip", "head_kernels.hip", "gemm_f32.hip", "gemm_mfma.hip"]
 COMMON_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -81,8 +81,9 @@ struct WsPlan {
     size_t fixed_bytes, chunk_bytes; // bytes of the per-call regions / of one set of per-chunk regions
     int sets;                      // sets of per-chunk regions (2: the forward of chunk c + 1 runs ahead of the backward of chunk c)
     // region offsets
-    size_t o_wt, o_logp, o_ell, o_kl, o_clip, o_seq, o_sratio, o_hc, o_hct, o_part, o_zg, o_gt, o_y, o_rowc, o_zy, o_lse, o_c;
+    size_t o_wt, o_logp, o_ell, o_kl, o_clip, o_seq, o_sratio, o_hc, o_hct, o_part, o_zg, o_fpart, o_y, o_rowc, o_zy, o_lse, o_c;
     size_t o_bref, o_mx, o_scale, o_redo_list, o_redo_sum, o_redo_count, o_dwpart;   // bf16 backward only
+    int f32_parts;                 // float32: parts the K dimension of the dH GEMM may be cut into (scratch for their sums)
     size_t total;
 };
 
@@ -100,7 +101,7 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, REGION_ALIGN); return o; };
     const size_t N = (size_t)s.N;
-    p.o_wt = take(!bwd ? 0 : s.dtype == 1 ? gemm_b_blocked_elems(s.D, p.Vp) * p.es : (size_t)s.D * p.Vp * p.es);
+    p.o_wt = take(bwd && s.dtype == 1 ? gemm_b_blocked_elems(s.D, p.Vp) * p.es : 0);
     p.o_logp = take(bwd ? N * 4 : 0);   // log-probs of the batch when the caller wants none back
     p.o_ell = take(bwd ? N * 4 : 0);
     p.o_kl = take(bwd ? N * 4 : 0);
@@ -110,10 +111,13 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
     p.o_dwpart = take(bwd && s.dtype == 1 ? mfma_dw_partial_bytes() : 0);
     p.fixed_bytes = off;
     p.o_hc = take((size_t)n_cp * s.D * p.es);
-    p.o_hct = take(!bwd ? 0 : s.dtype == 1 ? gemm_b_blocked_elems(s.D, n_cp) * p.es : (size_t)n_cp * s.D * p.es);
+    p.o_hct = take(bwd && s.dtype == 1 ? gemm_b_blocked_elems(s.D, n_cp) * p.es : 0);
     p.o_part = take((size_t)p.n_tiles * n_cp * 8);
     p.o_zg = take(need_z ? (size_t)n_cp * p.Vp * p.zs : 0);
-    p.o_gt = take(bwd && s.dtype == 0 ? (size_t)n_cp * p.Vp * p.zs : 0);   // transposed copy: float32 path only
+    // (never more scratch than one chunk of logits)
+    const int64_t max_parts = p.Vp / s.D, k_parts = gemm_f32_max_parts(s.V);
+    p.f32_parts = bwd && s.dtype == 0 ? (int)(max_parts < k_parts ? max_parts : k_parts) : 0;
+    p.o_fpart = take(p.f32_parts > 1 ? (size_t)p.f32_parts * n_cp * s.D * 4 : 0);
     p.o_y = take((size_t)n_cp * 4);
     p.o_rowc = take((size_t)n_cp * 4);
     p.o_zy = take((size_t)n_cp * 4);
@@ -213,9 +217,8 @@ struct Regions {
 
 // Forward statistics of one chunk: Hc, targets, log-probs, lse. `ws` is the base of the set of
 // per-chunk regions to use (the workspace itself for set 0); no per-call region is touched. With keep_z the chunk's logits
-// stay in the workspace for the backward pass: as float32 logits (float32 path, which also gets
-// HcT), or as bf16 exponentials against the per-token reference left in the bref region (bf16 path).
-int chunk_forward(const dppo_head_shape& s, const WsPlan& p, char* ws, const void* H, const void* W,
+// stay in the workspace for the backward pass: as float32 logits (float32 path), or as bf16 exponentials against the per-token reference left in the bref region (bf16 path).
+int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, const void* H, const void* W,
                    const int32_t* ids, const int32_t* loss_pos, ChunkView cv, bool keep_z,
                    float* logp_all, float* lse_all, int32_t* status, hipStream_t st) {
     void* Hc = ws + p.o_hc;
@@ -224,8 +227,11 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, char* ws, const voi
     float* lse_c = reinterpret_cast<float*>(ws + p.o_lse);
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-        launch_gather_rows(s.dtype, H, ids, loss_pos, s.T, s.D, s.V, cv, Hc, keep_z && s.dtype == 0 ? ws + p.o_hct : nullptr,
-                           y, reinterpret_cast<int32_t*>(ws + p.o_rowc), status, st);
+        const bool exp_ref = s.dtype == 1 && keep_z;
+        GatherArgs ga{H, W, ids, loss_pos, s.T, s.D, s.V, Hc, y, reinterpret_cast<int32_t*>(ws + p.o_rowc), status, zy,
+                      exp_ref ? reinterpret_cast<float*>(ws + p.o_bref) : nullptr,
+                      exp_ref ? reinterpret_cast<int32_t*>(ws + p.o_redo_count) : nullptr};
+        launch_gather_rows(s.dtype, ga, cv, st);
     }
     if (s.dtype == 1 && keep_z) {
         float2* part = reinterpret_cast<float2*>(ws + p.o_part);
@@ -236,10 +242,6 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, char* ws, const voi
         float* redo_sum = reinterpret_cast<float*>(ws + p.o_redo_sum);
         // reference of the stored exponentials = the target logit: lse - reference = -logp of a
         // token that was sampled from (nearly) this policy, a few units in any sane batch
-        {
-            StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-            launch_target_logit(1, Hc, W, y, cv.n_cp, s.D, zy, bref, redo_count, st);
-        }
         {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
             const int rc = launch_mfma_logits_exp(W, s.V, s.D, Hc, cv.n_cp, part, bref, ws + p.o_zg, p.Vp, p.Vp, st);
@@ -256,12 +258,11 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, char* ws, const voi
             launch_mfma_logits(W, s.V, s.D, Hc, cv.n_cp, part, st);
         }
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-        launch_target_logit(1, Hc, W, y, cv.n_cp, s.D, zy, nullptr, nullptr, st);
         launch_combine_logprob(part, p.n_tiles, zy, cv, lse_c, logp_all, lse_all, st);
     } else {
-        StoreSpec out{ws + p.o_zg, p.Vp, 0, 0, nullptr, 0};
-        launch_gemm_plain_f32(reinterpret_cast<const float*>(Hc), s.D, reinterpret_cast<const float*>(W), s.D,
-                              cv.n_cp, s.V, s.D, out, st);
+        GemmF32 g{reinterpret_cast<const float*>(Hc), s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
+                  reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 1};
+        launch_gemm_f32(g, cus, st);
         launch_row_stats_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, s.V, y, cv, lse_c, logp_all,
                              lse_all, st);
     }
@@ -470,13 +471,13 @@ int dppo_token_logprob(const dppo_head_shape* shape, const void* H, const void* 
     if (rc != DPPO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     char* w = reinterpret_cast<char*>(ws);
-    if (status) launch_fill_zero(status, 4, st);
+    if (status) launch_fill_zero(nullptr, 0, status, st);
     for (int64_t n0 = 0; n0 < s.N; n0 += p.n_cp) {
         ChunkView cv;
         cv.n0 = n0;
         cv.n_c = (int32_t)((s.N - n0) < p.n_cp ? (s.N - n0) : p.n_cp);
         cv.n_cp = round_up32(cv.n_c, CHUNK_ALIGN);
-        if (int rc = chunk_forward(s, p, w, H, W, ids, loss_pos, cv, false, logp, lse, status, st)) return rc;
+        if (int rc = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, cv, false, logp, lse, status, st)) return rc;
     }
     return check_launch("dppo_token_logprob");
 }
@@ -556,12 +557,11 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     float* clipf = reinterpret_cast<float*>(w + p.o_clip);
     float* seq_tmp = reinterpret_cast<float*>(w + p.o_seq);
 
-    if (status) launch_fill_zero(status, 4, st);
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-        launch_fill_zero(dH, (size_t)s.T * s.D * p.es, st);
-        if (!lp->accumulate_dW && s.N == 0) launch_fill_zero(dW, (size_t)s.V * s.D * 4, st);
-        if (s.N > 0) launch_transpose_w(s.dtype, W, s.V, s.D, p.Vp, w + p.o_wt, st);
+        launch_fill_zero(dH, (size_t)s.T * s.D * p.es, status, st);
+        if (!lp->accumulate_dW && s.N == 0) launch_fill_zero(dW, (size_t)s.V * s.D * 4, nullptr, st);
+        if (s.N > 0 && s.dtype == 1) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
     }
 
     const bool recompute = lp->recompute_logits != 0;
@@ -579,7 +579,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
 
     if (seq_level && !ahead) {
         for (int64_t c = 0; c < p.n_chunks; ++c)
-            if (int rc2 = chunk_forward(s, p, w, H, W, ids, loss_pos, view(c), false, logp_all, nullptr, status, st)) return rc2;
+            if (int rc2 = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, view(c), false, logp_all, nullptr, status, st)) return rc2;
         launch_seq_ratio(loss_cu, S, logp_all, logp_old, seq_ratio, 0, s.N, nullptr, st);
     }
 
@@ -587,7 +587,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     // with the forward running ahead, also the ratios of the sequences that end in it
     auto forward = [&](int64_t c) -> int {
         const ChunkView cv = view(c);
-        if (int rc2 = chunk_forward(s, p, regions(c), H, W, ids, loss_pos, cv, s.dtype == 0 || !recompute, logp_all, nullptr, status, st))
+        if (int rc2 = chunk_forward(s, p, cus, regions(c), H, W, ids, loss_pos, cv, s.dtype == 0 || !recompute, logp_all, nullptr, status, st))
             return rc2;
         if (ahead) launch_seq_ratio(loss_cu, S, logp_all, logp_old, seq_ratio, cv.n0, cv.n0 + cv.n_c, status, st);
         return DPPO_OK;
@@ -612,13 +612,12 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         const float* lse_c = reinterpret_cast<const float*>(wc + p.o_lse);
         // bf16: the chunk region holds either gradient entries (recompute) or exponentials whose
         // row scale goes to the dH epilogue and into the HcT operand of dW; in the blocked layout it
-        // serves both GEMMs. float32: row-major G and its transposed copy GT.
+        // serves both GEMMs. float32: row-major G, which the GEMMs read along either dimension.
         void* G = wc + p.o_zg;
         const float* row_scale = nullptr;
         if (s.dtype == 0) {
             StageTimer tm(DPPO_STAGE_GRAD_LOGITS, st);
-            launch_grad_logits_f32(reinterpret_cast<float*>(G), reinterpret_cast<float*>(wc + p.o_gt), s.V, p.Vp, y, lse_c,
-                                   ta.c_chunk, cv.n_cp, st);
+            launch_grad_logits_f32(reinterpret_cast<float*>(G), s.V, p.Vp, y, lse_c, ta.c_chunk, cv.n_c, st);
         } else if (recompute) {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
             const int rc2 = launch_mfma_logits_grad(W, s.V, s.D, wc + p.o_hc, cv.n_cp, y, lse_c, ta.c_chunk, G, p.Vp,
@@ -657,10 +656,13 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
                                reinterpret_cast<float*>(w + p.o_dwpart), st);
             }
         } else {
-            launch_gemm_plain_f32(reinterpret_cast<const float*>(G), p.Vp, reinterpret_cast<const float*>(w + p.o_wt),
-                                  p.Vp, cv.n_c, s.D, p.Vp, oh, st);
-            launch_gemm_plain_f32(reinterpret_cast<const float*>(wc + p.o_gt), cv.n_cp,
-                                  reinterpret_cast<const float*>(wc + p.o_hct), cv.n_cp, s.V, s.D, cv.n_cp, ow, st);
+            const float* Gf = reinterpret_cast<const float*>(G);
+            GemmF32 gh{Gf, p.Vp, 0, reinterpret_cast<const float*>(W), s.D, 1, cv.n_c, s.D, s.V, reinterpret_cast<float*>(oh.C),
+                       oh.ldc, 0, oh.row_map, p.f32_parts > 1 ? reinterpret_cast<float*>(wc + p.o_fpart) : nullptr, p.f32_parts};
+            launch_gemm_f32(gh, cus, st);
+            GemmF32 gw{Gf, p.Vp, 1, reinterpret_cast<const float*>(wc + p.o_hc), s.D, 1, s.V, s.D, cv.n_c,
+                       reinterpret_cast<float*>(ow.C), ow.ldc, ow.accumulate, nullptr, nullptr, 1};
+            launch_gemm_f32(gw, cus, st);
         }
         return DPPO_OK;
     };

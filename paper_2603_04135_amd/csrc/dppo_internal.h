@@ -41,13 +41,19 @@ struct ChunkView {
     int32_t n_cp;  // padded chunk rows (multiple of 256)
 };
 
-void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// Clears p, and *word too if it is not NULL.
+void launch_fill_zero(void* p, size_t bytes, int32_t* word, hipStream_t st);
 // y[n] = target id of loss token n0+n and rowc[n] = its row of H, both clamped into range (a clamp
 // that changed something is OR-ed into *status, see DPPO_HEAD_BAD_*; status may be NULL);
-// Hc[n_cp, D] = H[rowc[n]] (zero rows beyond n_c); HcT[D, n_cp] its transpose (may be NULL).
-void launch_gather_rows(int dtype, const void* H, const int32_t* ids, const int32_t* loss_pos,
-                        int64_t T, int32_t D, int32_t V, ChunkView cv, void* Hc, void* HcT,
-                        int32_t* y, int32_t* rowc, int32_t* status, hipStream_t st);
+// Hc[n_cp, D] = H[rowc[n]] (zero rows beyond n_c). bfloat16: also zy[n] = H[rowc[n]] . W[y[n]] in fp32 (0 beyond
+// n_c), copied to bref[n] and *flag cleared where not NULL.
+struct GatherArgs {
+    const void* H; const void* W; const int32_t* ids; const int32_t* loss_pos;
+    int64_t T; int32_t D, V;
+    void* Hc; int32_t* y; int32_t* rowc; int32_t* status;
+    float* zy; float* bref; int32_t* flag;
+};
+void launch_gather_rows(int dtype, const GatherArgs& a, ChunkView cv, hipStream_t st);
 // Blocked layout of the B operand of the dH and dW GEMMs (WT, HcT): blocks of GEMM_B_BLOCK_ROWS rows x
 // GEMM_B_BLOCK_K columns of a [rows, K] matrix, block (i, j) at (i * K / GEMM_B_BLOCK_K + j) blocks from
 // the start, row-major inside; the rows are padded to whole blocks (the pad rows are never written and only
@@ -56,19 +62,15 @@ constexpr int GEMM_B_BLOCK_ROWS = 256, GEMM_B_BLOCK_K = 64;
 inline size_t gemm_b_blocked_elems(int64_t rows, int64_t K) {
     return (size_t)((rows + GEMM_B_BLOCK_ROWS - 1) / GEMM_B_BLOCK_ROWS * GEMM_B_BLOCK_ROWS) * (size_t)K;
 }
-// WT = transpose of W[V, D], columns v >= V zero: row-major [D, Vp] (float32) or blocked (bfloat16, K = Vp).
-void launch_transpose_w(int dtype, const void* W, int32_t V, int32_t D, int32_t Vp, void* WT,
-                        hipStream_t st);
-// zy[n] = Hc[n] . W[y[n]] in fp32; also copied to bref[n] and *flag cleared where not NULL.
-void launch_target_logit(int dtype, const void* Hc, const void* W, const int32_t* y, int32_t n_cp,
-                         int32_t D, float* zy, float* bref, int32_t* flag, hipStream_t st);
+// WT = transpose of the bfloat16 W[V, D], columns v >= V zero, in the blocked layout (K = Vp).
+void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* WT, hipStream_t st);
 // lse from per-tile partial (max, sumexp) pairs part[tile][n_cp]; logp = zy - lse.
 void launch_combine_logprob(const float2* part, int32_t n_tiles, const float* zy, ChunkView cv,
                             float* lse_chunk, float* logp_out, float* lse_out, hipStream_t st);
 // Statistics of the GEMM that stores exponentials against the per-token reference bref[n]:
 // part[tile][n] = (max z, sum exp(z - bref[n])); lse = bref + log(sum), logp = zy - lse, mx[n] = row
 // maximum. Tokens whose sum is out of the safe range are appended to redo_list (count in
-// *redo_count, cleared beforehand by launch_target_logit) instead.
+// *redo_count, cleared beforehand by launch_gather_rows) instead.
 void launch_combine_exp(const float2* part, int32_t n_tiles, const float* zy, const float* bref, ChunkView cv,
                         float* lse_chunk, float* logp_out, float* mx, int32_t* redo_count, int32_t* redo_list,
                         float* redo_sum, hipStream_t st);
@@ -111,9 +113,9 @@ void launch_token_norm_coef(int32_t Q, int32_t G, const int32_t* comp_len, const
                             hipStream_t st);
 
 // float32 path, in place over the chunk's stored logits: G[n,v] = c[n] (1[v==y[n]] - exp(z - lse[n]))
-// for v < V, 0 for V <= v < Vp; row-major [n_cp, Vp], also written transposed to GT[Vp, n_cp].
-void launch_grad_logits_f32(float* ZG, float* GT, int32_t V, int32_t Vp, const int32_t* y, const float* lse,
-                            const float* c, int32_t n_cp, hipStream_t st);
+// for n < n_c, v < V, 0 for V <= v < Vp; row-major, pitch Vp.
+void launch_grad_logits_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const float* lse, const float* c,
+                            int32_t n_c, hipStream_t st);
 
 struct SeqReduceArgs {
     const int32_t* loss_cu; int32_t S; int64_t N;
@@ -135,9 +137,19 @@ struct StoreSpec {
     const int32_t* row_map;    // output row = row_map[row_base + m] if not NULL
     int64_t row_base;
 };
-// fp32 reference-grade GEMM (any sizes), gemm_plain.hip.
-void launch_gemm_plain_f32(const float* A, int64_t lda, const float* B, int64_t ldb, int32_t M,
-                           int32_t N, int32_t K, const StoreSpec& out, hipStream_t st);
+// fp32 GEMM of any size (gemm_f32.hip): A is [M, K] with pitch lda, or [K, M] if a_km; B likewise [N, K] or [K, N].
+// Output row m is row row_map[m] of C if row_map is not NULL. With `partial` (scratch of max_parts * M * N floats)
+// the K dimension may be cut into up to max_parts parts whose sums are added up in a fixed order.
+struct GemmF32 {
+    const float* A; int64_t lda; int a_km;
+    const float* B; int64_t ldb; int b_km;
+    int32_t M, N, K;
+    float* C; int64_t ldc; int accumulate;
+    const int32_t* row_map;
+    float* partial; int max_parts;
+};
+int gemm_f32_max_parts(int64_t K);
+void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st);
 
 // bf16 MFMA GEMMs (gemm_mfma.hip). K must be a multiple of 64; A and B rows may be read up
 // to the next multiple of the tile size, so operands are padded scratch buffers or clamped.

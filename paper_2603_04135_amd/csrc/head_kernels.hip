@@ -10,14 +10,9 @@
 namespace dppo {
 namespace {
 
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
-__device__ __forceinline__ float to_f32(float x) { return x; }
-__device__ __forceinline__ float to_f32(uint16_t x) { return bf16_to_f32(x); }
-
 // ------------------------------------------------------------------------------------
-__global__ void fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t ntail) {
+__global__ void fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t ntail, int32_t* word) {
+    if (word && blockIdx.x == 0 && threadIdx.x == 0) *word = 0;
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < n16; i += stride) p[i] = make_uint4(0, 0, 0, 0);
@@ -25,97 +20,65 @@ __global__ void fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size
 }
 
 // ------------------------------------------------------------------------------------
-// Tiled gather + transpose. Source rows come from `src` (row stride ld_src) through an
-// optional row index; rows >= n_valid read as zero. Writes dst[r, c] (optional) and
-// dstT[c, r] (optional) for r < n_rows_out, c < n_cols_out where columns >= n_cols read as 0.
+// One wavefront per row of the chunk: target id and (clamped) row of H of the loss token, a copy of that row
+// to Hc (zero beyond n_c), and for bfloat16 the target logit zy = H[row] . W[y] from the same registers. An id
+// outside [0, V) or a position outside [0, T) is clamped into the range and reported in *status, so that every
+// later gather and scatter of the call stays in bounds.
+// Bound by HBM: 3 rows of D elements per token. One launch instead of three (targets, copy, dot product), the copy
+// is not read back.
 template <typename E>
-__global__ __launch_bounds__(256) void gather_transpose_kernel(
-    const E* __restrict__ src, int64_t ld_src, const int32_t* __restrict__ row_index, int64_t row_index_base,
-    int64_t src_row0, int64_t src_rows_total, int32_t n_valid, int32_t n_cols, int32_t n_rows_out,
-    int32_t n_cols_out, E* __restrict__ dst, int64_t ld_dst, E* __restrict__ dstT, int64_t ld_dstT) {
-    __shared__ E tile[64][65];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int rr = ty; rr < 64; rr += 4) {
-        const int r = r0 + rr, c = c0 + tx;
-        E v = (E)0;
-        if (r < n_valid && c < n_cols) {
-            int64_t sr = row_index ? (int64_t)row_index[row_index_base + r] : src_row0 + r;
-            sr = sr < 0 ? 0 : (sr >= src_rows_total ? src_rows_total - 1 : sr);
-            v = src[sr * ld_src + c];
-        }
-        tile[rr][tx] = v;
-        if (dst && r < n_rows_out && c < n_cols_out) dst[(int64_t)r * ld_dst + c] = v;
-    }
-    __syncthreads();
-    if (dstT) {
-        for (int cc = ty; cc < 64; cc += 4) {
-            const int c = c0 + cc, r = r0 + tx;
-            if (c < n_cols_out && r < n_rows_out) dstT[(int64_t)c * ld_dstT + r] = tile[tx][cc];
-        }
-    }
-}
-
-// Target id and (clamped) row of H of every loss token of the chunk. An id outside [0, V) or a
-// position outside [0, T) is clamped into the range and reported in *status, so that every later
-// gather and scatter of the call stays in bounds.
-__global__ void targets_kernel(const int32_t* __restrict__ ids, const int32_t* __restrict__ loss_pos, int64_t T,
-                               int32_t V, int64_t n0, int32_t n_c, int32_t n_cp, int32_t* __restrict__ y,
-                               int32_t* __restrict__ rowc, int32_t* status) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= n_cp) return;
-    int32_t t = 0, row = 0;
-    int flags = 0;
-    if (n < n_c) {
-        int64_t r = loss_pos ? (int64_t)loss_pos[n0 + n] : n0 + n;
-        int64_t pos = loss_pos ? r + 1 : r;
-        if (r < 0 || pos >= T) flags |= DPPO_HEAD_BAD_POSITION;
-        r = r < 0 ? 0 : (r >= T ? T - 1 : r);
-        pos = pos < 0 ? 0 : (pos >= T ? T - 1 : pos);
-        t = ids[pos];
-        if (t < 0 || t >= V) flags |= DPPO_HEAD_BAD_TARGET;
-        t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-        row = (int32_t)r;
-    }
-    y[n] = t;
-    rowc[n] = row;
-    if (flags != 0 && status != nullptr) atomicOr(status, flags);
-}
-
-// ------------------------------------------------------------------------------------
-// One wavefront per token: zy[n] = Hc[n] . W[y[n]], copied to bref[n] if bref is not NULL;
-// clears *flag if flag is not NULL.
-template <typename E>
-__global__ __launch_bounds__(256) void target_logit_kernel(const E* __restrict__ Hc, const E* __restrict__ W,
-                                                           const int32_t* __restrict__ y, int32_t n_cp, int32_t D,
-                                                           float* __restrict__ zy, float* __restrict__ bref,
-                                                           int32_t* __restrict__ flag) {
+__global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t n0, int32_t n_c, int32_t n_cp, int vec) {
     const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (flag && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
+    if (a.flag && blockIdx.x == 0 && threadIdx.x == 0) *a.flag = 0;
     if (n >= n_cp) return;
-    const E* h = Hc + (size_t)n * D;
-    const E* w = W + (size_t)y[n] * D;
+    int64_t row = 0;
+    int32_t t = 0;
+    const bool valid = n < n_c;
+    if (valid) {
+        int flags = 0;
+        row = a.loss_pos ? (int64_t)a.loss_pos[n0 + n] : n0 + n;
+        int64_t pos = a.loss_pos ? row + 1 : row;
+        if (row < 0 || pos >= a.T) flags |= DPPO_HEAD_BAD_POSITION;
+        row = row < 0 ? 0 : (row >= a.T ? a.T - 1 : row);
+        pos = pos < 0 ? 0 : (pos >= a.T ? a.T - 1 : pos);
+        t = a.ids[pos];
+        if (t < 0 || t >= a.V) flags |= DPPO_HEAD_BAD_TARGET;
+        t = t < 0 ? 0 : (t >= a.V ? a.V - 1 : t);
+        if (flags != 0 && a.status != nullptr && lane == 0) atomicOr(a.status, flags);
+    }
+    if (lane == 0) {
+        a.y[n] = t;
+        a.rowc[n] = (int32_t)row;
+    }
+    const E* src = reinterpret_cast<const E*>(a.H) + (size_t)row * a.D;
+    E* dst = reinterpret_cast<E*>(a.Hc) + (size_t)n * a.D;
     float s = 0.0f;
-    if (sizeof(E) == 2 && D % 8 == 0) {          // bf16 rows (16-byte aligned): 8 elements per lane and step
-        const uint4* h8 = reinterpret_cast<const uint4*>(h);
-        const uint4* w8 = reinterpret_cast<const uint4*>(w);
-        for (int c = lane; c < D / 8; c += 64) {
-            const uint4 a = h8[c], b = w8[c];
-            const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+    if (vec) {                                   // rows of whole 16-byte vectors, 16-byte aligned
+        constexpr int PER = 16 / (int)sizeof(E);
+        const uint4* h = reinterpret_cast<const uint4*>(src);
+        const uint4* w = reinterpret_cast<const uint4*>(reinterpret_cast<const E*>(a.W) + (size_t)t * a.D);
+        for (int c = lane; c < a.D / PER; c += 64) {
+            const uint4 x = valid ? h[c] : make_uint4(0, 0, 0, 0);
+            reinterpret_cast<uint4*>(dst)[c] = x;
+            if (sizeof(E) == 2) {
+                const uint4 b = w[c];
+                const uint32_t aw[4] = {x.x, x.y, x.z, x.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                s = fmaf(__uint_as_float(aw[k] << 16), __uint_as_float(bw[k] << 16), s);
-                s = fmaf(__uint_as_float(aw[k] & 0xffff0000u), __uint_as_float(bw[k] & 0xffff0000u), s);
+                for (int k = 0; k < 4; ++k) {
+                    s = fmaf(__uint_as_float(aw[k] << 16), __uint_as_float(bw[k] << 16), s);
+                    s = fmaf(__uint_as_float(aw[k] & 0xffff0000u), __uint_as_float(bw[k] & 0xffff0000u), s);
+                }
             }
         }
     } else {
-        for (int d = lane; d < D; d += 64) s = fmaf(to_f32(h[d]), to_f32(w[d]), s);
+        for (int d = lane; d < a.D; d += 64) dst[d] = valid ? src[d] : (E)0;
     }
+    if (sizeof(E) == 4) return;
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if (lane == 0) {
-        zy[n] = s;
-        if (bref) bref[n] = s;
+        a.zy[n] = s;
+        if (a.bref) a.bref[n] = s;
     }
 }
 
@@ -353,25 +316,6 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __r
     }
 }
 
-// bf16 row gather by 16-byte vectors: dst[r] = src[row(r)] for r < n_valid (row through the
-// optional index, clamped), zero rows up to n_rows_out. vec_per_row = D / 8.
-__global__ __launch_bounds__(256) void gather_rows_bf16_kernel(const uint4* __restrict__ src, int32_t vec_per_row,
-                                                               const int32_t* __restrict__ row_index,
-                                                               int64_t row_index_base, int64_t src_row0,
-                                                               int64_t src_rows_total, int32_t n_valid,
-                                                               int32_t n_rows_out, uint4* __restrict__ dst) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)n_rows_out * vec_per_row) return;
-    const int32_t r = (int32_t)(i / vec_per_row), c = (int32_t)(i % vec_per_row);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < n_valid) {
-        int64_t sr = row_index ? (int64_t)row_index[row_index_base + r] : src_row0 + r;
-        sr = sr < 0 ? 0 : (sr >= src_rows_total ? src_rows_total - 1 : sr);
-        v = src[sr * vec_per_row + c];
-    }
-    dst[i] = v;
-}
-
 // fp32 path: one workgroup per token over the stored logits row.
 __global__ __launch_bounds__(256) void row_stats_kernel(const float* __restrict__ Z, int64_t ldz, int32_t V,
                                                         const int32_t* __restrict__ y, int64_t n0, int32_t n_c,
@@ -442,45 +386,26 @@ __global__ void token_loss_kernel(TokenLossArgs a, int64_t n0, int32_t n_c, int3
 }
 
 // ------------------------------------------------------------------------------------
-// Softmax-gradient pass over a stored logits chunk, 64 tokens x 64 vocabulary entries per
-// workgroup: in place Z[n,v] -> G[n,v], and the transposed copy GT[v,n] through LDS.
-template <typename ZT, typename GT_, typename ZV, typename GV>
-__global__ __launch_bounds__(256) void grad_logits_kernel(void* ZG, GT_* __restrict__ GTp, int32_t V, int64_t ld,
+// float32 path: softmax-gradient pass over the stored logits, in place, one 16-byte vector per thread (the pitch is
+// a multiple of 256 columns). Bound by HBM: 8 bytes per logit.
+__global__ __launch_bounds__(256) void grad_logits_kernel(float* __restrict__ ZG, int32_t V, int32_t Vp,
                                                           const int32_t* __restrict__ y, const float* __restrict__ lse,
-                                                          const float* __restrict__ cvec, int64_t n_cp) {
-    __shared__ GT_ tile[64][64 + 8];   // [v][n]
-    const int v0 = blockIdx.x * 64, nb = blockIdx.y * 64;
-    const int t = threadIdx.x;
-    const int kc = t & 7;
+                                                          const float* __restrict__ cvec) {
+    const int n = blockIdx.x;
+    const float l = lse[n], cn = cvec[n];
+    const int yt = y[n];
+    float4* row = reinterpret_cast<float4*>(ZG + (size_t)n * Vp);
+    for (int i = blockIdx.y * 256 + threadIdx.x; i < Vp / 4; i += gridDim.y * 256) {
+        const float4 z = row[i];
+        const float zz[4] = {z.x, z.y, z.z, z.w};
+        float g[4];
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int r = (t >> 3) + pass * 32;
-        const int64_t n = nb + r;
-        const float l = lse[n], cn = cvec[n];
-        const int yt = y[n];
-        char* p = reinterpret_cast<char*>(ZG) + ((size_t)n * ld + v0 + kc * 8) * sizeof(ZT);
-        const ZV z = *reinterpret_cast<const ZV*>(p);
-        GV g;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int v = v0 + kc * 8 + q;
-            const float pr = expf((float)z[q] - l);
-            float gv = cn * ((v == yt ? 1.0f : 0.0f) - pr);
-            gv = v < V ? gv : 0.0f;
-            const GT_ b = (GT_)gv;   // keep the scalar: reading g[q] back right after writing it miscompiles
-            g[q] = b;
-            tile[kc * 8 + q][r] = b;
+        for (int q = 0; q < 4; ++q) {
+            const int v = i * 4 + q;
+            const float gv = cn * ((v == yt ? 1.0f : 0.0f) - expf(zz[q] - l));
+            g[q] = v < V ? gv : 0.0f;
         }
-        *reinterpret_cast<GV*>(p) = g;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int v = (t >> 3) + pass * 32;
-        GV g;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) g[q] = tile[v][kc * 8 + q];
-        *reinterpret_cast<GV*>(GTp + (size_t)(v0 + v) * n_cp + nb + kc * 8) = g;
+        row[i] = make_float4(g[0], g[1], g[2], g[3]);
     }
 }
 
@@ -589,60 +514,30 @@ __global__ __launch_bounds__(256) void final_reduce_kernel(SeqReduceArgs a) {
 }  // namespace
 
 // ======================================================================================
-void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
-    if (bytes == 0) return;
+void launch_fill_zero(void* p, size_t bytes, int32_t* word, hipStream_t st) {
+    if (bytes == 0 && !word) return;
     const size_t n16 = bytes / 16, ntail = bytes % 16;
     size_t blocks = (n16 + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks == 0) blocks = 1;
     fill_zero_kernel<<<(unsigned)blocks, 256, 0, st>>>(reinterpret_cast<uint4*>(p), n16,
-                                                       reinterpret_cast<unsigned char*>(p) + n16 * 16, ntail);
+                                                       reinterpret_cast<unsigned char*>(p) + n16 * 16, ntail, word);
 }
 
-void launch_gather_rows(int dtype, const void* H, const int32_t* ids, const int32_t* loss_pos, int64_t T,
-                        int32_t D, int32_t V, ChunkView cv, void* Hc, void* HcT, int32_t* y, int32_t* rowc,
-                        int32_t* status, hipStream_t st) {
-    targets_kernel<<<(unsigned)ceil_div(cv.n_cp, 256), 256, 0, st>>>(ids, loss_pos, T, V, cv.n0, cv.n_c, cv.n_cp, y,
-                                                                     rowc, status);
-    dim3 grid((unsigned)ceil_div(D, 64), (unsigned)(cv.n_cp / 64));
-    if (dtype == 1 && HcT == nullptr && D % 8 == 0) {
-        const int64_t n_vec = (int64_t)cv.n_cp * (D / 8);
-        gather_rows_bf16_kernel<<<(unsigned)ceil_div(n_vec, 256), 256, 0, st>>>(
-            reinterpret_cast<const uint4*>(H), D / 8, rowc, 0, 0, T, cv.n_c, cv.n_cp, reinterpret_cast<uint4*>(Hc));
-    } else if (dtype == 1) {
-        gather_transpose_kernel<uint16_t><<<grid, 256, 0, st>>>(
-            reinterpret_cast<const uint16_t*>(H), D, rowc, 0, 0, T, cv.n_c, D, cv.n_cp, D,
-            reinterpret_cast<uint16_t*>(Hc), D, reinterpret_cast<uint16_t*>(HcT), cv.n_cp);
+void launch_gather_rows(int dtype, const GatherArgs& a, ChunkView cv, hipStream_t st) {
+    const unsigned blocks = (unsigned)ceil_div(cv.n_cp, 4);
+    if (dtype == 1) {                            // D is a multiple of 64, H and W are 16-byte aligned
+        gather_rows_kernel<uint16_t><<<blocks, 256, 0, st>>>(a, cv.n0, cv.n_c, cv.n_cp, 1);
     } else {
-        gather_transpose_kernel<float><<<grid, 256, 0, st>>>(
-            reinterpret_cast<const float*>(H), D, rowc, 0, 0, T, cv.n_c, D, cv.n_cp, D,
-            reinterpret_cast<float*>(Hc), D, reinterpret_cast<float*>(HcT), cv.n_cp);
+        const int vec = a.D % 4 == 0 && (reinterpret_cast<uintptr_t>(a.H) & 15u) == 0 ? 1 : 0;
+        gather_rows_kernel<float><<<blocks, 256, 0, st>>>(a, cv.n0, cv.n_c, cv.n_cp, vec);
     }
 }
 
-void launch_transpose_w(int dtype, const void* W, int32_t V, int32_t D, int32_t Vp, void* WT, hipStream_t st) {
-    dim3 grid((unsigned)ceil_div(D, 64), (unsigned)ceil_div(Vp, 64));
-    if (dtype == 1) {      // D and Vp are multiples of 64 on the bf16 path
-        transpose_bf16_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(W), D, V, nullptr,
-                                                    reinterpret_cast<uint16_t*>(WT), Vp, 1);
-    } else {
-        gather_transpose_kernel<float><<<grid, 256, 0, st>>>(reinterpret_cast<const float*>(W), D, nullptr, 0, 0, V,
-                                                             V, D, Vp, D, nullptr, 0, reinterpret_cast<float*>(WT),
-                                                             Vp);
-    }
-}
-
-void launch_target_logit(int dtype, const void* Hc, const void* W, const int32_t* y, int32_t n_cp, int32_t D,
-                         float* zy, float* bref, int32_t* flag, hipStream_t st) {
-    const unsigned blocks = (unsigned)ceil_div(n_cp, 4);
-    if (dtype == 1)
-        target_logit_kernel<uint16_t><<<blocks, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(Hc),
-                                                              reinterpret_cast<const uint16_t*>(W), y, n_cp, D, zy,
-                                                              bref, flag);
-    else
-        target_logit_kernel<float><<<blocks, 256, 0, st>>>(reinterpret_cast<const float*>(Hc),
-                                                           reinterpret_cast<const float*>(W), y, n_cp, D, zy, bref,
-                                                           flag);
+void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* WT, hipStream_t st) {
+    dim3 grid((unsigned)(D / 64), (unsigned)(Vp / 64));      // D and Vp are multiples of 64 on the bf16 path
+    transpose_bf16_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(W), D, V, nullptr,
+                                                reinterpret_cast<uint16_t*>(WT), Vp, 1);
 }
 
 void launch_combine_exp(const float2* part, int32_t n_tiles, const float* zy, const float* bref, ChunkView cv,
@@ -704,10 +599,11 @@ void launch_token_norm_coef(int32_t Q, int32_t G, const int32_t* comp_len, const
     token_norm_coef_kernel<<<(unsigned)ceil_div(Q, 64), 64, 0, st>>>(Q, G, comp_len, coef, coef_out);
 }
 
-void launch_grad_logits_f32(float* ZG, float* GT, int32_t V, int32_t Vp, const int32_t* y, const float* lse,
-                            const float* c, int32_t n_cp, hipStream_t st) {
-    dim3 grid((unsigned)(Vp / 64), (unsigned)(n_cp / 64));
-    grad_logits_kernel<float, float, f32x8, f32x8><<<grid, 256, 0, st>>>(ZG, GT, V, Vp, y, lse, c, n_cp);
+void launch_grad_logits_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const float* lse, const float* c,
+                            int32_t n_c, hipStream_t st) {
+    const int64_t per_row = ceil_div(Vp / 4, 256);
+    dim3 grid((unsigned)n_c, (unsigned)(per_row < 64 ? per_row : 64));
+    grad_logits_kernel<<<grid, 256, 0, st>>>(ZG, V, Vp, y, lse, c);
 }
 
 void launch_seq_reduce(const SeqReduceArgs& a, hipStream_t st) {

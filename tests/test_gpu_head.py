@@ -136,6 +136,19 @@ def test_vocab_and_token_tails(lib):
     _run_case(lib, case, TOL["f32"])
 
 
+# (workload, loss tokens, D, V): every tile of the fp32 GEMM (32, 64, 128) with remainders in all dimensions, a
+# single column, unaligned rows, K slices with a tail, and dH cut along the vocabulary
+@pytest.mark.parametrize("name,tokens,D,V", [("tiny", 1, 1, 2), ("tiny", None, 33, 3001), ("tiny", 33, 300, 65),
+                                             ("small", 700, 130, 1100), ("small", 1100, 257, 4099)])
+def test_fp32_tiles_and_splits(lib, name, tokens, D, V):
+    case = _case(name, tokens, dtype="f32", D=D, V=V)
+    out, _ = _run_case(lib, case, TOL["f32"])
+    acc = out["dW"].clone()
+    lib.dppo_loss_fwd_bwd(case.H, case.W, case.ids, case.loss_pos, case.loss_cu, case.seq_adv, case.seq_coef,
+                          case.logp_old, case.logp_ref, dW=acc, accumulate_dW=True)
+    assert torch.equal(acc, 2.0 * out["dW"])
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
