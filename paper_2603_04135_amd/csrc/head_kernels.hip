@@ -83,87 +83,96 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t 
 }
 
 // ------------------------------------------------------------------------------------
-// 64 tokens per workgroup, the vocabulary tiles split over 4 wavefronts; each thread folds its
-// tiles into a running (max, sum) pair in one pass, the four pairs of a token meet in LDS.
-__global__ __launch_bounds__(256) void combine_logprob_kernel(const float2* __restrict__ part, int32_t n_tiles,
-                                                              const float* __restrict__ zy, int64_t n0, int32_t n_c,
-                                                              int32_t n_cp, float* __restrict__ lse_chunk,
-                                                              float* __restrict__ logp_out,
-                                                              float* __restrict__ lse_out) {
-    __shared__ float2 red[4][64];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + lane;
-    const float NEG_INF = -__builtin_inff();
-    float m = NEG_INF, s = 0.0f;
-    if (n < n_c) {
-        for (int t = q; t < n_tiles; t += 4) {
-            const float2 p = part[(size_t)t * n_cp + n];
-            if (p.x > m) { s = s * expf(m - p.x) + p.y; m = p.x; }      // exp(-inf) = 0 on the first tile
-            else if (p.x > NEG_INF) s += p.y * expf(p.x - m);
+// Per-tile softmax partials part[tile][n] of 16 tokens per workgroup -> lse and log-prob. The tiles are split over
+// 64 lane groups (16 tokens = one 128-byte line per tile), eight loads in flight per thread; the groups meet by
+// shuffles and in LDS, in a fixed order.
+// Bound by HBM for many tokens (8 bytes per tile and token) and by latency for few: with 64 tokens and 4 groups per
+// workgroup, a thread walked 149 dependent loads and 256 tokens kept four workgroups busy (V = 151936, 33 tokens:
+// 68 us of a 276 us call; now 9 us).
+constexpr int COMBINE_TOK = 16, COMBINE_GROUPS = 64, COMBINE_WAVES = COMBINE_TOK * COMBINE_GROUPS / 64;
+constexpr int COMBINE_UNROLL = 8;
+
+// (max, sum exp(z - max)) of the union of two sets.
+__device__ __forceinline__ float2 join_softmax(float2 a, float2 b) {
+    const float m = fmaxf(a.x, b.x);
+    if (m == -__builtin_inff()) return make_float2(m, 0.0f);
+    return make_float2(m, a.y * expf(a.x - m) + b.y * expf(b.x - m));
+}
+// (max z, sum exp(z - reference)) with one reference per token: the sums just add up.
+__device__ __forceinline__ float2 join_referenced(float2 a, float2 b) { return make_float2(fmaxf(a.x, b.x), a.y + b.y); }
+
+// The token's joined pair, valid in the first COMBINE_TOK threads of the workgroup.
+template <bool REFERENCED>
+__device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part, int32_t n_tiles, int32_t n_cp, int n) {
+    __shared__ float2 red[COMBINE_WAVES][COMBINE_TOK];
+    const int group = threadIdx.x / COMBINE_TOK, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto join = [](float2 a, float2 b) { return REFERENCED ? join_referenced(a, b) : join_softmax(a, b); };
+    const float2 none = make_float2(-__builtin_inff(), 0.0f);
+    float2 r = none;
+    if (n < n_cp) {
+        for (int t0 = group; t0 < n_tiles; t0 += COMBINE_GROUPS * COMBINE_UNROLL) {
+            float2 p[COMBINE_UNROLL];
+#pragma unroll
+            for (int u = 0; u < COMBINE_UNROLL; ++u) {
+                const int t = t0 + u * COMBINE_GROUPS;
+                p[u] = t < n_tiles ? part[(size_t)t * n_cp + n] : none;
+            }
+            float m = r.x, s = 0.0f;
+#pragma unroll
+            for (int u = 0; u < COMBINE_UNROLL; ++u) m = fmaxf(m, p[u].x);
+            const bool any = m != none.x;
+#pragma unroll
+            for (int u = 0; u < COMBINE_UNROLL; ++u) s += REFERENCED ? p[u].y : any ? p[u].y * expf(p[u].x - m) : 0.0f;
+            r = make_float2(m, s + (REFERENCED ? r.y : any ? r.y * expf(r.x - m) : 0.0f));
         }
     }
-    red[q][lane] = make_float2(m, s);
+#pragma unroll
+    for (int off = COMBINE_TOK; off < 64; off <<= 1)
+        r = join(r, make_float2(__shfl_xor(r.x, off, 64), __shfl_xor(r.y, off, 64)));
+    if (lane < COMBINE_TOK) red[wave][lane] = r;
     __syncthreads();
-    if (q != 0 || n >= n_cp) return;
-    if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
-    float mm = NEG_INF;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) mm = fmaxf(mm, red[i][lane].x);
-    float ss = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float2 r = red[i][lane];
-        ss += (r.x == NEG_INF) ? 0.0f : r.y * expf(r.x - mm);
+    if (threadIdx.x < COMBINE_TOK) {
+        r = red[0][threadIdx.x];
+        for (int w = 1; w < COMBINE_WAVES; ++w) r = join(r, red[w][threadIdx.x]);
     }
-    const float lse = mm + logf(ss);
+    return r;
+}
+
+__global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_logprob_kernel(
+    const float2* __restrict__ part, int32_t n_tiles, const float* __restrict__ zy, int64_t n0, int32_t n_c, int32_t n_cp,
+    float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ lse_out) {
+    const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
+    const float2 r = combine_tiles<false>(part, n_tiles, n_cp, n);
+    if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
+    if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
+    const float lse = r.x + logf(r.y);
     lse_chunk[n] = lse;
     logp_out[n0 + n] = zy[n] - lse;
     if (lse_out) lse_out[n0 + n] = lse;
 }
 
-// Same split of the work for the GEMM that stores exponentials: part[tile][n] = (max z, sum of
-// exp(z - bref[n])) with one reference per token, so the sums of the tiles add up and
+// The same for the GEMM that stores exponentials: part[tile][n] = (max z, sum of exp(z - bref[n])),
 // lse = bref + log(sum). With the target logit as reference the sum is 1 / p(target), the stored
 // exponentials reach that size and the row scale c p(target) shrinks by it; beyond 1e15 (a target
 // token with log-prob below about -34.5) the scaled hidden-state rows of the dW operand would
 // approach the bottom of the bf16 range for small loss weights, so the token goes on the redo
 // list instead and is redone against its row maximum.
 constexpr float EXP_SUM_LIMIT = 1e15f;
-__global__ __launch_bounds__(256) void combine_exp_kernel(const float2* __restrict__ part, int32_t n_tiles,
-                                                          const float* __restrict__ zy,
-                                                          const float* __restrict__ bref, int64_t n0, int32_t n_c,
-                                                          int32_t n_cp, float* __restrict__ lse_chunk,
-                                                          float* __restrict__ logp_out, float* __restrict__ mx,
-                                                          int32_t* redo_count, int32_t* __restrict__ redo_list,
-                                                          float* __restrict__ redo_sum) {
-    __shared__ float2 red[4][64];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + lane;
-    float m = -__builtin_inff(), s = 0.0f;
-    if (n < n_cp) {
-#pragma unroll 8
-        for (int t = q; t < n_tiles; t += 4) {
-            const float2 p = part[(size_t)t * n_cp + n];
-            m = fmaxf(m, p.x);
-            s += p.y;
-        }
-    }
-    red[q][lane] = make_float2(m, s);
-    __syncthreads();
-    if (q != 0 || n >= n_cp) return;
-#pragma unroll
-    for (int i = 1; i < 4; ++i) {
-        m = fmaxf(m, red[i][lane].x);
-        s += red[i][lane].y;
-    }
-    mx[n] = m;
+__global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_exp_kernel(
+    const float2* __restrict__ part, int32_t n_tiles, const float* __restrict__ zy, const float* __restrict__ bref, int64_t n0,
+    int32_t n_c, int32_t n_cp, float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ mx,
+    int32_t* redo_count, int32_t* __restrict__ redo_list, float* __restrict__ redo_sum) {
+    const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
+    const float2 r = combine_tiles<true>(part, n_tiles, n_cp, n);
+    if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
+    mx[n] = r.x;
     if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
-    if (!(s < EXP_SUM_LIMIT)) {
+    if (!(r.y < EXP_SUM_LIMIT)) {
         redo_list[atomicAdd(redo_count, 1)] = n;
         redo_sum[n] = 0.0f;
         return;
     }
-    const float lse = bref[n] + logf(s);
+    const float lse = bref[n] + logf(r.y);
     lse_chunk[n] = lse;
     logp_out[n0 + n] = zy[n] - lse;
 }
@@ -543,9 +552,8 @@ void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* W
 void launch_combine_exp(const float2* part, int32_t n_tiles, const float* zy, const float* bref, ChunkView cv,
                         float* lse_chunk, float* logp_out, float* mx, int32_t* redo_count, int32_t* redo_list,
                         float* redo_sum, hipStream_t st) {
-    combine_exp_kernel<<<(unsigned)ceil_div(cv.n_cp, 64), 256, 0, st>>>(part, n_tiles, zy, bref, cv.n0, cv.n_c, cv.n_cp,
-                                                                        lse_chunk, logp_out, mx, redo_count, redo_list,
-                                                                        redo_sum);
+    combine_exp_kernel<<<(unsigned)ceil_div(cv.n_cp, COMBINE_TOK), COMBINE_TOK * COMBINE_GROUPS, 0, st>>>(
+        part, n_tiles, zy, bref, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, mx, redo_count, redo_list, redo_sum);
 }
 
 void launch_exp_redo_rows(const int32_t* redo_count, const int32_t* redo_list, float* redo_sum, const void* Hc,
@@ -574,8 +582,8 @@ void launch_scale_transpose_bf16(const void* Hc, const float* scale, int32_t n_c
 
 void launch_combine_logprob(const float2* part, int32_t n_tiles, const float* zy, ChunkView cv, float* lse_chunk,
                             float* logp_out, float* lse_out, hipStream_t st) {
-    combine_logprob_kernel<<<(unsigned)ceil_div(cv.n_cp, 64), 256, 0, st>>>(part, n_tiles, zy, cv.n0, cv.n_c, cv.n_cp,
-                                                                            lse_chunk, logp_out, lse_out);
+    combine_logprob_kernel<<<(unsigned)ceil_div(cv.n_cp, COMBINE_TOK), COMBINE_TOK * COMBINE_GROUPS, 0, st>>>(
+        part, n_tiles, zy, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, lse_out);
 }
 
 void launch_row_stats_f32(const float* Z, int64_t ldz, int32_t V, const int32_t* y, ChunkView cv, float* lse_chunk,
