@@ -73,6 +73,11 @@ int32_t chunk_max_for(int32_t D, size_t es) {
     return (int32_t)(fit < CHUNK_ALIGN ? CHUNK_ALIGN : (fit > CHUNK_MAX ? CHUNK_MAX : fit));
 }
 constexpr size_t REGION_ALIGN = 256;
+// Up to this many loss tokens the dH GEMM reads W as it lies, [K, N], instead of a transposed blocked copy of it:
+// the GEMM takes 6 % (D = 4096) to 9 % (D = 2560) longer, the copy costs two passes over W. Measured with V =
+// 151936: 0.50 ms saved against 0.02 (300 tokens), 0.11 (2000) and 0.51 (9000) at D = 4096; 0.32 against 0.05,
+// 0.14 and 0.31 (6000) at D = 2560; with V = 32000, D = 1024 they are equal at 5000 tokens.
+constexpr int64_t DIRECT_W_TOKENS = 3072;
 
 struct WsPlan {
     int32_t Vp, n_tiles, n_cp;     // padded vocabulary, row tiles of the vocabulary GEMM, chunk rows
@@ -557,14 +562,15 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     float* clipf = reinterpret_cast<float*>(w + p.o_clip);
     float* seq_tmp = reinterpret_cast<float*>(w + p.o_seq);
 
+    const bool recompute = lp->recompute_logits != 0;
+    const bool direct_w = s.N <= DIRECT_W_TOKENS;
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         launch_fill_zero(dH, (size_t)s.T * s.D * p.es, status, st);
         if (!lp->accumulate_dW && s.N == 0) launch_fill_zero(dW, (size_t)s.V * s.D * 4, nullptr, st);
-        if (s.N > 0 && s.dtype == 1) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
+        if (s.N > 0 && s.dtype == 1 && !direct_w) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
     }
 
-    const bool recompute = lp->recompute_logits != 0;
     const bool seq_level = lp->ratio_level == DPPO_RATIO_SEQUENCE && s.N > 0;
     float* seq_ratio = reinterpret_cast<float*>(w + p.o_sratio);
     auto view = [&](int64_t c) {
@@ -648,7 +654,8 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         if (s.dtype == 1) {
             {
                 StageTimer tm(DPPO_STAGE_DH_GEMM, st);
-                launch_mfma_dh(cus, G, p.Vp, w + p.o_wt, cv.n_c, s.D, row_scale, oh, reinterpret_cast<float*>(w + p.o_dwpart), st);
+                launch_mfma_dh(cus, G, p.Vp, direct_w ? nullptr : w + p.o_wt, W, s.V, cv.n_c, s.D, row_scale, oh,
+                               reinterpret_cast<float*>(w + p.o_dwpart), st);
             }
             {
                 StageTimer tm(DPPO_STAGE_DW_GEMM, st);

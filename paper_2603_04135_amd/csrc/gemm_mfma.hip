@@ -37,14 +37,14 @@ enum { PHASE_LOGITS = 0, PHASE_DH = 1, PHASE_DW = 2 };
 
 template <class Cfg, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS, class Epi>
 void launch(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N, int K, const Epi& epi,
-            hipStream_t st, int tile0 = 0, int n_tiles = -1, int k_parts = 1, int phase_stage = -1) {
+            hipStream_t st, int tile0 = 0, int n_tiles = -1, int k_parts = 1, int phase_stage = -1, int b_rows = 0) {
     const int tiles_m = (int)ceil_div(M, Cfg::BM), tiles_n = (int)ceil_div(N, Cfg::BN);
     if (n_tiles < 0) n_tiles = tiles_m * tiles_n - tile0;
     if (n_tiles <= 0) return;
     unsigned long long* phase = phase_stage >= 0 && k_parts == 1 ? g_phase_counters.load() : nullptr;
     if (phase) phase += 4 * phase_stage;
     gemm_nt_kernel<Cfg, Epi, AM, MAP, BL><<<dim3(n_tiles * k_parts), dim3(Cfg::NT), lds_request<Cfg, Epi>(), st>>>(
-        reinterpret_cast<const uint16_t*>(A), lda, reinterpret_cast<const uint16_t*>(B), ldb, M, N, K, tiles_m,
+        reinterpret_cast<const uint16_t*>(A), lda, reinterpret_cast<const uint16_t*>(B), ldb, b_rows, M, N, K, tiles_m,
         tiles_n, tile0, k_parts, epi, phase);
 }
 
@@ -113,6 +113,7 @@ int mfma_setup(int* compute_units) {
         e = hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDW, A_BLK_KM, WG_RANGES, B_BLK>();
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_BLK>();
+        if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_KM>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogits>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsExp>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsGrad>();
@@ -177,24 +178,33 @@ static int tail_split(int cus, int tiles, int k_slices, const float* partial, in
     return parts < 2 ? 1 : parts;
 }
 
-void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, int32_t n_c, int32_t D, const float* row_scale,
-                    const StoreSpec& out, float* partial, hipStream_t st) {
+namespace {
+template <int BL>
+void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, int b_rows, int32_t n_c, int32_t D,
+               const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st) {
     EpiStoreDH e{nullptr, reinterpret_cast<uint16_t*>(out.C), out.ldc, 0, out.row_map, out.row_base, row_scale, nullptr};
     const int tiles_m = (int)ceil_div(n_c, CfgGrad::BM), tiles_n = (int)ceil_div(D, CfgGrad::BN);
     const int tiles = tiles_m * tiles_n;
     int tail;
     const int parts = tail_split(cus, tiles, Vp / CfgGrad::BK, partial, tail);
     if (parts == 1) {
-        launch<CfgGrad, A_BLK_ROWS, WG_RANGES, B_BLK>(G, Vp, WT, 0, n_c, D, Vp, e, st, 0, -1, 1, PHASE_DH);
+        launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, e, st, 0, -1, 1, PHASE_DH, b_rows);
         return;
     }
-    launch<CfgGrad, A_BLK_ROWS, WG_RANGES, B_BLK>(G, Vp, WT, 0, n_c, D, Vp, e, st, 0, tiles - tail, 1, PHASE_DH);
+    launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, e, st, 0, tiles - tail, 1, PHASE_DH, b_rows);
     EpiStoreDH ep = e;
     ep.partial = partial;
-    launch<CfgGrad, A_BLK_ROWS, WG_RANGES, B_BLK>(G, Vp, WT, 0, n_c, D, Vp, ep, st, tiles - tail, tail, parts);
+    launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, ep, st, tiles - tail, tail, parts, -1, b_rows);
     sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / 16), 256, 0, st>>>(
         partial, tiles - tail, parts, tiles_m, tiles_n, nullptr, out.ldc, n_c, D, 0, reinterpret_cast<uint16_t*>(out.C),
         out.row_map, out.row_base, row_scale);
+}
+}  // namespace
+
+void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, const void* W, int32_t V, int32_t n_c, int32_t D,
+                    const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st) {
+    if (WT) launch_dh<B_BLK>(cus, G, Vp, WT, 0, 0, n_c, D, row_scale, out, partial, st);
+    else launch_dh<B_KM>(cus, G, Vp, W, D, V, n_c, D, row_scale, out, partial, st);
 }
 
 void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t n_cp, int32_t V, int32_t D,

@@ -84,6 +84,9 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const lds_char* __restrict__ p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
 }
 
+// XOR term of a k-row's 16-byte chunks in a k-major slice (see A_BLK_KM).
+__device__ __forceinline__ int km_swz(int krow) { return 4 * (krow & 3) + 2 * ((krow >> 3) & 1); }
+
 // XOR term of the LDS swizzle: logical 16-byte chunk kc of tile row `row` lives at physical chunk
 // kc ^ swz(row). Kinds 0..2: (row >> kind) & (CPR - 1) (kind 0 is the conflict-free choice for
 // BK = 64, kind 2 for BK = 32); kind 3: (row & 7) ^ ((row >> 3) & 1).
@@ -147,7 +150,9 @@ enum { A_ROWS = 0, A_BLK_ROWS = 1, A_BLK_KM = 2 };
 //           row-major inside: the slice a tile loads is one contiguous 32 KB run instead of BN pieces of
 //           128 bytes a row pitch apart (with pitches of 64 KB to 300 KB that costs 5 % of the dH main loop's
 //           cycles and 2.5 % of dW's). N is padded to whole blocks; ldb is not used.
-enum { B_ROWS = 0, B_BLK = 1 };
+//   B_KM    B is [K, N] row-major, ldb = row pitch, with b_rows <= K rows in memory (the last one is read in place of
+//           those beyond: the A operand is zero there); operands are gathered by transposing reads as for A_BLK_KM.
+enum { B_ROWS = 0, B_BLK = 1, B_KM = 2 };
 constexpr int BLK_R = 64, BLK_C = 256;
 __host__ __device__ __forceinline__ size_t blk_offset(int64_t r, int64_t c, int64_t ld) {
     return (size_t)(r / BLK_R) * BLK_R * ld + (size_t)(c / BLK_C) * (BLK_R * BLK_C) + (r % BLK_R) * BLK_C + c % BLK_C;
@@ -175,10 +180,10 @@ __host__ __device__ __forceinline__ void tile_coords(int tile, int tiles_m, int 
 // (k_parts = 1: whole tiles).
 enum { WG_ROUNDS = 0, WG_RANGES = 1 };
 template <class Cfg, class Epi, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS>
-__global__ __launch_bounds__(Cfg::NT) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                          const uint16_t* __restrict__ B, int64_t ldb, int M,
-                                                          int N, int K, int tiles_m, int tiles_n, int tile0,
-                                                          int k_parts, Epi epi, unsigned long long* phase) {
+__global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
+                                                             const uint16_t* __restrict__ B, int64_t ldb, int b_rows, int M,
+                                                             int N, int K, int tiles_m, int tiles_n, int tile0,
+                                                             int k_parts, Epi epi, unsigned long long* phase) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // phase (benchmark aid, normally NULL): 4 counters that every workgroup adds to: shader cycles from
     // its start to the first slice in LDS, in the main loop, in the epilogue, and 1.
@@ -225,6 +230,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_nt_kernel(const uint16_t* __rest
     const int wave_m = wave % Cfg::WGM, wave_n = wave / Cfg::WGM;
     const int bm0 = tm * Cfg::BM, bn0 = tn * Cfg::BN;
 
+    constexpr int B_KM_CPR = Cfg::BN / 8;                       // B_KM: 16-byte chunks per k-row of the slice
     // one pointer per load (A loads first, then B loads)
     const uint16_t* pl[LPS];
 #pragma unroll
@@ -236,8 +242,13 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_nt_kernel(const uint16_t* __rest
             static_assert(!A_KM || (BLK_R % Cfg::BK == 0 && Cfg::BM == BLK_C), "a slice stays inside one block");
             constexpr int CPR_A = Cfg::BM / 8;
             const int krow = ci / CPR_A, pc = ci % CPR_A;
-            const int mc = pc ^ (4 * (krow & 3) + 2 * ((krow >> 3) & 1));
+            const int mc = pc ^ km_swz(krow);
             pl[i] = A + blk_offset(krow, bm0 + mc * 8, lda);
+            continue;
+        }
+        if (BL == B_KM && !isA) {
+            const int col = bn0 + ((ci % B_KM_CPR) ^ km_swz(ci / B_KM_CPR)) * 8;
+            pl[i] = B + (col < N ? col : N - 8);          // (N is a multiple of 64)
             continue;
         }
         const int row = ci / CPR, pc = ci % CPR;
@@ -267,7 +278,12 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_nt_kernel(const uint16_t* __rest
         const bool isA = i >= Cfg::B_LD;
         const int ii = isA ? i - Cfg::B_LD : i;
         char* dst = smem + (isA ? bufa * Cfg::A_BYTES : Cfg::B_RING + bufb * Cfg::B_BYTES) + (ii * Cfg::NW + wave) * 1024;
-        const uint16_t* src = isA ? pl[ii] + koff_a : pl[Cfg::A_LD + ii] + (BL == B_BLK ? koff * Cfg::BN : koff);
+        size_t koff_b = BL == B_BLK ? koff * Cfg::BN : koff;
+        if (BL == B_KM && !isA) {
+            const int k = (int)koff + ((ii * Cfg::NW + wave) * 64 + lane) / B_KM_CPR;
+            koff_b = (size_t)(k < b_rows ? k : b_rows - 1) * ldb;
+        }
+        const uint16_t* src = isA ? pl[ii] + koff_a : pl[Cfg::A_LD + ii] + koff_b;
         __builtin_amdgcn_global_load_lds(DPPO_GPTR(src), DPPO_LPTR(dst), 16, 0, 0);
     };
 
@@ -296,19 +312,37 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_nt_kernel(const uint16_t* __rest
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) a_km[mi] = lane_off + 32 * (mi ^ xl);
     }
+    // B_KM: the same for the B slice, whose wavefront columns are WTN wide (the swizzle reaches over to a neighbour's)
+    constexpr int ROWB_B = Cfg::BN * 2;
+    int b_km[NI];
+    if (BL == B_KM) {
+        static_assert(BL != B_KM || (Cfg::WTN % 16 == 0 && Cfg::BN >= 128), "swizzle of the [K, N] slice");
+        const int s16 = lane & 15;
+        const int xl = 2 * (s16 >> 2) + (frag_q & 1);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            b_km[ni] = (8 * frag_q + (s16 >> 2)) * ROWB_B + 32 * ((wave_n * NI + ni) ^ xl) + ((s16 & 3) >> 1) * 16 + (s16 & 1) * 8;
+    }
+    auto read_km = [](const char* at, int row_bytes) {
+        const lds_char* p = (const lds_char*)at;
+        const s16x4 lo = lds_read_tr16(p);
+        const s16x4 hi = lds_read_tr16(p + 4 * row_bytes);
+        const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return __builtin_bit_cast(bf16x8, v);
+    };
     auto read_a = [&](int slot, const char* st, int kk, int mi) {
         if (A_KM) {
-            const lds_char* p = (const lds_char*)(st + a_km[mi] + kk * MK * ROWB_A);
-            const s16x4 lo = lds_read_tr16(p);
-            const s16x4 hi = lds_read_tr16(p + 4 * ROWB_A);
-            const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            af[slot] = __builtin_bit_cast(bf16x8, v);
+            af[slot] = read_km(st + a_km[mi] + kk * MK * ROWB_A, ROWB_A);
         } else {
             const int kc_off = ((kk * 4 + frag_q) ^ sw) << 4;
             af[slot] = *reinterpret_cast<const bf16x8*>(st + a_base + mi * MB * ROWB + kc_off);
         }
     };
     auto read_b = [&](int set, const char* st, int kk, int ni) {
+        if (BL == B_KM) {
+            bfr[set][ni] = read_km(st + b_km[ni] + kk * MK * ROWB_B, ROWB_B);
+            return;
+        }
         const int kc_off = ((kk * 4 + frag_q) ^ sw) << 4;
         bfr[set][ni] = *reinterpret_cast<const bf16x8*>(st + b_base + ni * MB * ROWB + kc_off);
     };

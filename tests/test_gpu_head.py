@@ -149,6 +149,14 @@ def test_fp32_tiles_and_splits(lib, name, tokens, D, V):
     assert torch.equal(acc, 2.0 * out["dW"])
 
 
+@pytest.mark.parametrize("tokens", [3072, 3073])
+@pytest.mark.parametrize("D,V", [(320, 777), (64, 257)])
+def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
+    # up to 3072 loss tokens the dH GEMM reads W as it lies, beyond a transposed copy: column tiles that are
+    # partly filled, a vocabulary with rows missing from its last slice
+    _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=V), TOL["bf16"])
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
