@@ -258,12 +258,13 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, 
                              bref, lse_c, logp_all, st);
     } else if (s.dtype == 1) {
         float2* part = reinterpret_cast<float2*>(ws + p.o_part);
+        LogitsPart lp;
         {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
-            launch_mfma_logits(W, s.V, s.D, Hc, cv.n_cp, part, st);
+            lp = launch_mfma_logits(W, s.V, s.D, Hc, cv.n_c, cv.n_cp, part, st);
         }
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-        launch_combine_logprob(part, p.n_tiles, zy, cv, lse_c, logp_all, lse_all, st);
+        launch_combine_logprob(part, lp, zy, cv, lse_c, logp_all, lse_all, st);
     } else {
         GemmF32 g{reinterpret_cast<const float*>(Hc), s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
                   reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 1};

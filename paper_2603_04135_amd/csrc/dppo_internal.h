@@ -64,8 +64,10 @@ inline size_t gemm_b_blocked_elems(int64_t rows, int64_t K) {
 }
 // WT = transpose of the bfloat16 W[V, D], columns v >= V zero, in the blocked layout (K = Vp).
 void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* WT, hipStream_t st);
-// lse from per-tile partial (max, sumexp) pairs part[tile][n_cp]; logp = zy - lse.
-void launch_combine_logprob(const float2* part, int32_t n_tiles, const float* zy, ChunkView cv,
+// Softmax pairs of the forward-only vocabulary GEMM: how many row tiles, at which pitch.
+struct LogitsPart { int32_t tiles, pitch; };
+// lse from per-tile partial (max, sumexp) pairs part[tile][pitch]; logp = zy - lse. lse_chunk[n] = 0 for n_c <= n < n_cp.
+void launch_combine_logprob(const float2* part, LogitsPart lp, const float* zy, ChunkView cv,
                             float* lse_chunk, float* logp_out, float* lse_out, hipStream_t st);
 // Statistics of the GEMM that stores exponentials against the per-token reference bref[n]:
 // part[tile][n] = (max z, sum exp(z - bref[n])); lse = bref + log(sum), logp = zy - lse, mx[n] = row
@@ -157,11 +159,14 @@ void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st);
 // returns a dppo status.
 int mfma_setup(int* compute_units);
 // Vocabulary GEMM: rows = vocabulary entries (A = W[V,D]), columns = tokens (B = Hc[n_cp,D]).
-// Writes per-(row tile, token) partial (max, sum exp(z - max)) to part[tile*n_cp + n].
+// Writes per-(row tile, token) partial (max, sum exp(z - max)) to part[tile * pitch + n] for the n_c tokens of the
+// chunk (others may be written up to the pitch); returns how many row tiles at which pitch. They never need
+// more than mfma_logits_row_tiles(V) * n_cp pairs.
 int32_t mfma_logits_row_tiles(int32_t V);
 int32_t mfma_vocab_tile();
-void launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp, float2* part,
-                        hipStream_t st);
+constexpr int32_t LOGITS_FEW_TOKENS = 128;
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_c, int32_t n_cp, float2* part,
+                              hipStream_t st);
 // Same GEMM; stores E[n, v] = exp(z[n, v] - bref[n]) as bf16 (0 for V <= v < Vp) to E, a [n_cp, lde]
 // matrix in the blocked chunk layout (blocks of 64 tokens x 256 vocabulary entries, each
 // contiguous; block (i, j) at element i * 64 * lde + j * 16384); lde = Vp must be a multiple of

@@ -19,6 +19,15 @@ using namespace mfma;
 // is as good (dW) or 0.9 % better (dH) than interleaved rounds.
 typedef PipeCfg<256, 256, 64, 2, 4, 2, 0, 1, 4, 1> CfgBig;
 typedef PipeCfg<256, 256, 64, 2, 4, 2, 0, 1, 1, 1> CfgGrad;
+// Forward-only vocabulary GEMM of few tokens. Up to LOGITS_FEW_TOKENS it is bound by reading W once: 128 vocabulary rows by one
+// column of 96 or 128 tokens, four wavefronts, 72 or 80 KB of LDS, so that two workgroups share a compute unit and
+// one's prologue, barriers and epilogue fall into the other's loads (33 tokens, whole call: V = 151936, D = 2560
+// 222 -> 175 us, D = 4096 361 -> 280 us = W at 4.4 TB/s; V = 32000, D = 1024 35 -> 25 us). 64 columns are no faster
+// than 96 (178 and 303 us: too few MFMAs between a k-step's LDS reads). Beyond, the matrix pipes bound it, and where columns of 192 tokens
+// cover the chunk with as many tiles as columns of 256, a quarter of the products is saved (333 tokens, D = 4096:
+// 478 -> 437 us; 192 tokens 362 -> 347; 520 tokens 658 -> 586).
+template <int BN> using CfgFew = PipeCfg<128, BN, 64, 2, 2, 2, 0, 1, 1, 1>;
+typedef PipeCfg<256, 192, 64, 2, 4, 2, 0, 1, 4, 1> CfgBig192;
 static_assert(CfgGrad::BN == GEMM_B_BLOCK_ROWS && CfgGrad::BK == GEMM_B_BLOCK_K, "blocked B operand = the tile's slices");
 
 // Dynamic LDS of a kernel: the operand slices, or the epilogue's staging area if that is larger.
@@ -115,6 +124,9 @@ int mfma_setup(int* compute_units) {
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_BLK>();
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_KM>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogits>();
+        if (e == hipSuccess) e = allow_lds<CfgBig192, EpiLogits>();
+        if (e == hipSuccess) e = allow_lds<CfgFew<96>, EpiLogits>();
+        if (e == hipSuccess) e = allow_lds<CfgFew<128>, EpiLogits>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsExp>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsGrad>();
         d.status = e == hipSuccess ? (int)DPPO_OK
@@ -131,10 +143,22 @@ void mfma_set_phase_counters(unsigned long long* counters) { g_phase_counters.st
 int32_t mfma_logits_row_tiles(int32_t V) { return (int32_t)ceil_div(V, CfgBig::BM); }
 int32_t mfma_vocab_tile() { return CfgBig::BM; }
 
-void launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp, float2* part,
-                        hipStream_t st) {
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_c, int32_t n_cp, float2* part,
+                              hipStream_t st) {
+    LogitsPart lp{mfma_logits_row_tiles(V), n_cp};
+    if (n_c <= LOGITS_FEW_TOKENS) {
+        // as many pairs in all as with 256-row tiles: twice the row tiles, half the pitch
+        lp = LogitsPart{(int32_t)ceil_div(V, CfgFew<128>::BM), LOGITS_FEW_TOKENS};
+        EpiLogits e{part, lp.pitch};
+        if (n_c <= 96) launch<CfgFew<96>>(W, D, Hc, D, V, 96, D, e, st);
+        else launch<CfgFew<128>>(W, D, Hc, D, V, 128, D, e, st);
+        return lp;
+    }
     EpiLogits e{part, n_cp};
-    launch<CfgBig>(W, D, Hc, D, V, n_cp, D, e, st, 0, -1, 1, PHASE_LOGITS);
+    const int32_t columns = (int32_t)ceil_div(n_c, CfgBig::BN);
+    if (n_c <= columns * CfgBig192::BN) launch<CfgBig192>(W, D, Hc, D, V, columns * CfgBig192::BN, D, e, st);
+    else launch<CfgBig>(W, D, Hc, D, V, n_cp, D, e, st, 0, -1, 1, PHASE_LOGITS);
+    return lp;
 }
 
 int launch_mfma_logits_exp(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp, float2* part,

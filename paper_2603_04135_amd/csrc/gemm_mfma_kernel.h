@@ -125,7 +125,10 @@ struct PipeCfg {
     static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile vs wavefront count");
     static_assert(SA * LPS <= 63, "vmcnt range");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-    static_assert(NI >= 3 && NI <= MI && LPS <= MI, "read and load slots of a k-step");
+    static_assert(NI >= 2 && NI <= MI && LPS <= MI * NI, "read and load slots of a k-step");
+    // MFMA of a k-step behind which load i of a slice is issued: the 3rd of row i, or spread over the step
+    // where the wavefront's sub-tile has too few rows or columns for that
+    static constexpr int load_slot(int i) { return NI >= 3 && LPS <= MI ? i * NI + 2 : i * MI * NI / LPS; }
 };
 
 // Layout of the A operand (template parameter AM):
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                 // works on block (q / NI, q % NI); behind it, in the row of A block mi = q / NI:
                 //   first MFMA of the step: the next step's last A block (into its spare registers),
                 //   2nd MFMA of rows 0 .. NI-1: the next step's B block mi,
-                //   3rd MFMA of rows 0 .. LPS-1: one global load (B loads first),
+                //   MFMAs load_slot(0 .. LPS-1) (3rd of rows 0 .. LPS-1): one global load (B loads first),
                 //   last MFMA of rows 0 .. MI-2: the next step's A block mi, over the one just used.
                 const char* rsa = smem + read_bufa * Cfg::A_BYTES;
                 const char* rsb = smem + Cfg::B_RING + read_bufb * Cfg::B_BYTES;
@@ -437,9 +440,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                         if (ni == 1 && mi < NI) read_b(nxt, rsb, read_kk, mi);
                         if (ni == NI - 1 && mi < MI - 1) read_a(mi, rsa, read_kk, mi);
                     }
-                    if (ni == 2 && mi < LPS) {
-                        if (mi < B_LD) { if (loads_b) issue_load(bufa, bufb, kt + SB, mi); }
-                        else if (loads_a) issue_load(bufa, bufb, kt + SA, mi);
+#pragma unroll
+                    for (int i = 0; i < LPS; ++i) {
+                        if (q != Cfg::load_slot(i)) continue;
+                        if (i < B_LD) { if (loads_b) issue_load(bufa, bufb, kt + SB, i); }
+                        else if (loads_a) issue_load(bufa, bufb, kt + SA, i);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }

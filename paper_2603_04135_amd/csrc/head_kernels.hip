@@ -103,19 +103,19 @@ __device__ __forceinline__ float2 join_referenced(float2 a, float2 b) { return m
 
 // The token's joined pair, valid in the first COMBINE_TOK threads of the workgroup.
 template <bool REFERENCED>
-__device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part, int32_t n_tiles, int32_t n_cp, int n) {
+__device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part, int32_t n_tiles, int32_t pitch, int32_t n_c, int n) {
     __shared__ float2 red[COMBINE_WAVES][COMBINE_TOK];
     const int group = threadIdx.x / COMBINE_TOK, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto join = [](float2 a, float2 b) { return REFERENCED ? join_referenced(a, b) : join_softmax(a, b); };
     const float2 none = make_float2(-__builtin_inff(), 0.0f);
     float2 r = none;
-    if (n < n_cp) {
+    if (n < n_c) {
         for (int t0 = group; t0 < n_tiles; t0 += COMBINE_GROUPS * COMBINE_UNROLL) {
             float2 p[COMBINE_UNROLL];
 #pragma unroll
             for (int u = 0; u < COMBINE_UNROLL; ++u) {
                 const int t = t0 + u * COMBINE_GROUPS;
-                p[u] = t < n_tiles ? part[(size_t)t * n_cp + n] : none;
+                p[u] = t < n_tiles ? part[(size_t)t * pitch + n] : none;
             }
             float m = r.x, s = 0.0f;
 #pragma unroll
@@ -139,10 +139,10 @@ __device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part,
 }
 
 __global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_logprob_kernel(
-    const float2* __restrict__ part, int32_t n_tiles, const float* __restrict__ zy, int64_t n0, int32_t n_c, int32_t n_cp,
-    float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ lse_out) {
+    const float2* __restrict__ part, int32_t n_tiles, int32_t pitch, const float* __restrict__ zy, int64_t n0, int32_t n_c,
+    int32_t n_cp, float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ lse_out) {
     const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
-    const float2 r = combine_tiles<false>(part, n_tiles, n_cp, n);
+    const float2 r = combine_tiles<false>(part, n_tiles, pitch, n_c, n);
     if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
     if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
     const float lse = r.x + logf(r.y);
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_exp_kerne
     int32_t n_c, int32_t n_cp, float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ mx,
     int32_t* redo_count, int32_t* __restrict__ redo_list, float* __restrict__ redo_sum) {
     const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
-    const float2 r = combine_tiles<true>(part, n_tiles, n_cp, n);
+    const float2 r = combine_tiles<true>(part, n_tiles, n_cp, n_c, n);
     if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
     mx[n] = r.x;
     if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
@@ -580,10 +580,10 @@ void launch_scale_transpose_bf16(const void* Hc, const float* scale, int32_t n_c
                                                 reinterpret_cast<uint16_t*>(HcT), n_cp, 1);
 }
 
-void launch_combine_logprob(const float2* part, int32_t n_tiles, const float* zy, ChunkView cv, float* lse_chunk,
+void launch_combine_logprob(const float2* part, LogitsPart lp, const float* zy, ChunkView cv, float* lse_chunk,
                             float* logp_out, float* lse_out, hipStream_t st) {
     combine_logprob_kernel<<<(unsigned)ceil_div(cv.n_cp, COMBINE_TOK), COMBINE_TOK * COMBINE_GROUPS, 0, st>>>(
-        part, n_tiles, zy, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, lse_out);
+        part, lp.tiles, lp.pitch, zy, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, lse_out);
 }
 
 void launch_row_stats_f32(const float* Z, int64_t ldz, int32_t V, const int32_t* y, ChunkView cv, float* lse_chunk,

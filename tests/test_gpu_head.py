@@ -157,6 +157,22 @@ def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
     _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=V), TOL["bf16"])
 
 
+# forward-only token columns of 96, 128, 192 and 256: one token, each width full, one token more
+@pytest.mark.parametrize("tokens", [1, 96, 97, 128, 129, 192, 193, 384, 385])
+@pytest.mark.parametrize("D,V", [(64, 257), (320, 1000)])
+def test_token_columns_of_the_forward(lib, tokens, D, V):
+    case = _case("small", tokens, dtype="bf16", D=D, V=V)
+    ws = lib.alloc_workspace(lib.dppo_workspace_bytes(case.pk["T"], tokens, D, V, 1, 0), DEV)
+    ws.fill_(0xFF)                               # NaN wherever a statistic that nobody wrote is read
+    logp, lse = lib.dppo_token_logprob(case.H, case.W, case.ids, case.loss_pos, ws=ws)
+    # fp32 sums of D products |h w| < 1 in any order: D^2 2^-24 at worst, 2e-2 of that in practice
+    logp_ref, lse_ref = case.oracle_logprob()
+    assert np.abs(logp.cpu().numpy() - logp_ref).max() <= 1e-4
+    assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-4
+    if tokens in (97, 193):                      # the recomputed gradient uses these statistics for the padding too
+        _run_case(lib, case, TOL["bf16"], recompute_logits=True)
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
