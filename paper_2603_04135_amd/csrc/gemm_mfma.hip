@@ -58,9 +58,11 @@ void launch(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N
 }
 
 // Sums the k_parts partial tiles of each of the n_tiles tiles from tile0 on, in part order, into
-// C (overwrite or accumulate). One workgroup per 16 rows of a tile; N and ldc multiples of 4.
+// C (overwrite or accumulate). One workgroup per SUM_ROWS rows of a tile, a 16-byte vector per thread; N and ldc
+// multiples of 4.
 // With Cb != NULL the sums go out as bf16 instead: row m times row_scale[m] (if not NULL) to row
 // row_map[row_base + m] (if not NULL) of Cb.
+constexpr int SUM_ROWS = 4;
 template <class Cfg>
 __global__ __launch_bounds__(256) void sum_partial_tiles_kernel(const float* __restrict__ partial, int tile0,
                                                                 int k_parts, int tiles_m, int tiles_n, float* C,
@@ -72,26 +74,26 @@ __global__ __launch_bounds__(256) void sum_partial_tiles_kernel(const float* __r
     int tm, tn;
     tile_coords<Cfg::GROUP_M>(tile0 + blockIdx.x, tiles_m, tiles_n, tm, tn);
     const float* src = partial + (size_t)blockIdx.x * k_parts * (Cfg::BM * Cfg::BN);
-    for (int i = threadIdx.x; i < 16 * VPR; i += 256) {
-        const int r = blockIdx.y * 16 + i / VPR, cv = i % VPR;
-        const int row = tm * Cfg::BM + r, col = tn * Cfg::BN + cv * 4;
-        if (row >= M || col >= N) continue;
-        f32x4v v = *reinterpret_cast<const f32x4v*>(src + (size_t)r * Cfg::BN + cv * 4);
-        for (int p = 1; p < k_parts; ++p)
-            v += *reinterpret_cast<const f32x4v*>(src + (size_t)p * (Cfg::BM * Cfg::BN) + (size_t)r * Cfg::BN + cv * 4);
-        if (Cb) {
-            const float rs = row_scale ? row_scale[row] : 1.0f;
-            const int64_t orow = row_map ? (int64_t)row_map[row_base + row] : (int64_t)row;
-            const __bf16 b0 = (__bf16)(v[0] * rs), b1 = (__bf16)(v[1] * rs), b2 = (__bf16)(v[2] * rs), b3 = (__bf16)(v[3] * rs);
-            const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, b0) | ((uint32_t)__builtin_bit_cast(uint16_t, b1) << 16);
-            const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, b2) | ((uint32_t)__builtin_bit_cast(uint16_t, b3) << 16);
-            *reinterpret_cast<uint2*>(Cb + (size_t)orow * ldc + col) = make_uint2(lo, hi);
-            continue;
-        }
-        f32x4v* dst = reinterpret_cast<f32x4v*>(C + (size_t)row * ldc + col);
-        if (accumulate) v += *dst;
-        *dst = v;
+    static_assert(SUM_ROWS * VPR == 256, "one vector per thread");
+    const int r = blockIdx.y * SUM_ROWS + threadIdx.x / VPR, cv = threadIdx.x % VPR;
+    const int row = tm * Cfg::BM + r, col = tn * Cfg::BN + cv * 4;
+    if (row >= M || col >= N) return;
+    f32x4v v = *reinterpret_cast<const f32x4v*>(src + (size_t)r * Cfg::BN + cv * 4);
+#pragma unroll 8
+    for (int p = 1; p < k_parts; ++p)
+        v += *reinterpret_cast<const f32x4v*>(src + (size_t)p * (Cfg::BM * Cfg::BN) + (size_t)r * Cfg::BN + cv * 4);
+    if (Cb) {
+        const float rs = row_scale ? row_scale[row] : 1.0f;
+        const int64_t orow = row_map ? (int64_t)row_map[row_base + row] : (int64_t)row;
+        const __bf16 b0 = (__bf16)(v[0] * rs), b1 = (__bf16)(v[1] * rs), b2 = (__bf16)(v[2] * rs), b3 = (__bf16)(v[3] * rs);
+        const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, b0) | ((uint32_t)__builtin_bit_cast(uint16_t, b1) << 16);
+        const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, b2) | ((uint32_t)__builtin_bit_cast(uint16_t, b3) << 16);
+        *reinterpret_cast<uint2*>(Cb + (size_t)orow * ldc + col) = make_uint2(lo, hi);
+        return;
     }
+    f32x4v* dst = reinterpret_cast<f32x4v*>(C + (size_t)row * ldc + col);
+    if (accumulate) v += *dst;
+    *dst = v;
 }
 
 template <class Cfg, class Epi, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS>
@@ -187,15 +189,17 @@ size_t mfma_dw_partial_bytes() { return (size_t)256 * CfgBig::BM * CfgBig::BN * 
 
 // One workgroup per compute unit at a time: the last round of tiles holds tiles % cus of them. If
 // that is at most half the chip, those tiles are cut along K into as many parts as fill it (at
-// most 8, at least 16 slices each), each part writes its partial tile to scratch, and a small
+// least 16 slices each), each part writes its partial tile to scratch, and a small
 // kernel adds the parts up in order (the same sums in a different association; deterministic).
+// The parts of a launch never hold more than one tile per compute unit, so many parts of few tiles cost the sum no
+// more than few parts of many (64 MB in all). With at most 8 parts, 250 tokens of D = 4096 (16 tiles of dH) kept half the
+// chip idle: 437 us, now 290.
 // Returns the number of parts (1 = no split) and the number of tail tiles.
 static int tail_split(int cus, int tiles, int k_slices, const float* partial, int& tail) {
     tail = cus > 0 ? tiles % cus : 0;
     int parts = 1;
     if (partial && tail > 0 && 2 * tail <= cus) {
         parts = cus / tail;
-        if (parts > 8) parts = 8;
         if (parts > k_slices / 16) parts = k_slices / 16;
         if ((size_t)tail * parts * CfgBig::BM * CfgBig::BN * 4 > mfma_dw_partial_bytes()) parts = 1;
     }
@@ -219,7 +223,7 @@ void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, i
     EpiStoreDH ep = e;
     ep.partial = partial;
     launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, ep, st, tiles - tail, tail, parts, -1, b_rows);
-    sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / 16), 256, 0, st>>>(
+    sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / SUM_ROWS), 256, 0, st>>>(
         partial, tiles - tail, parts, tiles_m, tiles_n, nullptr, out.ldc, n_c, D, 0, reinterpret_cast<uint16_t*>(out.C),
         out.row_map, out.row_base, row_scale);
 }
@@ -246,7 +250,7 @@ void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t
     EpiStoreDW ep = e;
     ep.partial = partial;
     launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, ep, st, tiles - tail, tail, parts);
-    sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / 16), 256, 0, st>>>(
+    sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / SUM_ROWS), 256, 0, st>>>(
         partial, tiles - tail, parts, tiles_m, tiles_n, reinterpret_cast<float*>(out.C), out.ldc, V, D, out.accumulate,
         nullptr, nullptr, 0, nullptr);
 }

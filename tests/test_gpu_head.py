@@ -173,6 +173,12 @@ def test_token_columns_of_the_forward(lib, tokens, D, V):
         _run_case(lib, case, TOL["bf16"], recompute_logits=True)
 
 
+@pytest.mark.parametrize("tokens,D", [(40, 64), (256, 320), (257, 64)])
+def test_dh_of_few_tiles_in_many_parts(lib, tokens, D):
+    # 313 slices of the vocabulary against one or two tiles of dH: cut into 19 parts of 16 and 17 slices
+    _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=20001), TOL["bf16"])
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
