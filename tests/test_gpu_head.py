@@ -179,6 +179,19 @@ def test_dh_of_few_tiles_in_many_parts(lib, tokens, D):
     _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=20001), TOL["bf16"])
 
 
+@pytest.mark.parametrize("V", [3, 16384, 16385, 33001])
+def test_fp32_row_statistics(lib, V):
+    # one sweep of the row, one logit more, three sweeps with a ragged end; the padding of the logits holds NaN
+    case = _case("tiny", 40, dtype="f32", D=16, V=V)
+    ws = lib.alloc_workspace(lib.dppo_workspace_bytes(case.pk["T"], case.pk["N"], 16, V, 0, 0), DEV)
+    ws.fill_(0xFF)
+    logp, lse = lib.dppo_token_logprob(case.H, case.W, case.ids, case.loss_pos, ws=ws)
+    # fp32 sums of V positive terms, 64 partial sums and more: a few times 2^-24 of a log-sum of at most 12
+    logp_ref, lse_ref = case.oracle_logprob()
+    assert np.abs(logp.cpu().numpy() - logp_ref).max() <= 1e-5
+    assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-5
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
