@@ -39,22 +39,24 @@ constexpr int lds_request() {
 }
 
 // Launches the tiles [tile0, tile0 + n_tiles) of the tile walk, each cut into k_parts work items
-// along K; n_tiles < 0: all tiles.
+// along K; n_tiles < 0: all tiles. max_workgroups > 0: at most that many workgroups, which take several items each.
 // Tile-phase counters of the benchmark aid (NULL = off): 4 counters per GEMM stage, see gemm_nt_kernel.
 std::atomic<unsigned long long*> g_phase_counters{nullptr};
 enum { PHASE_LOGITS = 0, PHASE_DH = 1, PHASE_DW = 2 };
 
 template <class Cfg, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS, class Epi>
 void launch(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N, int K, const Epi& epi,
-            hipStream_t st, int tile0 = 0, int n_tiles = -1, int k_parts = 1, int phase_stage = -1, int b_rows = 0) {
+            hipStream_t st, int tile0 = 0, int n_tiles = -1, int k_parts = 1, int phase_stage = -1, int b_rows = 0,
+            int max_workgroups = 0) {
     const int tiles_m = (int)ceil_div(M, Cfg::BM), tiles_n = (int)ceil_div(N, Cfg::BN);
     if (n_tiles < 0) n_tiles = tiles_m * tiles_n - tile0;
     if (n_tiles <= 0) return;
     unsigned long long* phase = phase_stage >= 0 && k_parts == 1 ? g_phase_counters.load() : nullptr;
     if (phase) phase += 4 * phase_stage;
-    gemm_nt_kernel<Cfg, Epi, AM, MAP, BL><<<dim3(n_tiles * k_parts), dim3(Cfg::NT), lds_request<Cfg, Epi>(), st>>>(
+    const int items = n_tiles * k_parts, workgroups = max_workgroups > 0 && items > max_workgroups ? max_workgroups : items;
+    gemm_nt_kernel<Cfg, Epi, AM, MAP, BL><<<dim3(workgroups), dim3(Cfg::NT), lds_request<Cfg, Epi>(), st>>>(
         reinterpret_cast<const uint16_t*>(A), lda, reinterpret_cast<const uint16_t*>(B), ldb, b_rows, M, N, K, tiles_m,
-        tiles_n, tile0, k_parts, epi, phase);
+        tiles_n, tile0, k_parts, items, epi, phase);
 }
 
 // Sums the k_parts partial tiles of each of the n_tiles tiles from tile0 on, in part order, into
@@ -243,10 +245,10 @@ void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t
     int tail;
     const int parts = tail_split(cus, tiles, n_cp / CfgGrad::BK, partial, tail);
     if (parts == 1) {
-        launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, -1, 1, PHASE_DW);
+        launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, -1, 1, PHASE_DW, 0, cus);
         return;
     }
-    launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, tiles - tail, 1, PHASE_DW);
+    launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, tiles - tail, 1, PHASE_DW, 0, cus);
     EpiStoreDW ep = e;
     ep.partial = partial;
     launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, ep, st, tiles - tail, tail, parts);

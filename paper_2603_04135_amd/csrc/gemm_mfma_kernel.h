@@ -186,7 +186,7 @@ template <class Cfg, class Epi, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B
 __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                              const uint16_t* __restrict__ B, int64_t ldb, int b_rows, int M,
                                                              int N, int K, int tiles_m, int tiles_n, int tile0,
-                                                             int k_parts, Epi epi, unsigned long long* phase) {
+                                                             int k_parts, int n_items, Epi epi, unsigned long long* phase) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // phase (benchmark aid, normally NULL): 4 counters that every workgroup adds to: shader cycles from
     // its start to the first slice in LDS, in the main loop, in the epilogue, and 1.
@@ -205,71 +205,92 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     // anywhere in the bands, but consecutive rounds of an XCD are neighbours in the walk).
     // The vocabulary GEMM (bands of 4 x 126 tiles) uses rounds: 38 against 45 GB of L2 misses per
     // launch. dH and dW (one-row bands of 10 tiles) use ranges.
-    const int total = gridDim.x;
-    int logical = blockIdx.x;
+    // Where the epilogue leaves the LDS alone (Epi::SWAP), a launch may have fewer workgroups than items: those of an
+    // XCD then walk its range side by side, and a tile's first slices are loaded while the one before is stored.
+    constexpr bool PERSIST = Epi::SWAP;
+    static_assert(!PERSIST || (MAP == WG_RANGES && BL == B_BLK), "walk of a persistent workgroup");
+    int logical = blockIdx.x, item_end = 0, item_step = 0;
     {
         const int bid = blockIdx.x;
         const int xcd = bid % NUM_XCD, idx = bid / NUM_XCD;
         if (MAP == WG_ROUNDS) {
             constexpr int ROUND = NUM_XCD * CU_PER_XCD;
-            if (bid < total / ROUND * ROUND)         // the last, partial round keeps the identity
+            if (bid < n_items / ROUND * ROUND)       // the last, partial round keeps the identity
                 logical = ((idx / CU_PER_XCD) * NUM_XCD + xcd) * CU_PER_XCD + idx % CU_PER_XCD;
         } else {
-            const int per = total / NUM_XCD, rem = total % NUM_XCD;
-            logical = (xcd < rem) ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
+            const int per = n_items / NUM_XCD, rem = n_items % NUM_XCD;
+            const int start = xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per;
+            logical = start + idx;
+            item_end = start + per + (xcd < rem ? 1 : 0);
+            item_step = ((int)gridDim.x - xcd + NUM_XCD - 1) / NUM_XCD;
         }
     }
-    int tm, tn;
-    int kt_lo = 0, kt_hi = K / Cfg::BK, item_tile = logical;
-    if (k_parts != 1) {                          // whole tiles (the common case) skip these divisions
-        item_tile = logical / k_parts;
-        const int k_part = logical - item_tile * k_parts;
-        kt_lo = (int)((int64_t)k_part * (K / Cfg::BK) / k_parts);
-        kt_hi = (int)((int64_t)(k_part + 1) * (K / Cfg::BK) / k_parts);
-    }
-    tile_coords<Cfg::GROUP_M>(tile0 + item_tile, tiles_m, tiles_n, tm, tn);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps LDS targets in SGPRs
     const int wave_m = wave % Cfg::WGM, wave_n = wave / Cfg::WGM;
-    const int bm0 = tm * Cfg::BM, bn0 = tn * Cfg::BN;
+    int tm, tn, bm0, bn0, kt_lo, KT;
 
     constexpr int B_KM_CPR = Cfg::BN / 8;                       // B_KM: 16-byte chunks per k-row of the slice
-    // one pointer per load (A loads first, then B loads)
+    // One pointer per load (A loads first, then B loads). A_BLK_KM with B_BLK: every load of a tile is at a lane offset that holds for all tiles from a wave-uniform address
+    // (the rows of successive loads differ by a multiple of the swizzles' period), which leaves the registers of
+    // the per-load pointers to the epilogue.
     const uint16_t* pl[LPS];
-#pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-        const bool isA = i < Cfg::A_LD;
-        const int ii = isA ? i : i - Cfg::A_LD;
-        const int ci = (ii * Cfg::NW + wave) * 64 + lane;
-        if (A_KM && isA) {
-            static_assert(!A_KM || (BLK_R % Cfg::BK == 0 && Cfg::BM == BLK_C), "a slice stays inside one block");
-            constexpr int CPR_A = Cfg::BM / 8;
-            const int krow = ci / CPR_A, pc = ci % CPR_A;
-            const int mc = pc ^ km_swz(krow);
-            pl[i] = A + blk_offset(krow, bm0 + mc * 8, lda);
-            continue;
-        }
-        if (BL == B_KM && !isA) {
-            const int col = bn0 + ((ci % B_KM_CPR) ^ km_swz(ci / B_KM_CPR)) * 8;
-            pl[i] = B + (col < N ? col : N - 8);          // (N is a multiple of 64)
-            continue;
-        }
-        const int row = ci / CPR, pc = ci % CPR;
-        const int kc = pc ^ swz<CPR, Cfg::SWZ>(row);
-        if (BL == B_BLK && !isA) {
-            pl[i] = B + ((size_t)tn * (K / Cfg::BK) * Cfg::BN + row) * Cfg::BK + kc * 8;
-            continue;
-        }
-        int r = (isA ? bm0 : bn0) + row;
-        const int lim = isA ? M : N;
-        r = r < lim ? r : lim - 1;
-        if (AM == A_BLK_ROWS && isA) {
-            static_assert(AM != A_BLK_ROWS || BLK_C % Cfg::BK == 0, "a slice stays inside one block column");
-            pl[i] = A + blk_offset(r, kc * 8, lda);
-            continue;
-        }
-        pl[i] = (isA ? A : B) + (size_t)r * (isA ? lda : ldb) + kc * 8;
+    constexpr bool UNIFORM = A_KM;
+    static_assert(!A_KM || (BL == B_BLK && BLK_R % Cfg::BK == 0), "a slice stays inside one block");
+    constexpr int A_STEP = Cfg::NT * 8, B_STEP = Cfg::NT * 8;    // elements between successive loads of a slice
+    const uint16_t *ua = nullptr, *ub = nullptr;
+    uint32_t va = 0, vb = 0;
+    if (UNIFORM) {
+        static_assert(!UNIFORM || (Cfg::BM == BLK_C && Cfg::NT * 8 / Cfg::BM % 16 == 0 && Cfg::NT / CPR % 16 == 0), "period of the swizzles");
+        const int krow = tid / (Cfg::BM / 8), row = tid / CPR;
+        va = (uint32_t)(krow * BLK_C + ((tid % (Cfg::BM / 8)) ^ km_swz(krow)) * 8) * 2u;
+        vb = (uint32_t)(row * Cfg::BK + ((tid % CPR) ^ swz<CPR, Cfg::SWZ>(row)) * 8) * 2u;
     }
+    auto locate = [&](int item) __attribute__((always_inline)) {
+        kt_lo = 0;
+        int kt_hi = K / Cfg::BK, item_tile = item;
+        if (k_parts != 1) {                          // whole tiles (the common case) skip these divisions
+            item_tile = item / k_parts;
+            const int k_part = item - item_tile * k_parts;
+            kt_lo = (int)((int64_t)k_part * (K / Cfg::BK) / k_parts);
+            kt_hi = (int)((int64_t)(k_part + 1) * (K / Cfg::BK) / k_parts);
+        }
+        KT = kt_hi - kt_lo;
+        tile_coords<Cfg::GROUP_M>(tile0 + item_tile, tiles_m, tiles_n, tm, tn);
+        bm0 = tm * Cfg::BM; bn0 = tn * Cfg::BN;
+        if (UNIFORM) {
+            ua = A + blk_offset(0, bm0, lda);
+            ub = B + (size_t)tn * (K / Cfg::BK) * (Cfg::BN * Cfg::BK);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < LPS; ++i) {
+            const bool isA = i < Cfg::A_LD;
+            const int ii = isA ? i : i - Cfg::A_LD;
+            const int ci = (ii * Cfg::NW + wave) * 64 + lane;
+            if (BL == B_KM && !isA) {
+                const int col = bn0 + ((ci % B_KM_CPR) ^ km_swz(ci / B_KM_CPR)) * 8;
+                pl[i] = B + (col < N ? col : N - 8);          // (N is a multiple of 64)
+                continue;
+            }
+            const int row = ci / CPR, pc = ci % CPR;
+            const int kc = pc ^ swz<CPR, Cfg::SWZ>(row);
+            if (BL == B_BLK && !isA) {
+                pl[i] = B + ((size_t)tn * (K / Cfg::BK) * Cfg::BN + row) * Cfg::BK + kc * 8;
+                continue;
+            }
+            int r = (isA ? bm0 : bn0) + row;
+            const int lim = isA ? M : N;
+            r = r < lim ? r : lim - 1;
+            if (AM == A_BLK_ROWS && isA) {
+                static_assert(AM != A_BLK_ROWS || BLK_C % Cfg::BK == 0, "a slice stays inside one block column");
+                pl[i] = A + blk_offset(r, kc * 8, lda);
+                continue;
+            }
+            pl[i] = (isA ? A : B) + (size_t)r * (isA ? lda : ldb) + kc * 8;
+        }
+    };
+    locate(logical);
     // Issues load i of slice kt: i < B_LD is a B load into B-ring buffer bufb, the others are A loads
     // into A-ring buffer bufa. B goes first, so that at the next barrier "all but the newest A_LD
     // loads" means: this slice's B loads have landed, its A loads (due one slice later) may not have.
@@ -285,6 +306,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         if (BL == B_KM && !isA) {
             const int k = (int)koff + ((ii * Cfg::NW + wave) * 64 + lane) / B_KM_CPR;
             koff_b = (size_t)(k < b_rows ? k : b_rows - 1) * ldb;
+        }
+        if (UNIFORM) {
+            const char* base = reinterpret_cast<const char*>(isA ? ua + koff_a + ii * A_STEP : ub + koff_b + ii * B_STEP);
+            __builtin_amdgcn_global_load_lds(DPPO_GPTR(base + (isA ? va : vb)), DPPO_LPTR(dst), 16, 0, 0);
+            return;
         }
         const uint16_t* src = isA ? pl[ii] + koff_a : pl[Cfg::A_LD + ii] + koff_b;
         __builtin_amdgcn_global_load_lds(DPPO_GPTR(src), DPPO_LPTR(dst), 16, 0, 0);
@@ -351,137 +377,175 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     };
 
     f32x4 acc[MI][NI];
+    auto clear_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+            for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[mi][ni][j] = 0.0f;
+                for (int j = 0; j < 4; ++j) acc[mi][ni][j] = 0.0f;
+    };
+    clear_acc();
 
-    const int KT = kt_hi - kt_lo;
     constexpr int SA = Cfg::SA, SB = Cfg::SB, A_LD = Cfg::A_LD, B_LD = Cfg::B_LD;
     // Slice kt has its A part in A-ring buffer kt % SA and its B part in B-ring buffer kt % SB. The
     // barrier at the last k-step of slice kt releases both buffers of slice kt, and the loads
     // [B of slice kt+SB, A of slice kt+SA] are issued behind it, in that order. Prologue: the same
     // groups for the virtual slices -SA .. -1.
+    auto prologue_loads = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = -SA; j < 0; ++j) {
-        if (j + SB >= 0 && j + SB < KT) {
+        for (int j = -SA; j < 0; ++j) {
+            if (j + SB >= 0 && j + SB < KT) {
 #pragma unroll
-            for (int i = 0; i < B_LD; ++i) issue_load(0, (j + SB) % SB, j + SB, i);
-        }
-        if (j + SA < KT) {
-#pragma unroll
-            for (int i = 0; i < A_LD; ++i) issue_load((j + SA) % SA, 0, j + SA, B_LD + i);
-        }
-    }
-    // loads issued behind B of slice 0: A of slices 1 .. SA-1 and B of slices 1 .. SB-1
-    if (KT >= SA) wait_loads_then_barrier<(SA - 1) * A_LD + (SB - 1) * B_LD>();
-    else wait_loads_then_barrier<0>();
-    if (phase) pt1 = clock64();
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) read_a(a_slot(mi, 0), smem, 0, mi);
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) read_b(0, smem + Cfg::B_RING, 0, ni);
-
-    // One slice = KK k-steps. STEADY iterations (1 <= kt, kt + SA < KT) have every condition
-    // resolved at compile time, so the whole slice is straight-line code. PAR = parity of the
-    // slice's first k-step (which B register set it computes from); always 0 when KK is even.
-    // At the barrier of slice kt the data of slice kt+1 must have landed; behind its B part were
-    // issued (in steady state) SB-2 whole groups and, if the A ring is deeper, the A part of the
-    // group that brought it.
-    constexpr int STEADY_PENDING = (SB - 2) * LPS + (SA > SB ? A_LD : 0);
-    int bufa = 0, bufb = 0;
-    auto slice = [&](int kt, auto steady_tag, auto parity_tag) __attribute__((always_inline)) {
-        constexpr bool STEADY = decltype(steady_tag)::value;
-        constexpr int PAR = decltype(parity_tag)::value;
-        const int nbufa = (bufa + 1 == SA) ? 0 : bufa + 1;
-        const int nbufb = (bufb + 1 == SB) ? 0 : bufb + 1;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            const int cur = (kk + PAR) & 1, nxt = cur ^ 1;
-            // Issue priority: low in the k-steps that run up to the barrier, high in the one behind it.
-            // The two wavefronts of a SIMD drift apart (the older one wins every issue slot, reaches the
-            // barrier first and idles there while the other one's memory instructions stall with nobody
-            // to fill the matrix pipe); with the lagging wavefront preferred they reach the barrier
-            // together (barrier wait of the leading wavefront 35 % -> 23 % of the loop, 3 % fewer cycles).
-            if (kk == 0) __builtin_amdgcn_s_setprio(0);
-            bool loads_a = false, loads_b = false, reads_here = false;
-            int read_bufa = 0, read_bufb = 0, read_kk = 0;
-            if (kk == KK - 1) {
-                if (STEADY || kt + 1 < KT) {
-                    if (STEADY) wait_loads_then_barrier<STEADY_PENDING>();
-                    else wait_loads_then_barrier<0>();
-                    __builtin_amdgcn_s_setprio(2);
-                    loads_b = STEADY || kt + SB < KT;
-                    loads_a = STEADY || kt + SA < KT;
-                    read_bufa = nbufa; read_bufb = nbufb; read_kk = 0; reads_here = true;
-                }
-            } else {
-                read_bufa = bufa; read_bufb = bufb; read_kk = kk + 1; reads_here = true;
+                for (int i = 0; i < B_LD; ++i) issue_load(0, (j + SB) % SB, j + SB, i);
             }
-            {
-                // Instruction order of a k-step, pinned by scheduling barriers (left to itself the
-                // compiler sinks the reads next to their use and exposes the LDS latency). MFMA q
-                // works on block (q / NI, q % NI); behind it, in the row of A block mi = q / NI:
-                //   first MFMA of the step: the next step's last A block (into its spare registers),
-                //   2nd MFMA of rows 0 .. NI-1: the next step's B block mi,
-                //   MFMAs load_slot(0 .. LPS-1) (3rd of rows 0 .. LPS-1): one global load (B loads first),
-                //   last MFMA of rows 0 .. MI-2: the next step's A block mi, over the one just used.
-                const char* rsa = smem + read_bufa * Cfg::A_BYTES;
-                const char* rsb = smem + Cfg::B_RING + read_bufb * Cfg::B_BYTES;
+            if (j + SA < KT) {
 #pragma unroll
-                for (int q = 0; q < MI * NI; ++q) {
-                    const int mi = q / NI, ni = q % NI;
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a_slot(mi, cur)], bfr[cur][ni], acc[mi][ni], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (reads_here) {
-                        if (q == 0) read_a(a_slot(MI - 1, nxt), rsa, read_kk, MI - 1);
-                        if (ni == 1 && mi < NI) read_b(nxt, rsb, read_kk, mi);
-                        if (ni == NI - 1 && mi < MI - 1) read_a(mi, rsa, read_kk, mi);
-                    }
-#pragma unroll
-                    for (int i = 0; i < LPS; ++i) {
-                        if (q != Cfg::load_slot(i)) continue;
-                        if (i < B_LD) { if (loads_b) issue_load(bufa, bufb, kt + SB, i); }
-                        else if (loads_a) issue_load(bufa, bufb, kt + SA, i);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                for (int i = 0; i < A_LD; ++i) issue_load((j + SA) % SA, 0, j + SA, B_LD + i);
             }
         }
-        bufa = nbufa; bufb = nbufb;
     };
-    typedef std::integral_constant<int, 0> P0;
-    typedef std::integral_constant<int, 1> P1;
-    int kt = 0;
-    if (KT > 0) { slice(0, std::false_type{}, P0{}); kt = 1; }
-    if (KK & 1) {
-        // odd KK: the register-set parity alternates from slice to slice; kt stays odd here, so
-        // slices go in pairs of parity (1, 0)
-        for (; kt + 1 + SA < KT; kt += 2) { slice(kt, std::true_type{}, P1{}); slice(kt + 1, std::true_type{}, P0{}); }
-        for (; kt + 1 < KT; kt += 2) { slice(kt, std::false_type{}, P1{}); slice(kt + 1, std::false_type{}, P0{}); }
-        if (kt < KT) slice(kt, std::false_type{}, P1{});
-    } else {
-        for (; kt + SA < KT; ++kt) slice(kt, std::true_type{}, P0{});
-        for (; kt < KT; ++kt) slice(kt, std::false_type{}, P0{});
-    }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_s_setprio(0);
-    if (phase) pt2 = clock64();
+    prologue_loads();
+    // loads issued behind B of slice 0: A of slices 1 .. SA-1 and B of slices 1 .. SB-1
+    constexpr int HEAD_PENDING = (SA - 1) * A_LD + (SB - 1) * B_LD;
+    // the same at the barrier of slice 0, behind B of slice 1: A of slices 2 .. SA-1 and B of slices 2 .. SB-1
+    constexpr int FIRST_PENDING = (SA - 2) * A_LD + (SB - 2) * B_LD;
+    // Stores of the tile before that a wavefront may still have under way, behind those loads (loads and stores
+    // complete in order and count alike): all of a whole tile's, so that they drain under the first slices.
+    constexpr int STORES = PERSIST ? MI * NI : 0;
+    static_assert(HEAD_PENDING + STORES <= 63, "vmcnt range");
+    bool stores_pending = false;
+    if (KT >= SA) wait_loads_then_barrier<HEAD_PENDING>();
+    else wait_loads_then_barrier<0>();
+    while (true) {
+        if (phase) pt1 = clock64();
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) read_a(a_slot(mi, 0), smem, 0, mi);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) read_b(0, smem + Cfg::B_RING, 0, ni);
 
-    TileCtx c;
-    c.M = M; c.N = N; c.tm = tm; c.tn = tn;
-    c.bm0 = bm0; c.bn0 = bn0;
-    c.m0 = bm0 + wave_m * Cfg::WTM; c.n0 = bn0 + wave_n * Cfg::WTN;
-    c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.item = logical; c.smem = smem;
-    epi.template run<Cfg>(acc, c);
-    if (phase && tid == 0) {
-        const unsigned long long pt3 = clock64();
-        atomicAdd(phase + 0, pt1 - pt0);
-        atomicAdd(phase + 1, pt2 - pt1);
-        atomicAdd(phase + 2, pt3 - pt2);
-        atomicAdd(phase + 3, 1ull);
+        // One slice = KK k-steps. STEADY iterations (1 <= kt, kt + SA < KT) have every condition
+        // resolved at compile time, so the whole slice is straight-line code. PAR = parity of the
+        // slice's first k-step (which B register set it computes from); always 0 when KK is even.
+        // At the barrier of slice kt the data of slice kt+1 must have landed; behind its B part were
+        // issued (in steady state) SB-2 whole groups and, if the A ring is deeper, the A part of the
+        // group that brought it.
+        constexpr int STEADY_PENDING = (SB - 2) * LPS + (SA > SB ? A_LD : 0);
+        int bufa = 0, bufb = 0;
+        auto slice = [&](int kt, auto steady_tag, auto parity_tag) __attribute__((always_inline)) {
+            constexpr bool STEADY = decltype(steady_tag)::value;
+            constexpr int PAR = decltype(parity_tag)::value;
+            const int nbufa = (bufa + 1 == SA) ? 0 : bufa + 1;
+            const int nbufb = (bufb + 1 == SB) ? 0 : bufb + 1;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const int cur = (kk + PAR) & 1, nxt = cur ^ 1;
+                // Issue priority: low in the k-steps that run up to the barrier, high in the one behind it.
+                // The two wavefronts of a SIMD drift apart (the older one wins every issue slot, reaches the
+                // barrier first and idles there while the other one's memory instructions stall with nobody
+                // to fill the matrix pipe); with the lagging wavefront preferred they reach the barrier
+                // together (barrier wait of the leading wavefront 35 % -> 23 % of the loop, 3 % fewer cycles).
+                if (kk == 0) __builtin_amdgcn_s_setprio(0);
+                bool loads_a = false, loads_b = false, reads_here = false;
+                int read_bufa = 0, read_bufb = 0, read_kk = 0;
+                if (kk == KK - 1) {
+                    if (STEADY || kt + 1 < KT) {
+                        if (STEADY) wait_loads_then_barrier<STEADY_PENDING>();
+                        else if (PERSIST && kt == 0 && stores_pending) wait_loads_then_barrier<FIRST_PENDING + STORES>();
+                        else wait_loads_then_barrier<0>();
+                        __builtin_amdgcn_s_setprio(2);
+                        loads_b = STEADY || kt + SB < KT;
+                        loads_a = STEADY || kt + SA < KT;
+                        read_bufa = nbufa; read_bufb = nbufb; read_kk = 0; reads_here = true;
+                    }
+                } else {
+                    read_bufa = bufa; read_bufb = bufb; read_kk = kk + 1; reads_here = true;
+                }
+                {
+                    // Instruction order of a k-step, pinned by scheduling barriers (left to itself the
+                    // compiler sinks the reads next to their use and exposes the LDS latency). MFMA q
+                    // works on block (q / NI, q % NI); behind it, in the row of A block mi = q / NI:
+                    //   first MFMA of the step: the next step's last A block (into its spare registers),
+                    //   2nd MFMA of rows 0 .. NI-1: the next step's B block mi,
+                    //   MFMAs load_slot(0 .. LPS-1) (3rd of rows 0 .. LPS-1): one global load (B loads first),
+                    //   last MFMA of rows 0 .. MI-2: the next step's A block mi, over the one just used.
+                    const char* rsa = smem + read_bufa * Cfg::A_BYTES;
+                    const char* rsb = smem + Cfg::B_RING + read_bufb * Cfg::B_BYTES;
+#pragma unroll
+                    for (int q = 0; q < MI * NI; ++q) {
+                        const int mi = q / NI, ni = q % NI;
+                        acc[mi][ni] = Epi::SWAP
+                            ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[cur][ni], af[a_slot(mi, cur)], acc[mi][ni], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a_slot(mi, cur)], bfr[cur][ni], acc[mi][ni], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (reads_here) {
+                            if (q == 0) read_a(a_slot(MI - 1, nxt), rsa, read_kk, MI - 1);
+                            if (ni == 1 && mi < NI) read_b(nxt, rsb, read_kk, mi);
+                            if (ni == NI - 1 && mi < MI - 1) read_a(mi, rsa, read_kk, mi);
+                        }
+#pragma unroll
+                        for (int i = 0; i < LPS; ++i) {
+                            if (q != Cfg::load_slot(i)) continue;
+                            if (i < B_LD) { if (loads_b) issue_load(bufa, bufb, kt + SB, i); }
+                            else if (loads_a) issue_load(bufa, bufb, kt + SA, i);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            bufa = nbufa; bufb = nbufb;
+        };
+        typedef std::integral_constant<int, 0> P0;
+        typedef std::integral_constant<int, 1> P1;
+        int kt = 0;
+        if (KT > 0) { slice(0, std::false_type{}, P0{}); kt = 1; }
+        if (KK & 1) {
+            // odd KK: the register-set parity alternates from slice to slice; kt stays odd here, so
+            // slices go in pairs of parity (1, 0)
+            for (; kt + 1 + SA < KT; kt += 2) { slice(kt, std::true_type{}, P1{}); slice(kt + 1, std::true_type{}, P0{}); }
+            for (; kt + 1 < KT; kt += 2) { slice(kt, std::false_type{}, P1{}); slice(kt + 1, std::false_type{}, P0{}); }
+            if (kt < KT) slice(kt, std::false_type{}, P1{});
+        } else {
+            for (; kt + SA < KT; ++kt) slice(kt, std::true_type{}, P0{});
+            for (; kt < KT; ++kt) slice(kt, std::false_type{}, P0{});
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_s_setprio(0);
+        if (phase) pt2 = clock64();
+
+        TileCtx c;
+        c.M = M; c.N = N; c.tm = tm; c.tn = tn;
+        c.bm0 = bm0; c.bn0 = bn0;
+        c.m0 = bm0 + wave_m * Cfg::WTM; c.n0 = bn0 + wave_n * Cfg::WTN;
+        c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.item = logical; c.smem = smem;
+        const bool more = PERSIST && logical + item_step < item_end;
+        if (more) {
+            logical += item_step;
+            locate(logical);
+            prologue_loads();
+            // the waits below count on every store being issued behind these loads
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        epi.template run<Cfg>(acc, c);
+        unsigned long long pt3 = 0;
+        if (phase) pt3 = clock64();
+        if (phase && tid == 0) {
+            atomicAdd(phase + 0, pt1 - pt0);
+            atomicAdd(phase + 1, pt2 - pt1);
+            atomicAdd(phase + 2, pt3 - pt2);
+            atomicAdd(phase + 3, 1ull);
+        }
+        if (!more) return;
+        pt0 = pt3;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        clear_acc();
+        bufa = 0; bufb = 0;
+        // a tile over the edge issues fewer stores than a whole one
+        stores_pending = KT >= SA && c.bm0 + Cfg::BM <= M && c.bn0 + Cfg::BN <= N;
+        if (stores_pending) wait_loads_then_barrier<HEAD_PENDING + STORES>();
+        else wait_loads_then_barrier<0>();
     }
 }
 
@@ -490,10 +554,12 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
 // ---------------------------------------------------------------------------------------
 // Store of the accumulators. KIND 0 (dW): float output, overwrite or accumulate. KIND 1 (dH):
 // bf16 output, optional row scatter through row_map.
-// dW is a read-modify-write of 256 KB per tile; straight from the accumulator layout it would be
-// 4-byte accesses in 64-byte runs, so the tile goes through LDS (free after the main loop) in two
-// halves of BM/2 rows = the rows of one wavefront row, and leaves as 16-byte accesses that cover
-// whole 1 KB output rows. The sums are the same numbers in the same order.
+// dW is a read-modify-write of 256 KB per tile. With the MFMA operands swapped (SWAP) a lane's four accumulators are four
+// neighbouring columns, so the tile leaves the registers in 16-byte accesses of 64-byte runs, and 16 old values per lane
+// are in flight together. The LDS stays free for the next tile's first slices (see gemm_nt_kernel). Against a
+// tile staged through LDS by workgroups of one tile each, dW added to what is there: 250 tokens of D = 4096,
+// V = 151936 1.41 -> 1.08 ms, 650 tokens 1.84 -> 1.53, 1300 of D = 2560 1.55 -> 1.35, 8600 5.38 -> 5.30;
+// overwritten: 250 tokens 0.80 -> 0.78, 650 1.26 -> 1.22, the longer ones the same. Streaming stores: 12 % slower.
 template <int KIND>
 struct EpiStore {
     float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map; int64_t row_base;
@@ -504,45 +570,41 @@ struct EpiStore {
     template <class Cfg>
     __device__ __forceinline__ void run(f32x4 (&acc)[Cfg::MI][Cfg::NI], const TileCtx& c) const {
         if (KIND == 0) {
-            static_assert(KIND != 0 || Cfg::WGM == 2, "one half of the tile per wavefront row");
+            // accumulator lane: vocabulary row lane % 16, columns 4 (lane / 16) .. + 3 of each block
             typedef float f32x4v __attribute__((ext_vector_type(4)));
-            constexpr int PITCH = Cfg::BN * 4 + 16;           // bytes per staged row
-            constexpr int HALF = Cfg::BM / 2;
-            constexpr int VPR = Cfg::BN / 4;                   // float4 per row
-            constexpr int RPP = Cfg::NT / VPR;                 // rows per pass
+            const int64_t ld = partial ? Cfg::BN : ldc;
+            float* base = partial ? partial + (size_t)c.item * (Cfg::BM * Cfg::BN) : Cf + (size_t)c.bm0 * ldc + c.bn0;
+            const int rows = partial ? Cfg::BM : c.M - c.bm0, cols = partial ? Cfg::BN : c.N - c.bn0;
+            const bool add = accumulate && !partial;
+            const int r0 = c.wave_m * Cfg::WTM + (c.lane & 15), c0 = c.wave_n * Cfg::WTN + 4 * (c.lane >> 4);
+            float* p = base + (size_t)r0 * ld + c0;
+            auto store = [&](auto full_tag) __attribute__((always_inline)) {
+                constexpr bool FULL = decltype(full_tag)::value;
+                constexpr int GROUP = 4;                            // block rows whose old values are in flight together
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (c.wave_m == h) {
+                for (int m0 = 0; m0 < Cfg::MI; m0 += GROUP) {
+                    f32x4v old[GROUP][Cfg::NI];
+                    if (add) {
 #pragma unroll
-                    for (int mi = 0; mi < Cfg::MI; ++mi)
+                        for (int g = 0; g < GROUP; ++g)
+#pragma unroll
+                            for (int ni = 0; ni < Cfg::NI; ++ni)
+                                if (FULL || (r0 + (m0 + g) * MB < rows && c0 + ni * MB < cols))
+                                    old[g][ni] = *reinterpret_cast<const f32x4v*>(p + (size_t)((m0 + g) * MB) * ld + ni * MB);
+                    }
+#pragma unroll
+                    for (int g = 0; g < GROUP; ++g)
 #pragma unroll
                         for (int ni = 0; ni < Cfg::NI; ++ni)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                const int r = mi * MB + acc_row(c.lane, j);
-                                const int col = c.wave_n * Cfg::WTN + ni * MB + acc_col(c.lane);
-                                *reinterpret_cast<float*>(c.smem + r * PITCH + col * 4) = acc[mi][ni][j];
+                            if (FULL || (r0 + (m0 + g) * MB < rows && c0 + ni * MB < cols)) {
+                                f32x4v v = acc[m0 + g][ni];
+                                if (add) v += old[g][ni];
+                                *reinterpret_cast<f32x4v*>(p + (size_t)((m0 + g) * MB) * ld + ni * MB) = v;
                             }
                 }
-                __syncthreads();
-                const int cv = c.tid % VPR;
-                const int col = c.bn0 + cv * 4;
-#pragma unroll 4
-                for (int r = c.tid / VPR; r < HALF; r += RPP) {
-                    const int row = c.bm0 + h * HALF + r;
-                    if (partial) {
-                        *reinterpret_cast<f32x4v*>(partial + (size_t)c.item * (Cfg::BM * Cfg::BN) +
-                                                   (size_t)(h * HALF + r) * Cfg::BN + cv * 4) =
-                            *reinterpret_cast<const f32x4v*>(c.smem + r * PITCH + cv * 16);
-                    } else if (row < c.M && col < c.N) {
-                        f32x4v v = *reinterpret_cast<const f32x4v*>(c.smem + r * PITCH + cv * 16);
-                        f32x4v* dst = reinterpret_cast<f32x4v*>(Cf + (size_t)row * ldc + col);
-                        if (accumulate) v += *dst;
-                        *dst = v;
-                    }
-                }
-                __syncthreads();
-            }
+            };
+            if (rows >= Cfg::BM && cols >= Cfg::BN) store(std::true_type{});
+            else store(std::false_type{});
             return;
         }
         if (partial) {       // K-split launch: the raw fp32 tile, row-major, to this work item's slot
@@ -578,7 +640,8 @@ struct EpiStore {
 
     // KIND 0 needs N and ldc to be multiples of 4 and C 16-byte aligned (checked by the launcher).
     template <class Cfg>
-    static constexpr int lds_bytes() { return KIND == 0 ? (Cfg::BM / 2) * (Cfg::BN * 4 + 16) : 0; }
+    static constexpr int lds_bytes() { return 0; }
+    static constexpr bool SWAP = KIND == 0;
 };
 typedef EpiStore<0> EpiStoreDW;
 typedef EpiStore<1> EpiStoreDH;
@@ -670,6 +733,7 @@ struct EpiLogits {
 
     template <class Cfg>
     static constexpr int lds_bytes() { return Cfg::WGM * Cfg::BN * 8; }
+    static constexpr bool SWAP = false;
 };
 
 // Rows = vocabulary entries, columns = tokens. What the backward pass needs of the logits is the
@@ -789,6 +853,7 @@ struct EpiLogitsExp {
 
     template <class Cfg>
     static constexpr int lds_bytes() { return Cfg::BN * (Cfg::BM * 2 + 16) + Cfg::WGM * Cfg::BN * 8; }
+    static constexpr bool SWAP = false;
 };
 
 // Rows = vocabulary entries, columns = tokens: softmax-gradient entries straight from the logits,
@@ -835,6 +900,7 @@ struct EpiLogitsGrad {
 
     template <class Cfg>
     static constexpr int lds_bytes() { return Cfg::BN * (Cfg::BM * 2 + 16); }
+    static constexpr bool SWAP = false;
 };
 
 }  // namespace mfma

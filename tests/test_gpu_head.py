@@ -192,6 +192,19 @@ def test_fp32_row_statistics(lib, V):
     assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-5
 
 
+@pytest.mark.parametrize("tokens", [40, 300, 700])
+@pytest.mark.parametrize("D,V", [(1088, 33000), (512, 70000)])
+def test_dw_tiles_walked_by_resident_workgroups(lib, tokens, D, V):
+    # 645 and 548 tiles of dW for 256 workgroups, the last column or row of them partly filled, K of 4, 8 and 12 slices
+    case = _case("small", tokens, dtype="bf16", D=D, V=V)
+    out, _ = _run_case(lib, case, TOL["bf16"])
+    old = torch.randn(V, D, device=DEV)
+    acc = old.clone()
+    lib.dppo_loss_fwd_bwd(case.H, case.W, case.ids, case.loss_pos, case.loss_cu, case.seq_adv, case.seq_coef,
+                          case.logp_old, case.logp_ref, dW=acc, accumulate_dW=True)
+    assert torch.equal(acc, old + out["dW"])
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
