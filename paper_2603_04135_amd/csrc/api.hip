@@ -637,9 +637,12 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
                                  lse_c, ta.c_chunk, cv, G, p.Vp, scale, st);
             row_scale = scale;
         }
+        // dW sums over the chunk's tokens up to whole slices of its GEMM, not up to the chunk's padding (V = 151936,
+        // D = 4096, whole call: 33 tokens, one slice instead of four, 1.43 -> 1.16 ms; 300 tokens 1.99 -> 1.85 ms)
+        const int32_t n_sum = round_up32(cv.n_c, GEMM_B_BLOCK_K);
         if (s.dtype == 1) {
             StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-            launch_scale_transpose_bf16(wc + p.o_hc, row_scale, cv.n_cp, s.D, wc + p.o_hct, st);
+            launch_scale_transpose_bf16(wc + p.o_hc, row_scale, n_sum, s.D, wc + p.o_hct, st);
         }
 
         // dH rows of the chunk: diag(row_scale) G[n_c, Vp] * WT[D, Vp]^T, scattered to the loss rows of dH
@@ -660,7 +663,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
             }
             {
                 StageTimer tm(DPPO_STAGE_DW_GEMM, st);
-                launch_mfma_dw(cus, G, p.Vp, wc + p.o_hct, cv.n_cp, s.V, s.D, ow,
+                launch_mfma_dw(cus, G, p.Vp, wc + p.o_hct, n_sum, s.V, s.D, ow,
                                reinterpret_cast<float*>(w + p.o_dwpart), st);
             }
         } else {

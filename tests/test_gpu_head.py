@@ -205,6 +205,14 @@ def test_dw_tiles_walked_by_resident_workgroups(lib, tokens, D, V):
     assert torch.equal(acc, old + out["dW"])
 
 
+@pytest.mark.parametrize("tokens", [1, 64, 65, 128, 192, 193, 321])
+def test_dw_sums_over_whole_slices_of_tokens(lib, tokens):
+    # one to six slices of 64 tokens, whatever the chunk is padded to; 270 tiles for 256 resident workgroups
+    case = _case("small", tokens, dtype="bf16", D=320, V=34500)
+    _run_case(lib, case, TOL["bf16"])
+    _run_case(lib, case, TOL["bf16"], recompute_logits=True)
+
+
 def test_long_chunk_with_few_output_tiles(lib):
     # 8400 loss tokens against a dW of 8 x 1 tiles: the dW GEMM's last (only) round of tiles is
     # nearly empty, so its tiles are cut along the token axis and summed by the second kernel
