@@ -1,0 +1,57 @@
+"""What the compiler made of the kernels: properties of the gfx950 assembly that the sources rely on and that no result
+shows. Every source is compiled to assembly with the flags the library is built with."""
+import os
+import re
+
+import pytest
+
+from paper_2603_04135_amd import build as B
+
+
+@pytest.fixture(scope="module")
+def asm(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm")
+    texts = {}
+
+    def get(src):
+        if src not in texts:
+            path = str(out / src.replace(".hip", ".s"))
+            B._run([B._hipcc(), *B.COMMON_FLAGS, *B.PER_FILE_FLAGS.get(src, []), "--offload-device-only", "-S",
+                    os.path.join(B.CSRC, src), "-o", path])
+            with open(path) as f:
+                texts[src] = f.read()
+        return texts[src]
+
+    return get
+
+
+def _functions(text):
+    """Mangled kernel name -> its lines."""
+    out = {}
+    for m in re.finditer(r"^(_Z\w+):[^\n]*\n(.*?)^\.Lfunc_end", text, flags=re.S | re.M):
+        out[m.group(1)] = m.group(2).splitlines()
+    return out
+
+
+@pytest.fixture(scope="module")
+def dw_kernel(asm):
+    found = [lines for name, lines in _functions(asm("gemm_mfma.hip")).items()
+             if "gemm_nt_kernel" in name and "EpiStoreILi0E" in name]
+    assert len(found) == 1
+    return found[0]
+
+
+def _waits_for_memory(line):
+    return "s_waitcnt" in line and "vmcnt" in line
+
+
+def test_whole_dw_tile_is_overwritten_without_a_wait(dw_kernel):
+    """The 32 stores of a tile that overwrites dW follow each other: no wait for the next tile's slices between them."""
+    longest = run = 0
+    for line in dw_kernel:
+        if "global_store_dwordx4" in line:
+            run += 1
+            longest = max(longest, run)
+        elif _waits_for_memory(line) or "s_cbranch" in line or line.startswith(".LBB") or "global_load" in line:
+            run = 0
+    assert longest == 32
