@@ -581,30 +581,43 @@ struct EpiStore {
             // store of a tile that is overwritten too.
             auto store = [&](auto full_tag, auto add_tag) __attribute__((always_inline)) {
                 constexpr bool FULL = decltype(full_tag)::value, ADD = decltype(add_tag)::value;
-                constexpr int GROUP = 4;                            // block rows whose old values are in flight together
                 // The stores of an overwritten tile start when the next tile's slices have landed: mixed with those loads
                 // they take longer (V = 151936, D = 4096, dW stage of 250 tokens 0.835 ms mixed, 0.806 behind them; 40
                 // tokens 0.485 and 0.481; the same from 1300 tokens on).
                 if constexpr (!ADD) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                if constexpr (FULL) {
+                    constexpr int GROUP = 4;                        // block rows whose old values are in flight together
 #pragma unroll
-                for (int m0 = 0; m0 < Cfg::MI; m0 += GROUP) {
-                    f32x4v old[GROUP][Cfg::NI];
-                    if (ADD) {
+                    for (int m0 = 0; m0 < Cfg::MI; m0 += GROUP) {
+                        f32x4v old[GROUP][Cfg::NI];
+                        if (ADD) {
+#pragma unroll
+                            for (int g = 0; g < GROUP; ++g)
+#pragma unroll
+                                for (int ni = 0; ni < Cfg::NI; ++ni)
+                                    old[g][ni] = *reinterpret_cast<const f32x4v*>(p + (size_t)((m0 + g) * MB) * ld + ni * MB);
+                        }
 #pragma unroll
                         for (int g = 0; g < GROUP; ++g)
 #pragma unroll
-                            for (int ni = 0; ni < Cfg::NI; ++ni)
-                                if (FULL || (r0 + (m0 + g) * MB < rows && c0 + ni * MB < cols))
-                                    old[g][ni] = *reinterpret_cast<const f32x4v*>(p + (size_t)((m0 + g) * MB) * ld + ni * MB);
-                    }
-#pragma unroll
-                    for (int g = 0; g < GROUP; ++g)
-#pragma unroll
-                        for (int ni = 0; ni < Cfg::NI; ++ni)
-                            if (FULL || (r0 + (m0 + g) * MB < rows && c0 + ni * MB < cols)) {
+                            for (int ni = 0; ni < Cfg::NI; ++ni) {
                                 f32x4v v = acc[m0 + g][ni];
                                 if (ADD) v += old[g][ni];
                                 *reinterpret_cast<f32x4v*>(p + (size_t)((m0 + g) * MB) * ld + ni * MB) = v;
+                            }
+                    }
+                } else {
+                    // a tile over the edge: every old value is loaded and used under one condition, so that no load can be
+                    // under way behind it (the compiler would wait for it at the head of the next tile, and for the stores too)
+#pragma unroll
+                    for (int mi = 0; mi < Cfg::MI; ++mi)
+#pragma unroll
+                        for (int ni = 0; ni < Cfg::NI; ++ni)
+                            if (r0 + mi * MB < rows && c0 + ni * MB < cols) {
+                                f32x4v* dst = reinterpret_cast<f32x4v*>(p + (size_t)(mi * MB) * ld + ni * MB);
+                                f32x4v v = acc[mi][ni];
+                                if (ADD) v += *dst;
+                                *dst = v;
                             }
                 }
             };

@@ -55,3 +55,11 @@ def test_whole_dw_tile_is_overwritten_without_a_wait(dw_kernel):
         elif _waits_for_memory(line) or "s_cbranch" in line or line.startswith(".LBB") or "global_load" in line:
             run = 0
     assert longest == 32
+
+
+def test_dw_tile_begins_while_the_stores_of_the_one_before_are_under_way(dw_kernel):
+    """From the head of the tile loop to the first product there is no wait for memory: the counted wait in front of
+    it leaves the stores of the tile before outstanding."""
+    head = next(i for i, line in enumerate(dw_kernel) if "Loop Header: Depth=1" in line and "Inner" not in line)
+    first = next(i for i in range(head, len(dw_kernel)) if "v_mfma" in dw_kernel[i])
+    assert not [line for line in dw_kernel[head:first] if _waits_for_memory(line)]
