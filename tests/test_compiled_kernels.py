@@ -63,3 +63,10 @@ def test_dw_tile_begins_while_the_stores_of_the_one_before_are_under_way(dw_kern
     head = next(i for i, line in enumerate(dw_kernel) if "Loop Header: Depth=1" in line and "Inner" not in line)
     first = next(i for i in range(head, len(dw_kernel)) if "v_mfma" in dw_kernel[i])
     assert not [line for line in dw_kernel[head:first] if _waits_for_memory(line)]
+
+
+@pytest.mark.parametrize("src", ["gemm_f32.hip", "gemm_mfma.hip", "head_kernels.hip", "pack.hip", "select.hip"])
+def test_no_kernel_spills_vector_registers(asm, src):
+    text = asm(src)
+    spills = dict(re.findall(r"\.name: +(_Z\w+)\n.*?\.vgpr_spill_count: (\d+)\n", text, flags=re.S))
+    assert spills and {k: n for k, n in spills.items() if n != "0"} == {}
