@@ -88,6 +88,7 @@ struct WsPlan {
     // region offsets
     size_t o_wt, o_logp, o_ell, o_kl, o_clip, o_seq, o_sratio, o_hc, o_hct, o_part, o_zg, o_fpart, o_y, o_rowc, o_zy, o_lse, o_c;
     size_t o_bref, o_mx, o_scale, o_redo_list, o_redo_sum, o_redo_count, o_dwpart;   // bf16 backward only
+    bool direct_w;                 // bf16 backward: the dH GEMM reads W as it lies, no transposed copy is written or reserved
     int f32_parts;                 // float32: parts the K dimension of the dH GEMM may be cut into (scratch for their sums)
     size_t total;
 };
@@ -106,7 +107,8 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, REGION_ALIGN); return o; };
     const size_t N = (size_t)s.N;
-    p.o_wt = take(bwd && s.dtype == 1 ? gemm_b_blocked_elems(s.D, p.Vp) * p.es : 0);
+    p.direct_w = s.N <= DIRECT_W_TOKENS;
+    p.o_wt = take(bwd && s.dtype == 1 && !p.direct_w ? gemm_b_blocked_elems(s.D, p.Vp) * p.es : 0);
     p.o_logp = take(bwd ? N * 4 : 0);   // log-probs of the batch when the caller wants none back
     p.o_ell = take(bwd ? N * 4 : 0);
     p.o_kl = take(bwd ? N * 4 : 0);
@@ -564,12 +566,11 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     float* seq_tmp = reinterpret_cast<float*>(w + p.o_seq);
 
     const bool recompute = lp->recompute_logits != 0;
-    const bool direct_w = s.N <= DIRECT_W_TOKENS;
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         launch_fill_zero(dH, (size_t)s.T * s.D * p.es, status, st);
         if (!lp->accumulate_dW && s.N == 0) launch_fill_zero(dW, (size_t)s.V * s.D * 4, nullptr, st);
-        if (s.N > 0 && s.dtype == 1 && !direct_w) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
+        if (s.N > 0 && s.dtype == 1 && !p.direct_w) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
     }
 
     const bool seq_level = lp->ratio_level == DPPO_RATIO_SEQUENCE && s.N > 0;
@@ -658,7 +659,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         if (s.dtype == 1) {
             {
                 StageTimer tm(DPPO_STAGE_DH_GEMM, st);
-                launch_mfma_dh(cus, G, p.Vp, direct_w ? nullptr : w + p.o_wt, W, s.V, cv.n_c, s.D, row_scale, oh,
+                launch_mfma_dh(cus, G, p.Vp, p.direct_w ? nullptr : w + p.o_wt, W, s.V, cv.n_c, s.D, row_scale, oh,
                                reinterpret_cast<float*>(w + p.o_dwpart), st);
             }
             {

@@ -157,6 +157,25 @@ def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
     _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=V), TOL["bf16"])
 
 
+@pytest.mark.parametrize("tokens", [300, 3072])
+def test_direct_w_in_the_smallest_workspace(lib, tokens):
+    # no room for a transposed copy of W: nothing may be written in its place, and chunks of 256 tokens give the result of
+    # one chunk up to summation order
+    case = _case("small", tokens, dtype="bf16", D=320, V=777)
+    T, N = case.pk["T"], case.pk["N"]
+    out, _ = _run_case(lib, case, TOL["bf16"])
+    nbytes = lib.dppo_workspace_min_bytes(T, N, 320, 777, 1, True)
+    buf = lib.alloc_workspace(nbytes + 4096, DEV)
+    buf.fill_(0x5A)
+    small = lib.dppo_loss_fwd_bwd(case.H, case.W, case.ids, case.loss_pos, case.loss_cu, case.seq_adv, case.seq_coef,
+                                  case.logp_old, case.logp_ref, ws=buf[:nbytes])
+    torch.cuda.synchronize()
+    assert bool((buf[nbytes:] == 0x5A).all())
+    assert torch.equal(small["logp"], out["logp"])
+    assert rel_fro(to_np64(small["dH"]), to_np64(out["dH"])) <= 1e-3
+    assert rel_fro(to_np64(small["dW"]), to_np64(out["dW"])) <= 1e-5
+
+
 # forward-only token columns of 96, 128, 192 and 256: one token, each width full, one token more
 @pytest.mark.parametrize("tokens", [1, 96, 97, 128, 129, 192, 193, 384, 385])
 @pytest.mark.parametrize("D,V", [(64, 257), (320, 1000)])

@@ -84,6 +84,32 @@ def test_workspace_sizes(lib):
     assert 0 < fwd < mn < rec < 40 * 2**30
 
 
+@pytest.mark.parametrize("D,V", [(64, 257), (2560, 151936), (4096, 151936)])
+@pytest.mark.parametrize("backward", [1, 2])
+def test_transposed_w_is_reserved_only_for_calls_that_write_it(lib, D, V, backward):
+    """The blocked transpose of W is in the workspace of a bfloat16 loss call from some token count on, and in none
+    below it: the sizes grow by per-token arrays except for one step of exactly that copy."""
+    from paper_2603_04135_amd.binding import HeadShape
+
+    def smallest(N):
+        return lib.dppo_workspace_min_bytes(ctypes.byref(HeadShape(20000, N, D, V, 1)), backward)
+
+    lo, hi = 2048, 20000                         # lo without the copy, hi with it
+    wt = (D + 255) // 256 * 256 * ((V + 255) // 256 * 256) * 2
+    per_token = 4 * 8 * 20000 + 16 * 256         # eight fp32 arrays of N and their alignment
+    assert wt <= smallest(hi) - smallest(lo) <= wt + per_token
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if smallest(mid) - smallest(lo) < wt:
+            lo = mid
+        else:
+            hi = mid
+    assert wt <= smallest(hi) - smallest(lo) <= wt + 16 * 256
+    for N in (1, 300, 2048):                     # well below the step: less than the copy alone
+        if wt > 1 << 29:
+            assert smallest(N) < wt
+
+
 def test_validation_paths_under_host_sanitizers(tmp_path):
     """Builds the library's host code with AddressSanitizer and UndefinedBehaviorSanitizer (host side only; the
     device code is compiled as always) together with tests/abi_host_check.c, a plain-C driver that walks every
