@@ -73,11 +73,13 @@ int32_t chunk_max_for(int32_t D, size_t es) {
     return (int32_t)(fit < CHUNK_ALIGN ? CHUNK_ALIGN : (fit > CHUNK_MAX ? CHUNK_MAX : fit));
 }
 constexpr size_t REGION_ALIGN = 256;
-// Up to this many loss tokens the dH GEMM reads W as it lies, [K, N], instead of a transposed blocked copy of it:
-// the GEMM takes 6 % (D = 4096) to 9 % (D = 2560) longer, the copy costs two passes over W. Measured with V =
-// 151936: 0.50 ms saved against 0.02 (300 tokens), 0.11 (2000) and 0.51 (9000) at D = 4096; 0.32 against 0.05,
-// 0.14 and 0.31 (6000) at D = 2560; with V = 32000, D = 1024 they are equal at 5000 tokens.
-constexpr int64_t DIRECT_W_TOKENS = 3072;
+// Up to 4096 + D loss tokens the dH GEMM reads W as it lies, [K, N], instead of a transposed blocked copy of it: the GEMM
+// takes longer, by a share that falls with D, and the copy costs two passes over W. The line lies below every crossing
+// measured. Whole call, copy / W as it lies: D = 512, V = 151936 4000 tokens 1.861 / 1.825 ms, 5000 2.283 / 2.287; D = 1024,
+// V = 32000 4000 tokens 0.723 / 0.720, 5000 0.866 / 0.870; D = 2048, V = 50000 6000 tokens 2.988 / 2.974, 7000 3.363 /
+// 3.364; D = 2560, V = 151936 6000 tokens 10.69 / 10.64, 7000 12.31 / 12.33; D = 4096, V = 151936 2000 tokens 6.58 / 6.11,
+// 8000 21.77 / 21.61, 12000 32.23 / 32.22.
+bool reads_w_directly(int64_t N, int32_t D) { return N <= 4096 + (int64_t)D; }
 
 struct WsPlan {
     int32_t Vp, n_tiles, n_cp;     // padded vocabulary, row tiles of the vocabulary GEMM, chunk rows
@@ -107,7 +109,7 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, REGION_ALIGN); return o; };
     const size_t N = (size_t)s.N;
-    p.direct_w = s.N <= DIRECT_W_TOKENS;
+    p.direct_w = reads_w_directly(s.N, s.D);
     p.o_wt = take(bwd && s.dtype == 1 && !p.direct_w ? gemm_b_blocked_elems(s.D, p.Vp) * p.es : 0);
     p.o_logp = take(bwd ? N * 4 : 0);   // log-probs of the batch when the caller wants none back
     p.o_ell = take(bwd ? N * 4 : 0);

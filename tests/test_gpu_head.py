@@ -157,6 +157,13 @@ def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
     _run_case(lib, _case("small", tokens, dtype="bf16", D=D, V=V), TOL["bf16"])
 
 
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("D,V", [(320, 777), (64, 257)])
+def test_dh_on_both_sides_of_the_transposed_copy(lib, over, D, V):
+    # the last token count whose dH reads W as it lies, and the first with a transposed copy
+    _run_case(lib, _case("small", 4096 + D + over, dtype="bf16", D=D, V=V), TOL["bf16"])
+
+
 @pytest.mark.parametrize("tokens", [300, 3072])
 def test_direct_w_in_the_smallest_workspace(lib, tokens):
     # no room for a transposed copy of W: nothing may be written in its place, and chunks of 256 tokens give the result of

@@ -105,6 +105,7 @@ def test_transposed_w_is_reserved_only_for_calls_that_write_it(lib, D, V, backwa
         else:
             hi = mid
     assert wt <= smallest(hi) - smallest(lo) <= wt + 16 * 256
+    assert hi == 4096 + D + 1                    # the last call that reads W as it lies has 4096 + D loss tokens
     for N in (1, 300, 2048):                     # well below the step: less than the copy alone
         if wt > 1 << 29:
             assert smallest(N) < wt
