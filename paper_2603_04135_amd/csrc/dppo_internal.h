@@ -163,6 +163,10 @@ int mfma_setup(int* compute_units);
 // chunk (others may be written up to the pitch); returns how many row tiles at which pitch. They never need
 // more than mfma_logits_row_tiles(V) * n_cp pairs.
 int32_t mfma_logits_row_tiles(int32_t V);
+// Parts along K that the dH and dW GEMMs cut each of the `tail` tiles of their last round into (1 = whole tiles), and the
+// K slices of the dH GEMM.
+int mfma_tail_parts(int cus, int tail, int k_slices);
+int mfma_dh_slices(int32_t V);
 int32_t mfma_vocab_tile();
 constexpr int32_t LOGITS_FEW_TOKENS = 128;
 LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_c, int32_t n_cp, float2* part,

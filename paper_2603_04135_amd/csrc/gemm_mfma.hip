@@ -196,16 +196,19 @@ size_t mfma_dw_partial_bytes() { return (size_t)256 * CfgBig::BM * CfgBig::BN * 
 // The parts of a launch never hold more than one tile per compute unit, so many parts of few tiles cost the sum no
 // more than few parts of many (64 MB in all). With at most 8 parts, 250 tokens of D = 4096 (16 tiles of dH) kept half the
 // chip idle: 437 us, now 290.
+int mfma_tail_parts(int cus, int tail, int k_slices) {
+    if (tail <= 0 || 2 * tail > cus) return 1;
+    int parts = cus / tail;
+    if (parts > k_slices / 16) parts = k_slices / 16;
+    if ((size_t)tail * parts * CfgBig::BM * CfgBig::BN * 4 > mfma_dw_partial_bytes()) parts = 1;
+    return parts < 2 ? 1 : parts;
+}
+int mfma_dh_slices(int32_t V) { return mfma_logits_row_tiles(V) * (CfgBig::BM / CfgGrad::BK); }
+
 // Returns the number of parts (1 = no split) and the number of tail tiles.
 static int tail_split(int cus, int tiles, int k_slices, const float* partial, int& tail) {
     tail = cus > 0 ? tiles % cus : 0;
-    int parts = 1;
-    if (partial && tail > 0 && 2 * tail <= cus) {
-        parts = cus / tail;
-        if (parts > k_slices / 16) parts = k_slices / 16;
-        if ((size_t)tail * parts * CfgBig::BM * CfgBig::BN * 4 > mfma_dw_partial_bytes()) parts = 1;
-    }
-    return parts < 2 ? 1 : parts;
+    return partial ? mfma_tail_parts(cus, tail, k_slices) : 1;
 }
 
 namespace {

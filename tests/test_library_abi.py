@@ -111,6 +111,22 @@ def test_transposed_w_is_reserved_only_for_calls_that_write_it(lib, D, V, backwa
             assert smallest(N) < wt
 
 
+@pytest.mark.parametrize("N,D,V,chunk", [(33100, 320, 1000, 16640), (47500, 320, 1000, 23808),
+                                         (115000, 4096, 32000, 12800), (310000, 2560, 151936, 25856)])
+def test_chunk_size_prices_the_split_that_is_launched(lib, N, D, V, chunk):
+    """Chunk of the recommended workspace: the tiles of the last dH round are cut along the vocabulary only where it has
+    slices for that (16 a part): 33100 tokens of V = 1000, 16 slices in all, take two chunks, not the three that a
+    last round at an eighth of its cost would make best."""
+    from paper_2603_04135_amd.binding import HeadShape
+    hs = HeadShape(N, N, D, V, 1)
+    rec, smallest = (f(ctypes.byref(hs), 1) for f in (lib.dppo_workspace_bytes, lib.dppo_workspace_min_bytes))
+    rows = (V + 255) // 256
+    d_pad = (D + 255) // 256 * 256
+    # gathered rows, their transpose, softmax pairs, exponentials, ten words
+    per_token = 2 * D + 2 * d_pad + 8 * rows + 2 * 256 * rows + 40
+    assert rec - smallest == (chunk - 256) * per_token
+
+
 def test_validation_paths_under_host_sanitizers(tmp_path):
     """Builds the library's host code with AddressSanitizer and UndefinedBehaviorSanitizer (host side only; the
     device code is compiled as always) together with tests/abi_host_check.c, a plain-C driver that walks every
