@@ -218,6 +218,62 @@ def test_fp32_row_statistics(lib, V):
     assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-5
 
 
+def _logits_as_given(dtype, z, tokens):
+    """H, W and ids of `tokens` positions that all have exactly the logits z (bfloat16: rounded): W holds them in its
+    first column, H picks that column. Targets walk down the vocabulary from its last entry."""
+    V, D = len(z), 64 if dtype == torch.bfloat16 else 1
+    W = torch.zeros((V, D), dtype=dtype, device=DEV)
+    W[:, 0] = torch.as_tensor(z, device=DEV).to(dtype)
+    H = torch.zeros((tokens, D), dtype=dtype, device=DEV)
+    H[:, 0] = 1.0
+    ids = ((V - 1 - torch.arange(tokens, device=DEV, dtype=torch.int64) * 997) % V).to(torch.int32)
+    return H, W, ids, to_np64(W[:, 0])
+
+
+# one workgroup column of 96, 192 and 256 tokens; V: 71 and 142 softmax tiles against 64 lane groups of the combination,
+# for float32 three sweeps of a row
+@pytest.mark.parametrize("dtype,tokens,V", [(torch.bfloat16, 5, 18001), (torch.bfloat16, 130, 18001), (torch.bfloat16, 250, 18001),
+                                            (torch.float32, 5, 33001)])
+@pytest.mark.parametrize("kind", ["tile", "most", "lowest", "all", "nan", "inf"])
+def test_logits_that_are_not_finite(lib, dtype, tokens, V, kind):
+    """Vocabulary entries at minus infinity or at the type's lowest value carry no weight, also where they fill a softmax
+    tile, all tiles but one, or a whole sweep; a NaN entry and an entry at plus infinity make lse and log-prob NaN."""
+    z = np.random.default_rng(V).normal(size=V)
+    if kind == "tile":
+        z[256:512] = -np.inf                     # one tile of the 256-row and two of the 128-row GEMM
+    elif kind == "most":
+        z[:17920] = -np.inf                      # float32: the whole first sweep of 16384
+    elif kind == "lowest":
+        z[: V // 2] = float(torch.finfo(dtype).min)
+    elif kind == "all":
+        z[:] = -np.inf
+    elif kind == "nan":
+        z[300] = np.nan
+    elif kind == "inf":
+        z[V - 2] = np.inf
+    H, W, ids, z64 = _logits_as_given(dtype, z, tokens)
+    logp, lse = lib.dppo_token_logprob(H, W, ids, None)
+    one, cu = torch.ones(1, device=DEV), torch.tensor([0, tokens], dtype=torch.int32, device=DEV)
+    zeros = torch.zeros(tokens, device=DEV)
+    out = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, zeros, zeros)
+    torch.cuda.synchronize()
+    got = [logp.cpu().numpy().astype(np.float64), out["logp"].cpu().numpy().astype(np.float64)]
+    lse = lse.cpu().numpy().astype(np.float64)
+    if kind in ("all", "nan", "inf"):
+        assert np.isnan(got[0]).all() and np.isnan(got[1]).all()
+        assert np.isnan(lse).all() or (kind == "all" and (lse == -np.inf).all())
+        return
+    m = z64.max()
+    want = m + np.log(np.exp(z64 - m).sum())
+    # fp32 sums of at most 33001 positive terms in two levels and fp32 exponentials: below 32 2^-24 of a log-sum of 11
+    assert np.abs(lse - want).max() <= 32 * 2.0 ** -24 * 11
+    want = z64[ids.cpu().numpy()] - want
+    far = want < -1e30
+    for g in got:
+        assert np.abs(g[~far] - want[~far]).max() <= 32 * 2.0 ** -24 * 20
+        assert (g[far] < -1e30).all()
+
+
 @pytest.mark.parametrize("tokens", [40, 300, 700])
 @pytest.mark.parametrize("D,V", [(1088, 33000), (512, 70000)])
 def test_dw_tiles_walked_by_resident_workgroups(lib, tokens, D, V):
