@@ -218,12 +218,6 @@ int plan_for(const dppo_head_shape& s, bool bwd, size_t ws_bytes, int cus, WsPla
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-struct Regions {
-    char* base;
-    const WsPlan& p;
-    template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
-};
-
 // Forward statistics of one chunk: Hc, targets, log-probs, lse. `ws` is the base of the set of
 // per-chunk regions to use (the workspace itself for set 0); no per-call region is touched. With keep_z the chunk's logits
 // stay in the workspace for the backward pass: as float32 logits (float32 path), or as bf16 exponentials against the per-token reference left in the bref region (bf16 path).
@@ -650,14 +644,14 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
 
         // dH rows of the chunk: diag(row_scale) G[n_c, Vp] * WT[D, Vp]^T, scattered to the loss rows of dH
         StoreSpec oh;
-        oh.out_bf16 = s.dtype == 1; oh.accumulate = 0; oh.ldc = s.D;
+        oh.accumulate = 0; oh.ldc = s.D;
         // the scatter goes through the chunk's clamped rows, so it stays inside dH whatever loss_pos holds
-        if (loss_pos) { oh.C = dH; oh.row_map = reinterpret_cast<const int32_t*>(wc + p.o_rowc); oh.row_base = 0; }
-        else { oh.C = reinterpret_cast<char*>(dH) + (size_t)cv.n0 * s.D * p.es; oh.row_map = nullptr; oh.row_base = 0; }
+        if (loss_pos) { oh.C = dH; oh.row_map = reinterpret_cast<const int32_t*>(wc + p.o_rowc); }
+        else { oh.C = reinterpret_cast<char*>(dH) + (size_t)cv.n0 * s.D * p.es; oh.row_map = nullptr; }
         // dW[v, d] (+)= sum_n G[n, v] HcT[d, n]
         StoreSpec ow;
-        ow.C = dW; ow.ldc = s.D; ow.out_bf16 = 0; ow.accumulate = (first && !lp->accumulate_dW) ? 0 : 1;
-        ow.row_map = nullptr; ow.row_base = 0;
+        ow.C = dW; ow.ldc = s.D; ow.accumulate = (first && !lp->accumulate_dW) ? 0 : 1;
+        ow.row_map = nullptr;
         if (s.dtype == 1) {
             {
                 StageTimer tm(DPPO_STAGE_DH_GEMM, st);

@@ -134,12 +134,11 @@ void launch_seq_reduce(const SeqReduceArgs& a, hipStream_t st);
 // Output description of C[M,N] = A[M,K] B[N,K]^T.
 struct StoreSpec {
     void* C; int64_t ldc;
-    int32_t out_bf16;          // 0: float output, 1: bf16 output
     int32_t accumulate;        // add to existing contents (float output only)
-    const int32_t* row_map;    // output row = row_map[row_base + m] if not NULL
-    int64_t row_base;
+    const int32_t* row_map;    // output row = row_map[m] if not NULL
 };
 // fp32 GEMM of any size (gemm_f32.hip): A is [M, K] with pitch lda, or [K, M] if a_km; B likewise [N, K] or [K, N].
+// A k-major A goes with a k-major B (dW): the other pairing has no instance.
 // Output row m is row row_map[m] of C if row_map is not NULL. With `partial` (scratch of max_parts * M * N floats)
 // the K dimension may be cut into up to max_parts parts whose sums are added up in a fixed order.
 struct GemmF32 {

@@ -223,8 +223,7 @@ void launch_cfg(const GemmF32& p, int parts, hipStream_t st) {
     g.slices_per_part = (int)ceil_div(ceil_div(p.K, Cfg::BK), parts);
     g.C = p.C; g.ldc = p.ldc; g.accumulate = p.accumulate; g.row_map = p.row_map; g.partial = p.partial;
     const unsigned grid = (unsigned)(ceil_div(p.M, Cfg::BM) * g.tiles_n * parts);
-    if (p.a_km && p.b_km) gemm_f32_kernel<Cfg, true, true><<<grid, Cfg::NT, 0, st>>>(g);
-    else if (p.a_km) gemm_f32_kernel<Cfg, true, false><<<grid, Cfg::NT, 0, st>>>(g);
+    if (p.a_km) gemm_f32_kernel<Cfg, true, true><<<grid, Cfg::NT, 0, st>>>(g);
     else if (p.b_km) gemm_f32_kernel<Cfg, false, true><<<grid, Cfg::NT, 0, st>>>(g);
     else gemm_f32_kernel<Cfg, false, false><<<grid, Cfg::NT, 0, st>>>(g);
 }

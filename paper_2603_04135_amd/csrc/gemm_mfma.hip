@@ -17,8 +17,8 @@ using namespace mfma;
 // consecutive tiles and run in the same round (bands of 4 x 10 tiles straddle the rounds of 32:
 // dH +1.6 %, dW +1.2 % in time); with such bands a contiguous range of rows per XCD (WG_RANGES)
 // is as good (dW) or 0.9 % better (dH) than interleaved rounds.
-typedef PipeCfg<256, 256, 64, 2, 4, 2, 0, 1, 4, 1> CfgBig;
-typedef PipeCfg<256, 256, 64, 2, 4, 2, 0, 1, 1, 1> CfgGrad;
+typedef PipeCfg<256, 256, 2, 4, 2, 4, 1> CfgBig;
+typedef PipeCfg<256, 256, 2, 4, 2, 1, 1> CfgGrad;
 // Forward-only vocabulary GEMM of few tokens. Up to LOGITS_FEW_TOKENS it is bound by reading W once: 128 vocabulary rows by one
 // column of 96 or 128 tokens, four wavefronts, 72 or 80 KB of LDS, so that two workgroups share a compute unit and
 // one's prologue, barriers and epilogue fall into the other's loads (33 tokens, whole call: V = 151936, D = 2560
@@ -26,8 +26,8 @@ typedef PipeCfg<256, 256, 64, 2, 4, 2, 0, 1, 1, 1> CfgGrad;
 // than 96 (178 and 303 us: too few MFMAs between a k-step's LDS reads). Beyond, the matrix pipes bound it, and where columns of 192 tokens
 // cover the chunk with as many tiles as columns of 256, a quarter of the products is saved (333 tokens, D = 4096:
 // 478 -> 437 us; 192 tokens 362 -> 347; 520 tokens 658 -> 586).
-template <int BN> using CfgFew = PipeCfg<128, BN, 64, 2, 2, 2, 0, 1, 1, 1>;
-typedef PipeCfg<256, 192, 64, 2, 4, 2, 0, 1, 4, 1> CfgBig192;
+template <int BN> using CfgFew = PipeCfg<128, BN, 2, 2, 2, 1, 1>;
+typedef PipeCfg<256, 192, 2, 4, 2, 4, 1> CfgBig192;
 static_assert(CfgGrad::BN == GEMM_B_BLOCK_ROWS && CfgGrad::BK == GEMM_B_BLOCK_K, "blocked B operand = the tile's slices");
 
 // Dynamic LDS of a kernel: the operand slices, or the epilogue's staging area if that is larger.
@@ -63,14 +63,14 @@ void launch(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N
 // C (overwrite or accumulate). One workgroup per SUM_ROWS rows of a tile, a 16-byte vector per thread; N and ldc
 // multiples of 4.
 // With Cb != NULL the sums go out as bf16 instead: row m times row_scale[m] (if not NULL) to row
-// row_map[row_base + m] (if not NULL) of Cb.
+// row_map[m] (if not NULL) of Cb.
 constexpr int SUM_ROWS = 4;
 template <class Cfg>
 __global__ __launch_bounds__(256) void sum_partial_tiles_kernel(const float* __restrict__ partial, int tile0,
                                                                 int k_parts, int tiles_m, int tiles_n, float* C,
                                                                 int64_t ldc, int M, int N, int accumulate,
                                                                 uint16_t* Cb, const int32_t* __restrict__ row_map,
-                                                                int64_t row_base, const float* __restrict__ row_scale) {
+                                                                const float* __restrict__ row_scale) {
     typedef float f32x4v __attribute__((ext_vector_type(4)));
     constexpr int VPR = Cfg::BN / 4;
     int tm, tn;
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void sum_partial_tiles_kernel(const float* __r
         v += *reinterpret_cast<const f32x4v*>(src + (size_t)p * (Cfg::BM * Cfg::BN) + (size_t)r * Cfg::BN + cv * 4);
     if (Cb) {
         const float rs = row_scale ? row_scale[row] : 1.0f;
-        const int64_t orow = row_map ? (int64_t)row_map[row_base + row] : (int64_t)row;
+        const int64_t orow = row_map ? (int64_t)row_map[row] : (int64_t)row;
         const __bf16 b0 = (__bf16)(v[0] * rs), b1 = (__bf16)(v[1] * rs), b2 = (__bf16)(v[2] * rs), b3 = (__bf16)(v[3] * rs);
         const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, b0) | ((uint32_t)__builtin_bit_cast(uint16_t, b1) << 16);
         const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, b2) | ((uint32_t)__builtin_bit_cast(uint16_t, b3) << 16);
@@ -215,7 +215,7 @@ namespace {
 template <int BL>
 void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, int b_rows, int32_t n_c, int32_t D,
                const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st) {
-    EpiStoreDH e{nullptr, reinterpret_cast<uint16_t*>(out.C), out.ldc, 0, out.row_map, out.row_base, row_scale, nullptr};
+    EpiStoreDH e{nullptr, reinterpret_cast<uint16_t*>(out.C), out.ldc, 0, out.row_map, row_scale, nullptr};
     const int tiles_m = (int)ceil_div(n_c, CfgGrad::BM), tiles_n = (int)ceil_div(D, CfgGrad::BN);
     const int tiles = tiles_m * tiles_n;
     int tail;
@@ -230,7 +230,7 @@ void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, i
     launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, ep, st, tiles - tail, tail, parts, -1, b_rows);
     sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / SUM_ROWS), 256, 0, st>>>(
         partial, tiles - tail, parts, tiles_m, tiles_n, nullptr, out.ldc, n_c, D, 0, reinterpret_cast<uint16_t*>(out.C),
-        out.row_map, out.row_base, row_scale);
+        out.row_map, row_scale);
 }
 }  // namespace
 
@@ -242,7 +242,7 @@ void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, const vo
 
 void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t n_cp, int32_t V, int32_t D,
                     const StoreSpec& out, float* partial, hipStream_t st) {
-    EpiStoreDW e{reinterpret_cast<float*>(out.C), nullptr, out.ldc, out.accumulate, nullptr, 0, nullptr, nullptr};
+    EpiStoreDW e{reinterpret_cast<float*>(out.C), nullptr, out.ldc, out.accumulate, nullptr, nullptr, nullptr};
     const int tiles_m = (int)ceil_div(V, CfgGrad::BM), tiles_n = (int)ceil_div(D, CfgGrad::BN);
     const int tiles = tiles_m * tiles_n;
     int tail;
@@ -257,7 +257,7 @@ void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t
     launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, ep, st, tiles - tail, tail, parts);
     sum_partial_tiles_kernel<CfgGrad><<<dim3(tail, CfgGrad::BM / SUM_ROWS), 256, 0, st>>>(
         partial, tiles - tail, parts, tiles_m, tiles_n, reinterpret_cast<float*>(out.C), out.ldc, V, D, out.accumulate,
-        nullptr, nullptr, 0, nullptr);
+        nullptr, nullptr, nullptr);
 }
 
 // Register-only loop of the GEMMs' MFMA instruction (8 wavefronts per compute unit, 32 independent

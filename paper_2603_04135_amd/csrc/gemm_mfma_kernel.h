@@ -22,7 +22,7 @@
 // lanes that go together are {0-7, 24-31}, {8-15, 16-23}, {32-39, 56-63}, {40-47, 48-55}. With the
 // 16x16x32 operand layout (lane l: tile row l % 16, k-chunk l / 16) these are tile rows 0-7 at
 // chunk c with rows 8-15 at chunk c ^ 1, which the plain swizzle chunk ^ (row & 7) keeps apart
-// (kind 0; the bank-conflict counter reads 0). A global_load_lds instruction always writes 64
+// (the bank-conflict counter reads 0). A global_load_lds instruction always writes 64
 // lanes x 16 bytes contiguously, so the swizzle is applied on the global-address side: each lane
 // fetches the chunk that belongs at the LDS position it will be written to.
 //
@@ -88,25 +88,19 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const lds_char* __restrict__ p) {
 __device__ __forceinline__ int km_swz(int krow) { return 4 * (krow & 3) + 2 * ((krow >> 3) & 1); }
 
 // XOR term of the LDS swizzle: logical 16-byte chunk kc of tile row `row` lives at physical chunk
-// kc ^ swz(row). Kinds 0..2: (row >> kind) & (CPR - 1) (kind 0 is the conflict-free choice for
-// BK = 64, kind 2 for BK = 32); kind 3: (row & 7) ^ ((row >> 3) & 1).
-template <int CPR, int SWZ> __device__ __forceinline__ int swz(int row) {
-    if (SWZ == 3) return ((row & 7) ^ ((row >> 3) & 1)) & (CPR - 1);
-    return (row >> SWZ) & (CPR - 1);
-}
+// kc ^ swz(row).
+template <int CPR> __device__ __forceinline__ int swz(int row) { return row & (CPR - 1); }
 
-// BM x BN x BK tile, WGM x WGN wavefronts, STAGES slices of B and STAGES + AX slices of A in
+// BM x BN x 64 tile, WGM x WGN wavefronts, STAGES slices of B and STAGES + AX slices of A in
 // flight (A is the operand that streams from HBM in all three GEMMs of the path, B the one that
 // stays cache-resident; with 2 + 1 stages of 32 KB A slices and 2 of B the 160 KB of LDS are used
-// up and the A loads get two slice times to land instead of one), swizzle kind SWZ; SPREAD must be
-// 1 (all loads of a slice are issued in the k-step that frees their buffers); GROUP_M tile rows
-// form one band of the tile walk.
-template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int STAGES_, int SWZ_, int SPREAD_, int GROUP_M_, int AX_ = 0>
+// up and the A loads get two slice times to land instead of one). All loads of a slice are issued in the
+// k-step that frees their buffers; GROUP_M tile rows form one band of the tile walk.
+template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, int GROUP_M_, int AX_ = 0>
 struct PipeCfg {
     static constexpr int SA = STAGES_ + AX_, SB = STAGES_;   // ring depths of the A and B slices
     static constexpr int GROUP_M = GROUP_M_;   // tile rows per band of the tile walk
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_;
-    static constexpr int SWZ = SWZ_, SPREAD = SPREAD_;
+    static constexpr int BM = BM_, BN = BN_, BK = 64, WGM = WGM_, WGN = WGN_;
     static constexpr int NW = WGM * WGN, NT = NW * 64;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;
     static constexpr int MI = WTM / MB, NI = WTN / MB;
@@ -119,9 +113,8 @@ struct PipeCfg {
     static constexpr int A_LD = A_BYTES / 1024 / NW;
     static constexpr int B_LD = B_BYTES / 1024 / NW;
     static constexpr int LPS = A_LD + B_LD;
-    static_assert(SPREAD == 1, "spread");
     static_assert(AX_ == 0 || AX_ == 1, "extra A stages");
-    static_assert(BK == 32 || BK == 64 || BK == 128, "BK");
+    static_assert(KK % 2 == 0, "every slice begins with the same set of B registers");
     static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile vs wavefront count");
     static_assert(SA * LPS <= 63, "vmcnt range");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
@@ -244,7 +237,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         static_assert(!UNIFORM || (Cfg::BM == BLK_C && Cfg::NT * 8 / Cfg::BM % 16 == 0 && Cfg::NT / CPR % 16 == 0), "period of the swizzles");
         const int krow = tid / (Cfg::BM / 8), row = tid / CPR;
         va = (uint32_t)(krow * BLK_C + ((tid % (Cfg::BM / 8)) ^ km_swz(krow)) * 8) * 2u;
-        vb = (uint32_t)(row * Cfg::BK + ((tid % CPR) ^ swz<CPR, Cfg::SWZ>(row)) * 8) * 2u;
+        vb = (uint32_t)(row * Cfg::BK + ((tid % CPR) ^ swz<CPR>(row)) * 8) * 2u;
     }
     auto locate = [&](int item) __attribute__((always_inline)) {
         kt_lo = 0;
@@ -274,7 +267,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                 continue;
             }
             const int row = ci / CPR, pc = ci % CPR;
-            const int kc = pc ^ swz<CPR, Cfg::SWZ>(row);
+            const int kc = pc ^ swz<CPR>(row);
             if (BL == B_BLK && !isA) {
                 pl[i] = B + ((size_t)tn * (K / Cfg::BK) * Cfg::BN + row) * Cfg::BK + kc * 8;
                 continue;
@@ -322,7 +315,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     // end of the k-step, so it alone has two register sets and is read first. B blocks are needed
     // throughout a k-step and are double-buffered.
     const int frag_row = lane & 15, frag_q = lane >> 4;
-    const int sw = swz<CPR, Cfg::SWZ>(frag_row);
+    const int sw = swz<CPR>(frag_row);
     const int a_base = (wave_m * Cfg::WTM + frag_row) * ROWB;
     const int b_base = (wave_n * Cfg::WTN + frag_row) * ROWB;
     bf16x8 af[MI + 1], bfr[2][NI];
@@ -425,21 +418,19 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         for (int ni = 0; ni < NI; ++ni) read_b(0, smem + Cfg::B_RING, 0, ni);
 
         // One slice = KK k-steps. STEADY iterations (1 <= kt, kt + SA < KT) have every condition
-        // resolved at compile time, so the whole slice is straight-line code. PAR = parity of the
-        // slice's first k-step (which B register set it computes from); always 0 when KK is even.
+        // resolved at compile time, so the whole slice is straight-line code.
         // At the barrier of slice kt the data of slice kt+1 must have landed; behind its B part were
         // issued (in steady state) SB-2 whole groups and, if the A ring is deeper, the A part of the
         // group that brought it.
         constexpr int STEADY_PENDING = (SB - 2) * LPS + (SA > SB ? A_LD : 0);
         int bufa = 0, bufb = 0;
-        auto slice = [&](int kt, auto steady_tag, auto parity_tag) __attribute__((always_inline)) {
+        auto slice = [&](int kt, auto steady_tag) __attribute__((always_inline)) {
             constexpr bool STEADY = decltype(steady_tag)::value;
-            constexpr int PAR = decltype(parity_tag)::value;
             const int nbufa = (bufa + 1 == SA) ? 0 : bufa + 1;
             const int nbufb = (bufb + 1 == SB) ? 0 : bufb + 1;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
-                const int cur = (kk + PAR) & 1, nxt = cur ^ 1;
+                const int cur = kk & 1, nxt = cur ^ 1;
                 // Issue priority: low in the k-steps that run up to the barrier, high in the one behind it.
                 // The two wavefronts of a SIMD drift apart (the older one wins every issue slot, reaches the
                 // barrier first and idles there while the other one's memory instructions stall with nobody
@@ -495,20 +486,10 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
             }
             bufa = nbufa; bufb = nbufb;
         };
-        typedef std::integral_constant<int, 0> P0;
-        typedef std::integral_constant<int, 1> P1;
         int kt = 0;
-        if (KT > 0) { slice(0, std::false_type{}, P0{}); kt = 1; }
-        if (KK & 1) {
-            // odd KK: the register-set parity alternates from slice to slice; kt stays odd here, so
-            // slices go in pairs of parity (1, 0)
-            for (; kt + 1 + SA < KT; kt += 2) { slice(kt, std::true_type{}, P1{}); slice(kt + 1, std::true_type{}, P0{}); }
-            for (; kt + 1 < KT; kt += 2) { slice(kt, std::false_type{}, P1{}); slice(kt + 1, std::false_type{}, P0{}); }
-            if (kt < KT) slice(kt, std::false_type{}, P1{});
-        } else {
-            for (; kt + SA < KT; ++kt) slice(kt, std::true_type{}, P0{});
-            for (; kt < KT; ++kt) slice(kt, std::false_type{}, P0{});
-        }
+        if (KT > 0) { slice(0, std::false_type{}); kt = 1; }
+        for (; kt + SA < KT; ++kt) slice(kt, std::true_type{});
+        for (; kt < KT; ++kt) slice(kt, std::false_type{});
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_s_setprio(0);
         if (phase) pt2 = clock64();
@@ -541,7 +522,6 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         clear_acc();
-        bufa = 0; bufb = 0;
         // a tile over the edge issues fewer stores than a whole one
         stores_pending = KT >= SA && c.bm0 + Cfg::BM <= M && c.bn0 + Cfg::BN <= N;
         if (stores_pending) wait_loads_then_barrier<HEAD_PENDING + STORES>();
@@ -562,7 +542,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
 // overwritten: 250 tokens 0.80 -> 0.78, 650 1.26 -> 1.22, the longer ones the same. Streaming stores: 12 % slower.
 template <int KIND>
 struct EpiStore {
-    float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map; int64_t row_base;
+    float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map;
     const float* row_scale;   // KIND 1: output row m is multiplied by row_scale[m] if not NULL
     float* partial;           // if not NULL, work item i stores its whole BM x BN fp32 tile, row-major, at
                               // partial + i * BM * BN instead (launches that split K; summed up by a second kernel)
@@ -650,7 +630,7 @@ struct EpiStore {
             for (int j = 0; j < 4; ++j) {
                 const int row = c.m0 + mi * MB + acc_row(c.lane, j);
                 if (row >= c.M) continue;
-                const int64_t orow = row_map ? (int64_t)row_map[row_base + row] : (int64_t)row;
+                const int64_t orow = row_map ? (int64_t)row_map[row] : (int64_t)row;
                 const float rs = row_scale ? row_scale[row] : 1.0f;
 #pragma unroll
                 for (int ni = 0; ni < Cfg::NI; ++ni) {
@@ -662,7 +642,8 @@ struct EpiStore {
             }
     }
 
-    // KIND 0 needs N and ldc to be multiples of 4 and C 16-byte aligned (checked by the launcher).
+    // KIND 0 needs N and ldc to be multiples of 4 and C 16-byte aligned: D is a multiple of 64 and dW 16-byte aligned,
+    // which the entry points check.
     template <class Cfg>
     static constexpr int lds_bytes() { return 0; }
     static constexpr bool SWAP = KIND == 0;

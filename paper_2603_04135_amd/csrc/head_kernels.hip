@@ -274,13 +274,12 @@ __global__ void softmax_scale_kernel(const int32_t* __restrict__ y, const float*
 // bf16 transpose by 16-byte accesses: dstT[c, r] = scale[r] * src[r, c] (scale NULL = 1) for
 // r < rows_out, c < cols; source rows >= rows_valid read as zero. cols and rows_out are
 // multiples of 64, all pointers and pitches multiples of 8 elements. A 64 x 64 tile goes through
-// LDS; every thread loads and stores whole 8-element vectors. dstT is row-major with pitch
-// ld_dstT, or (blocked != 0) the blocked B-operand layout of the MFMA GEMMs with ld_dstT = rows_out
-// columns in all: blocks of GEMM_B_BLOCK_ROWS rows x GEMM_B_BLOCK_K columns, block (i, j) at
-// (i * ld_dstT / GEMM_B_BLOCK_K + j) blocks from the start (a 64 x 64 tile is then one contiguous 8 KB run).
+// LDS; every thread loads and stores whole 8-element vectors. dstT has the blocked B-operand layout of the
+// MFMA GEMMs: blocks of GEMM_B_BLOCK_ROWS rows x GEMM_B_BLOCK_K columns, block (i, j) at
+// (i * rows_out / GEMM_B_BLOCK_K + j) blocks from the start (a 64 x 64 tile is then one contiguous 8 KB run).
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ src, int64_t ld_src,
                                                              int32_t rows_valid, const float* __restrict__ scale,
-                                                             uint16_t* __restrict__ dstT, int64_t ld_dstT, int blocked) {
+                                                             uint16_t* __restrict__ dstT, int64_t rows_out) {
     __shared__ uint16_t tile[64][64 + 2];
     const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
     const int vec = threadIdx.x & 7, line = threadIdx.x >> 3;
@@ -317,10 +316,9 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __r
             w[k] = (uint32_t)tile[vec * 8 + 2 * k][cc] | ((uint32_t)tile[vec * 8 + 2 * k + 1][cc] << 16);
         static_assert(GEMM_B_BLOCK_K == 64, "a 64-column tile = one block column");
         const int64_t drow = c0 + cc;
-        const int64_t off = blocked ? ((drow / GEMM_B_BLOCK_ROWS) * (ld_dstT / GEMM_B_BLOCK_K) + r0 / GEMM_B_BLOCK_K) *
-                                              (int64_t)(GEMM_B_BLOCK_ROWS * GEMM_B_BLOCK_K) +
-                                          (drow % GEMM_B_BLOCK_ROWS) * GEMM_B_BLOCK_K + vec * 8
-                                    : drow * ld_dstT + r0 + vec * 8;
+        const int64_t off = ((drow / GEMM_B_BLOCK_ROWS) * (rows_out / GEMM_B_BLOCK_K) + r0 / GEMM_B_BLOCK_K) *
+                                (int64_t)(GEMM_B_BLOCK_ROWS * GEMM_B_BLOCK_K) +
+                            (drow % GEMM_B_BLOCK_ROWS) * GEMM_B_BLOCK_K + vec * 8;
         *reinterpret_cast<uint4*>(dstT + off) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
@@ -568,7 +566,7 @@ void launch_gather_rows(int dtype, const GatherArgs& a, ChunkView cv, hipStream_
 void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* WT, hipStream_t st) {
     dim3 grid((unsigned)(D / 64), (unsigned)(Vp / 64));      // D and Vp are multiples of 64 on the bf16 path
     transpose_bf16_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(W), D, V, nullptr,
-                                                reinterpret_cast<uint16_t*>(WT), Vp, 1);
+                                                reinterpret_cast<uint16_t*>(WT), Vp);
 }
 
 void launch_combine_exp(const float2* part, int32_t n_tiles, const float* zy, const float* bref, ChunkView cv,
@@ -599,7 +597,7 @@ void launch_softmax_scale(const int32_t* y, const float* zy, const float* bref, 
 void launch_scale_transpose_bf16(const void* Hc, const float* scale, int32_t n_cp, int32_t D, void* HcT, hipStream_t st) {
     dim3 grid((unsigned)(D / 64), (unsigned)(n_cp / 64));
     transpose_bf16_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(Hc), D, n_cp, scale,
-                                                reinterpret_cast<uint16_t*>(HcT), n_cp, 1);
+                                                reinterpret_cast<uint16_t*>(HcT), n_cp);
 }
 
 void launch_combine_logprob(const float2* part, LogitsPart lp, const float* zy, ChunkView cv, float* lse_chunk,
