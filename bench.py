@@ -253,8 +253,8 @@ def main() -> int:
                              sel_bytes, "3 small kernels, latency-bound (one thread per group)"),
         "dppo_pack": stage(timed(lambda: P.dppo_pack(item_pl, item_cl, keep_flat, wl.capacity, wl.n_win,
                                                      loss_pos_capacity=lp_cap, device=dev), 10),
-                           pack_bytes, "one deterministic wavefront + loss_pos fill; the binding's host read-back of "
-                                       "the 8-int meta is inside the time"),
+                           pack_bytes, "one workgroup (one of its wavefronts places, deterministic) + loss_pos fill; the "
+                                       "binding's host read-back of the 8-int meta is inside the time"),
         "dppo_gather_f32": stage(timed(lambda: (P.dppo_gather_f32(pk["order"], sel["adv"]),
                                                 P.dppo_gather_f32(pk["order"], sel["coef"])), 10),
                                  gather_bytes, "two launches (adv, coef)"),
@@ -268,11 +268,10 @@ def main() -> int:
     ew_ms, _ = stages.get("elementwise", (0.0, 0))
     if ew_ms > 0:
         n_tiles = -(-wl.V // 256)
-        ew_bytes = (N * wl.D * es * 2          # row gather: read H rows, write the chunk copy
-                    + N * wl.D * es * 2        # target logits: chunk rows and W[y] rows
+        ew_bytes = (N * wl.D * es * 3          # row gather with target logits: read H and W[y] rows, write the chunk copy
                     + N * n_tiles * 8          # per-tile (max, sum) pairs
                     + N * wl.D * es * 2        # scaled transpose of the chunk copy
-                    + 2 * wl.V * wl.D * es     # W -> W^T, once per call
+                    + (2 * wl.V * wl.D * es if N > 4096 + wl.D else 0)   # W -> W^T, once per call of many tokens
                     + T * wl.D * es            # zero fill of dH
                     + N * 60)                  # per-token vectors
         other["elementwise_in_loss_fwd_bwd"] = stage(ew_ms / args.steps, ew_bytes,

@@ -135,7 +135,7 @@ int dppo_history_update(int32_t n, const int32_t* prompt_index, const uint8_t* k
  * `capacity`; 2 = N exceeds loss_pos_capacity; 3 = T does not fit int32. On a non-zero
  * status n_rows = T = N = S = 0 and no other output is meaningful.
  * cu_seqlens and loss_cu are also used as scratch while packing.
- * The result is a bit-exact function of the inputs (one deterministic wavefront).
+ * The result is a bit-exact function of the inputs (one workgroup, of which one wavefront places).
  */
 enum { DPPO_PACK_FIRST_FIT = 0, DPPO_PACK_BEST_FIT = 1 };
 

@@ -182,7 +182,8 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                                                              int k_parts, int n_items, Epi epi, unsigned long long* phase) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // phase (benchmark aid, normally NULL): 4 counters that every workgroup adds to: shader cycles from
-    // its start to the first slice in LDS, in the main loop, in the epilogue, and 1.
+    // its start to the first slice in LDS, in the main loop, in the epilogue, and 1. A resident workgroup adds once per
+    // tile: from the second one on, the first of them is the wait for slices that were loaded under the epilogue before.
     unsigned long long pt0 = 0, pt1 = 0, pt2 = 0;
     if (phase) pt0 = clock64();
     constexpr bool A_KM = AM == A_BLK_KM;
@@ -404,7 +405,8 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     // the same at the barrier of slice 0, behind B of slice 1: A of slices 2 .. SA-1 and B of slices 2 .. SB-1
     constexpr int FIRST_PENDING = (SA - 2) * A_LD + (SB - 2) * B_LD;
     // Stores of the tile before that a wavefront may still have under way, behind those loads (loads and stores
-    // complete in order and count alike): all of a whole tile's, so that they drain under the first slices.
+    // complete in order and count alike): all of a whole tile's, so that they drain under the first slices. The counts
+    // below rely on a whole tile issuing exactly these, whatever else it issues being loads that it waits for.
     constexpr int STORES = PERSIST ? MI * NI : 0;
     static_assert(HEAD_PENDING + STORES <= 63, "vmcnt range");
     bool stores_pending = false;
@@ -538,8 +540,8 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
 // neighbouring columns, so the tile leaves the registers in 16-byte accesses of 64-byte runs, and 16 old values per lane
 // are in flight together. The LDS stays free for the next tile's first slices (see gemm_nt_kernel). Against a
 // tile staged through LDS by workgroups of one tile each, dW added to what is there: 250 tokens of D = 4096,
-// V = 151936 1.41 -> 1.08 ms, 650 tokens 1.84 -> 1.53, 1300 of D = 2560 1.55 -> 1.35, 8600 5.38 -> 5.30;
-// overwritten: 250 tokens 0.80 -> 0.78, 650 1.26 -> 1.22, the longer ones the same. Streaming stores: 12 % slower.
+// V = 151936 1.41 -> 1.05 ms, 650 tokens 1.84 -> 1.50, 1300 of D = 2560 1.55 -> 1.29, 8600 5.38 -> 5.2;
+// overwritten: 250 tokens 0.80 -> 0.77, 650 1.26 -> 1.17, the longer ones the same. Streaming stores: 12 % slower.
 template <int KIND>
 struct EpiStore {
     float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map;
