@@ -5,6 +5,8 @@
 // chunk (float32 path), and the segmented (per packed sequence) loss reduction.
 // All global accesses are coalesced 16-byte (or full-wave contiguous) transactions; the
 // transposes go through padded LDS tiles.
+#include <type_traits>
+
 #include "dppo_internal.h"
 
 namespace dppo {
@@ -83,13 +85,16 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t 
 }
 
 // ------------------------------------------------------------------------------------
-// Per-tile softmax partials part[tile][n] of 16 tokens per workgroup -> lse and log-prob. The tiles are split over
-// 64 lane groups (16 tokens = one 128-byte line per tile), eight loads in flight per thread; the groups meet by
-// shuffles and in LDS, in a fixed order.
-// Bound by HBM for many tokens (8 bytes per tile and token) and by latency for few: with 64 tokens and 4 groups per
+// Per-tile softmax partials part[tile][n] of TOK tokens per workgroup -> lse and log-prob. The tiles are split over
+// COMBINE_THREADS / TOK lane groups, eight loads in flight per thread; the groups meet by shuffles and in LDS, in a fixed
+// order. Bound by HBM for many tokens (8 bytes per tile and token) and by latency for few: with 64 tokens and 4 groups per
 // workgroup, a thread walked 149 dependent loads and 256 tokens kept four workgroups busy (V = 151936, 33 tokens:
-// 68 us of a 276 us call; now 9 us).
-constexpr int COMBINE_TOK = 16, COMBINE_GROUPS = 64, COMBINE_WAVES = COMBINE_TOK * COMBINE_GROUPS / 64;
+// 68 us of a 276 us call; 16 tokens and 32 groups 8.6 us, 64 groups 9.5).
+// From COMBINE_WIDE_TOKENS on, where 32 tokens a workgroup still give every compute unit one, 256 bytes in a row are read
+// instead of 128: 32768 tokens of V = 151936 30 us (16 tokens and 32 groups 35, 64 groups 44), 18688 of V = 32000
+// 6.2 us (8.5, 13.4); 4096 tokens of V = 151936 8.6 against 7.7 us with 16.
+constexpr int COMBINE_THREADS = 512, COMBINE_WAVES = COMBINE_THREADS / 64;
+constexpr int COMBINE_WIDE_TOKENS = 8192;
 constexpr int COMBINE_UNROLL = 8;
 
 // (max, sum exp(z - max)) of the union of two sets.
@@ -101,20 +106,21 @@ __device__ __forceinline__ float2 join_softmax(float2 a, float2 b) {
 // (max z, sum exp(z - reference)) with one reference per token: the sums just add up.
 __device__ __forceinline__ float2 join_referenced(float2 a, float2 b) { return make_float2(fmaxf(a.x, b.x), a.y + b.y); }
 
-// The token's joined pair, valid in the first COMBINE_TOK threads of the workgroup.
-template <bool REFERENCED>
+// The token's joined pair, valid in the first TOK threads of the workgroup.
+template <bool REFERENCED, int TOK>
 __device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part, int32_t n_tiles, int32_t pitch, int32_t n_c, int n) {
-    __shared__ float2 red[COMBINE_WAVES][COMBINE_TOK];
-    const int group = threadIdx.x / COMBINE_TOK, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int GROUPS = COMBINE_THREADS / TOK;
+    __shared__ float2 red[COMBINE_WAVES][TOK];
+    const int group = threadIdx.x / TOK, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto join = [](float2 a, float2 b) { return REFERENCED ? join_referenced(a, b) : join_softmax(a, b); };
     const float2 none = make_float2(-__builtin_inff(), 0.0f);
     float2 r = none;
     if (n < n_c) {
-        for (int t0 = group; t0 < n_tiles; t0 += COMBINE_GROUPS * COMBINE_UNROLL) {
+        for (int t0 = group; t0 < n_tiles; t0 += GROUPS * COMBINE_UNROLL) {
             float2 p[COMBINE_UNROLL];
 #pragma unroll
             for (int u = 0; u < COMBINE_UNROLL; ++u) {
-                const int t = t0 + u * COMBINE_GROUPS;
+                const int t = t0 + u * GROUPS;
                 p[u] = t < n_tiles ? part[(size_t)t * pitch + n] : none;
             }
             float m = r.x, s = 0.0f;
@@ -127,23 +133,24 @@ __device__ __forceinline__ float2 combine_tiles(const float2* __restrict__ part,
         }
     }
 #pragma unroll
-    for (int off = COMBINE_TOK; off < 64; off <<= 1)
+    for (int off = TOK; off < 64; off <<= 1)
         r = join(r, make_float2(__shfl_xor(r.x, off, 64), __shfl_xor(r.y, off, 64)));
-    if (lane < COMBINE_TOK) red[wave][lane] = r;
+    if (lane < TOK) red[wave][lane] = r;
     __syncthreads();
-    if (threadIdx.x < COMBINE_TOK) {
+    if (threadIdx.x < TOK) {
         r = red[0][threadIdx.x];
         for (int w = 1; w < COMBINE_WAVES; ++w) r = join(r, red[w][threadIdx.x]);
     }
     return r;
 }
 
-__global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_logprob_kernel(
+template <int TOK>
+__global__ __launch_bounds__(COMBINE_THREADS) void combine_logprob_kernel(
     const float2* __restrict__ part, int32_t n_tiles, int32_t pitch, const float* __restrict__ zy, int64_t n0, int32_t n_c,
     int32_t n_cp, float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ lse_out) {
-    const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
-    const float2 r = combine_tiles<false>(part, n_tiles, pitch, n_c, n);
-    if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
+    const int n = blockIdx.x * TOK + threadIdx.x % TOK;
+    const float2 r = combine_tiles<false, TOK>(part, n_tiles, pitch, n_c, n);
+    if (threadIdx.x >= TOK || n >= n_cp) return;
     if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
     const float lse = r.x + logf(r.y);
     lse_chunk[n] = lse;
@@ -158,13 +165,14 @@ __global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_logprob_k
 // approach the bottom of the bf16 range for small loss weights, so the token goes on the redo
 // list instead and is redone against its row maximum.
 constexpr float EXP_SUM_LIMIT = 1e15f;
-__global__ __launch_bounds__(COMBINE_TOK* COMBINE_GROUPS) void combine_exp_kernel(
+template <int TOK>
+__global__ __launch_bounds__(COMBINE_THREADS) void combine_exp_kernel(
     const float2* __restrict__ part, int32_t n_tiles, const float* __restrict__ zy, const float* __restrict__ bref, int64_t n0,
     int32_t n_c, int32_t n_cp, float* __restrict__ lse_chunk, float* __restrict__ logp_out, float* __restrict__ mx,
     int32_t* redo_count, int32_t* __restrict__ redo_list, float* __restrict__ redo_sum) {
-    const int n = blockIdx.x * COMBINE_TOK + threadIdx.x % COMBINE_TOK;
-    const float2 r = combine_tiles<true>(part, n_tiles, n_cp, n_c, n);
-    if (threadIdx.x >= COMBINE_TOK || n >= n_cp) return;
+    const int n = blockIdx.x * TOK + threadIdx.x % TOK;
+    const float2 r = combine_tiles<true, TOK>(part, n_tiles, n_cp, n_c, n);
+    if (threadIdx.x >= TOK || n >= n_cp) return;
     mx[n] = r.x;
     if (n >= n_c) { lse_chunk[n] = 0.0f; return; }
     if (!(r.y < EXP_SUM_LIMIT)) {
@@ -572,8 +580,13 @@ void launch_transpose_w(const void* W, int32_t V, int32_t D, int32_t Vp, void* W
 void launch_combine_exp(const float2* part, int32_t n_tiles, const float* zy, const float* bref, ChunkView cv,
                         float* lse_chunk, float* logp_out, float* mx, int32_t* redo_count, int32_t* redo_list,
                         float* redo_sum, hipStream_t st) {
-    combine_exp_kernel<<<(unsigned)ceil_div(cv.n_cp, COMBINE_TOK), COMBINE_TOK * COMBINE_GROUPS, 0, st>>>(
-        part, n_tiles, zy, bref, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, mx, redo_count, redo_list, redo_sum);
+    auto run = [&](auto tok) {
+        constexpr int TOK = decltype(tok)::value;
+        combine_exp_kernel<TOK><<<(unsigned)ceil_div(cv.n_cp, TOK), COMBINE_THREADS, 0, st>>>(
+            part, n_tiles, zy, bref, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, mx, redo_count, redo_list, redo_sum);
+    };
+    if (cv.n_cp >= COMBINE_WIDE_TOKENS) run(std::integral_constant<int, 32>{});
+    else run(std::integral_constant<int, 16>{});
 }
 
 void launch_exp_redo_rows(const int32_t* redo_count, const int32_t* redo_list, float* redo_sum, const void* Hc,
@@ -602,8 +615,13 @@ void launch_scale_transpose_bf16(const void* Hc, const float* scale, int32_t n_c
 
 void launch_combine_logprob(const float2* part, LogitsPart lp, const float* zy, ChunkView cv, float* lse_chunk,
                             float* logp_out, float* lse_out, hipStream_t st) {
-    combine_logprob_kernel<<<(unsigned)ceil_div(cv.n_cp, COMBINE_TOK), COMBINE_TOK * COMBINE_GROUPS, 0, st>>>(
-        part, lp.tiles, lp.pitch, zy, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, lse_out);
+    auto run = [&](auto tok) {
+        constexpr int TOK = decltype(tok)::value;
+        combine_logprob_kernel<TOK><<<(unsigned)ceil_div(cv.n_cp, TOK), COMBINE_THREADS, 0, st>>>(
+            part, lp.tiles, lp.pitch, zy, cv.n0, cv.n_c, cv.n_cp, lse_chunk, logp_out, lse_out);
+    };
+    if (cv.n_cp >= COMBINE_WIDE_TOKENS) run(std::integral_constant<int, 32>{});
+    else run(std::integral_constant<int, 16>{});
 }
 
 void launch_row_stats_f32(const float* Z, int64_t ldz, int32_t V, const int32_t* y, ChunkView cv, float* lse_chunk,

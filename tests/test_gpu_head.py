@@ -218,6 +218,24 @@ def test_fp32_row_statistics(lib, V):
     assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-5
 
 
+@pytest.mark.parametrize("tokens,V", [(7936, 1000), (7937, 1000), (8190, 33000)])
+def test_statistics_of_many_tokens(lib, tokens, V):
+    # both sides of 8192 padded tokens, from where 32 tokens are combined per workgroup; 4 and 129 tiles for 16 lane groups
+    # of eight loads each
+    case = _case("small", tokens, dtype="bf16", D=64, V=V)
+    logp_ref, lse_ref = case.oracle_logprob()
+    ws = lib.alloc_workspace(lib.dppo_workspace_bytes(case.pk["T"], tokens, 64, V, 1, 1), DEV)
+    ws.fill_(0xFF)                               # NaN wherever a statistic that nobody wrote is read
+    logp, lse = lib.dppo_token_logprob(case.H, case.W, case.ids, case.loss_pos, ws=ws)
+    case.set_behaviour_logps(logp_ref)
+    out = lib.dppo_loss_fwd_bwd(case.H, case.W, case.ids, case.loss_pos, case.loss_cu, case.seq_adv, case.seq_coef,
+                                case.logp_old, case.logp_ref, ws=ws)
+    # fp32 sums of 64 products |h w| < 1 and of V exponentials in two levels: a few 2^-24 of a log-sum of at most 11
+    assert np.abs(logp.cpu().numpy() - logp_ref).max() <= 1e-4
+    assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-4
+    assert np.abs(out["logp"].cpu().numpy() - logp_ref).max() <= 1e-4
+
+
 def _logits_as_given(dtype, z, tokens):
     """H, W and ids of `tokens` positions that all have exactly the logits z (bfloat16: rounded): W holds them in its
     first column, H picks that column. Targets walk down the vocabulary from its last entry."""
