@@ -240,6 +240,19 @@ void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, const vo
     else launch_dh<B_KM>(cus, G, Vp, W, D, V, n_c, D, row_scale, out, partial, st);
 }
 
+// Whether dW's tiles are walked by resident workgroups, one per compute unit, that load a tile's first slices while the one
+// before is stored. Added to what is there, that hides the reading of the old values, until a long chunk's shared panels
+// matter more: residents drift apart, and a chunk of 32234 tokens of D = 2560 misses the L2 for 65 GB instead of 48. Overwritten,
+// it pays with one or two slices a tile only; further on the loads disturb the stores. dW stage, resident / one tile each, V =
+// 151936:
+//   added        D = 4096: 250 tokens 1.058 / 1.140 ms, 4000 4.186 / 4.239, 24576 21.94 / 21.80
+//                D = 2560: 1300 tokens 1.245 / 1.289, 16384 9.297 / 9.324, 32256 17.81 / 17.67
+//   overwritten  D = 4096: 40 tokens 0.473 / 0.496, 100 0.647 / 0.620, 130 0.743 / 0.675, 1500 1.901 / 1.820, 24576 21.64 / 21.51
+//                D = 2560: 100 tokens 0.361 / 0.372, 250 0.473 / 0.446, 1300 1.031 / 1.059, 32256 17.63 / 17.48
+static bool dw_resident(int32_t tokens, int accumulate) {
+    return tokens <= (accumulate ? 16384 : 2 * CfgGrad::BK);
+}
+
 void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t n_cp, int32_t V, int32_t D,
                     const StoreSpec& out, float* partial, hipStream_t st) {
     EpiStoreDW e{reinterpret_cast<float*>(out.C), nullptr, out.ldc, out.accumulate, nullptr, nullptr, nullptr};
@@ -247,11 +260,12 @@ void launch_mfma_dw(int cus, const void* G, int32_t Vp, const void* HcT, int32_t
     const int tiles = tiles_m * tiles_n;
     int tail;
     const int parts = tail_split(cus, tiles, n_cp / CfgGrad::BK, partial, tail);
+    const int workgroups = dw_resident(n_cp, out.accumulate) ? cus : 0;
     if (parts == 1) {
-        launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, -1, 1, PHASE_DW, 0, cus);
+        launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, -1, 1, PHASE_DW, 0, workgroups);
         return;
     }
-    launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, tiles - tail, 1, PHASE_DW, 0, cus);
+    launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, e, st, 0, tiles - tail, 1, PHASE_DW, 0, workgroups);
     EpiStoreDW ep = e;
     ep.partial = partial;
     launch<CfgGrad, A_BLK_KM, WG_RANGES, B_BLK>(G, Vp, HcT, 0, V, D, n_cp, ep, st, tiles - tail, tail, parts);

@@ -541,7 +541,8 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
 // are in flight together. The LDS stays free for the next tile's first slices (see gemm_nt_kernel). Against a
 // tile staged through LDS by workgroups of one tile each, dW added to what is there: 250 tokens of D = 4096,
 // V = 151936 1.41 -> 1.05 ms, 650 tokens 1.84 -> 1.50, 1300 of D = 2560 1.55 -> 1.29, 8600 5.38 -> 5.2;
-// overwritten: 250 tokens 0.80 -> 0.77, 650 1.26 -> 1.17, the longer ones the same. Streaming stores: 12 % slower.
+// overwritten (one tile each): 250 tokens 0.78 -> 0.76, 650 1.26 -> 1.14, the longer ones 1 % less. Streaming stores: 12 %
+// slower.
 template <int KIND>
 struct EpiStore {
     float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map;
@@ -564,8 +565,7 @@ struct EpiStore {
             auto store = [&](auto full_tag, auto add_tag) __attribute__((always_inline)) {
                 constexpr bool FULL = decltype(full_tag)::value, ADD = decltype(add_tag)::value;
                 // The stores of an overwritten tile start when the next tile's slices have landed: mixed with those loads
-                // they take longer (V = 151936, D = 4096, dW stage of 250 tokens 0.835 ms mixed, 0.806 behind them; 40
-                // tokens 0.485 and 0.481; the same from 1300 tokens on).
+                // they take longer (V = 151936, D = 4096, dW stage of 40 tokens 0.485 ms mixed, 0.481 behind them).
                 if constexpr (!ADD) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if constexpr (FULL) {
                     constexpr int GROUP = 4;                        // block rows whose old values are in flight together

@@ -305,6 +305,32 @@ def test_dw_tiles_walked_by_resident_workgroups(lib, tokens, D, V):
     assert torch.equal(acc, old + out["dW"])
 
 
+@pytest.mark.parametrize("tokens", [64, 128, 129, 16384, 16385])
+def test_dw_walks_agree(lib, tokens):
+    # resident workgroups add to what is there up to 16384 tokens and overwrite with up to 128; all other launches
+    # have a workgroup per tile (270 tiles here). The sums are the same numbers in the same order
+    D, V = 64, 69000
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), generator=g, device=DEV).to(torch.bfloat16)
+    W = (torch.randn((V, D), generator=g, device=DEV) * 0.1).to(torch.bfloat16)
+    ids = torch.randint(0, V, (tokens,), generator=g, device=DEV, dtype=torch.int32)
+    one, cu = torch.ones(1, device=DEV), torch.tensor([0, tokens], dtype=torch.int32, device=DEV)
+    logp, _ = lib.dppo_token_logprob(H, W, ids, None)
+    old = torch.randn((V, D), generator=g, device=DEV)
+    acc = old.clone()
+    ws = lib.alloc_workspace(lib.dppo_workspace_bytes(tokens, tokens, D, V, 1, 1), DEV)
+    out = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, logp, logp, ws=ws)
+    lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, logp, logp, dW=acc, accumulate_dW=True, ws=ws)
+    assert torch.equal(acc, old + out["dW"])
+    # ratio 1, no KL: d loss / d logp = -1 / tokens for every token; one vocabulary slice in float64
+    lo, hi = V - 300, V
+    p = torch.exp(H.double() @ W.double()[lo:hi].T - torch.logsumexp(H.float() @ W.float().T, dim=1, keepdim=True).double())
+    hot = (ids.long()[:, None] == torch.arange(lo, hi, device=DEV)[None]).double()
+    want = ((hot - p).T @ H.double()) * (-1.0 / tokens)
+    assert rel_fro(to_np64(out["dW"][lo:hi]), to_np64(want)) <= TOL["bf16"]["grad"]
+
+
 @pytest.mark.parametrize("tokens", [1, 64, 65, 128, 192, 193, 321])
 def test_dw_sums_over_whole_slices_of_tokens(lib, tokens):
     # one to six slices of 64 tokens, whatever the chunk is padded to; 270 tiles for 256 resident workgroups
