@@ -119,9 +119,14 @@ struct PipeCfg {
     static_assert(SA * LPS <= 63, "vmcnt range");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
     static_assert(NI >= 2 && NI <= MI && LPS <= MI * NI, "read and load slots of a k-step");
-    // MFMA of a k-step behind which load i of a slice is issued: the 3rd of row i, or spread over the step
-    // where the wavefront's sub-tile has too few rows or columns for that
-    static constexpr int load_slot(int i) { return NI >= 3 && LPS <= MI ? i * NI + 2 : i * MI * NI / LPS; }
+    // Load of a slice that is issued behind MFMA q of a k-step, or LPS for none: load i behind the 3rd of row i, or spread
+    // over the step where the wavefront's sub-tile has too few rows or columns for that. (A function of q: looked up from the
+    // load's side, no address depends on q, and the compiler forms them all ahead of the slice's first MFMA.)
+    static constexpr int load_at(int q) {
+        if (NI >= 3 && LPS <= MI) return q % NI == 2 && q / NI < LPS ? q / NI : LPS;
+        const int i = (q * LPS + MI * NI - 1) / (MI * NI);
+        return i < LPS && i * MI * NI / LPS == q ? i : LPS;
+    }
 };
 
 // Layout of the A operand (template parameter AM):
@@ -230,6 +235,10 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     // the per-load pointers to the epilogue.
     const uint16_t* pl[LPS];
     constexpr bool UNIFORM = A_KM;
+    // Where the addresses of a slice's loads are formed. Row-major A (the vocabulary GEMM): next to each load; ahead of the
+    // slice's first MFMA they cost 2 % of its main loop (D = 2560: 91.9 instead of 90.4 thousand cycles a tile). Blocked A (dH, dW),
+    // where they take more instructions: ahead of it; next to the loads 1.5 and 3 % more (5336 / 5421 and 1185 / 1218 thousand).
+    constexpr bool EARLY_ADDRESSES = AM != A_ROWS;
     static_assert(!A_KM || (BL == B_BLK && BLK_R % Cfg::BK == 0), "a slice stays inside one block");
     constexpr int A_STEP = Cfg::NT * 8, B_STEP = Cfg::NT * 8;    // elements between successive loads of a slice
     const uint16_t *ua = nullptr, *ub = nullptr;
@@ -285,29 +294,32 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         }
     };
     locate(logical);
-    // Issues load i of slice kt: i < B_LD is a B load into B-ring buffer bufb, the others are A loads
+    // Load i of slice kt: i < B_LD is a B load into B-ring buffer bufb, the others are A loads
     // into A-ring buffer bufa. B goes first, so that at the next barrier "all but the newest A_LD
     // loads" means: this slice's B loads have landed, its A loads (due one slice later) may not have.
-    auto issue_load = [&](int bufa, int bufb, int kt_rel, int i) {
+    auto load_dst = [&](int bufa, int bufb, int i) __attribute__((always_inline)) -> char* {
+        const bool isA = i >= Cfg::B_LD;
+        const int ii = isA ? i - Cfg::B_LD : i;
+        return smem + (isA ? bufa * Cfg::A_BYTES : Cfg::B_RING + bufb * Cfg::B_BYTES) + (ii * Cfg::NW + wave) * 1024;
+    };
+    auto load_src = [&](int kt_rel, int i) __attribute__((always_inline)) -> const void* {
         const int64_t kt = kt_lo + kt_rel;
         const size_t koff = (size_t)kt * Cfg::BK;
         const size_t koff_a = A_KM ? blk_offset(kt * Cfg::BK, 0, lda)
                               : AM == A_BLK_ROWS ? blk_offset(0, kt * Cfg::BK, lda) : koff;
         const bool isA = i >= Cfg::B_LD;
         const int ii = isA ? i - Cfg::B_LD : i;
-        char* dst = smem + (isA ? bufa * Cfg::A_BYTES : Cfg::B_RING + bufb * Cfg::B_BYTES) + (ii * Cfg::NW + wave) * 1024;
         size_t koff_b = BL == B_BLK ? koff * Cfg::BN : koff;
         if (BL == B_KM && !isA) {
             const int k = (int)koff + ((ii * Cfg::NW + wave) * 64 + lane) / B_KM_CPR;
             koff_b = (size_t)(k < b_rows ? k : b_rows - 1) * ldb;
         }
-        if (UNIFORM) {
-            const char* base = reinterpret_cast<const char*>(isA ? ua + koff_a + ii * A_STEP : ub + koff_b + ii * B_STEP);
-            __builtin_amdgcn_global_load_lds(DPPO_GPTR(base + (isA ? va : vb)), DPPO_LPTR(dst), 16, 0, 0);
-            return;
-        }
-        const uint16_t* src = isA ? pl[ii] + koff_a : pl[Cfg::A_LD + ii] + koff_b;
-        __builtin_amdgcn_global_load_lds(DPPO_GPTR(src), DPPO_LPTR(dst), 16, 0, 0);
+        if (UNIFORM)
+            return reinterpret_cast<const char*>(isA ? ua + koff_a + ii * A_STEP : ub + koff_b + ii * B_STEP) + (isA ? va : vb);
+        return isA ? pl[ii] + koff_a : pl[Cfg::A_LD + ii] + koff_b;
+    };
+    auto issue_load = [&](int bufa, int bufb, int kt_rel, int i) __attribute__((always_inline)) {
+        __builtin_amdgcn_global_load_lds(DPPO_GPTR(load_src(kt_rel, i)), DPPO_LPTR(load_dst(bufa, bufb, i)), 16, 0, 0);
     };
 
     // Operand registers. Block mi of A is needed by NI consecutive MFMAs of a k-step and is dead
@@ -430,6 +442,16 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
             constexpr bool STEADY = decltype(steady_tag)::value;
             const int nbufa = (bufa + 1 == SA) ? 0 : bufa + 1;
             const int nbufb = (bufb + 1 == SB) ? 0 : bufb + 1;
+            const void* src[LPS];
+            char* dst[LPS];
+            if (EARLY_ADDRESSES) {
+#pragma unroll
+                for (int i = 0; i < LPS; ++i) {
+                    src[i] = load_src(kt + (i < B_LD ? SB : SA), i);
+                    dst[i] = load_dst(bufa, bufb, i);
+                    asm volatile("" : "+v"(src[i]));   // (here, not next to the load)
+                }
+            }
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 const int cur = kk & 1, nxt = cur ^ 1;
@@ -460,7 +482,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                     // works on block (q / NI, q % NI); behind it, in the row of A block mi = q / NI:
                     //   first MFMA of the step: the next step's last A block (into its spare registers),
                     //   2nd MFMA of rows 0 .. NI-1: the next step's B block mi,
-                    //   MFMAs load_slot(0 .. LPS-1) (3rd of rows 0 .. LPS-1): one global load (B loads first),
+                    //   the MFMAs of load_at (3rd of rows 0 .. LPS-1): one global load (B loads first),
                     //   last MFMA of rows 0 .. MI-2: the next step's A block mi, over the one just used.
                     const char* rsa = smem + read_bufa * Cfg::A_BYTES;
                     const char* rsb = smem + Cfg::B_RING + read_bufb * Cfg::B_BYTES;
@@ -476,11 +498,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
                             if (ni == 1 && mi < NI) read_b(nxt, rsb, read_kk, mi);
                             if (ni == NI - 1 && mi < MI - 1) read_a(mi, rsa, read_kk, mi);
                         }
-#pragma unroll
-                        for (int i = 0; i < LPS; ++i) {
-                            if (q != Cfg::load_slot(i)) continue;
-                            if (i < B_LD) { if (loads_b) issue_load(bufa, bufb, kt + SB, i); }
-                            else if (loads_a) issue_load(bufa, bufb, kt + SA, i);
+                        const int load = Cfg::load_at(q);
+                        if (load < LPS && (load < B_LD ? loads_b : loads_a)) {
+                            if (EARLY_ADDRESSES)
+                                __builtin_amdgcn_global_load_lds(DPPO_GPTR(src[load]), DPPO_LPTR(dst[load]), 16, 0, 0);
+                            else issue_load(bufa, bufb, kt + (load < B_LD ? SB : SA), load);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
