@@ -77,11 +77,12 @@ struct Operand {
         } else {
             const int k = k0 + tid % BK;
             const int rb = row0 + tid / BK;
-            if (TAIL) {
-                // Row offsets formed for every load, and kept from being moved out of the K loop: the addresses of whole
-                // slices stay in registers there, a second set for this one slice would not fit (128 x 128 tiles, both
+            if (TAIL && PER_THREAD >= 16) {
+                // 128 x 128 tiles: row offsets formed for every load, and kept from being moved out of the K loop: the
+                // addresses of whole slices stay in registers there, a second set for this one slice would not fit (both
                 // operands K-contiguous: 24 registers spilled and reloaded one by one; log-probs of 2000 tokens, V = 32000, D =
-                // 1000 1.33 -> 1.27 ms, V = 30000, D = 300 0.515 -> 0.443). Forming them for every slice costs 2 % at D = 1024.
+                // 1000 1.33 -> 1.27 ms, V = 30000, D = 300 0.515 -> 0.443). Forming them for every slice costs 2 % at D = 1024,
+                // and in the smaller tiles' last slice 1 % (418 tokens, V = 1849, D = 709: 40.3 -> 40.9 us).
                 const int kc = k < K ? k : K - 1;
                 const int r0 = rb < rows ? rb : rows - 1;
                 int last = rows - 1 - r0;
@@ -95,11 +96,13 @@ struct Operand {
                 }
                 return;
             }
+            const int kc = !TAIL || k < K ? k : K - 1;
 #pragma unroll
             for (int i = 0; i < PER_THREAD; ++i) {
                 int r = rb + i * STEP;
                 r = r < rows ? r : rows - 1;
-                v[i] = X[(size_t)r * ld + k];
+                const float x = X[(size_t)r * ld + kc];
+                v[i] = !TAIL || k < K ? x : 0.0f;
             }
         }
     }
