@@ -91,7 +91,7 @@ struct WsPlan {
     size_t o_wt, o_logp, o_ell, o_kl, o_clip, o_seq, o_sratio, o_hc, o_hct, o_part, o_zg, o_fpart, o_y, o_rowc, o_zy, o_lse, o_c;
     size_t o_bref, o_mx, o_scale, o_redo_list, o_redo_sum, o_redo_count, o_dwpart;   // bf16 backward only
     bool direct_w;                 // bf16 backward: the dH GEMM reads W as it lies, no transposed copy is written or reserved
-    int f32_parts;                 // float32: parts the K dimension of the dH GEMM may be cut into (scratch for their sums)
+    int f32_parts;                 // float32: sums of all rows of a chunk that the scratch of a dH GEMM cut along K holds
     size_t total;
 };
 
@@ -265,7 +265,7 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, 
         launch_combine_logprob(part, lp, zy, cv, lse_c, logp_all, lse_all, st);
     } else {
         GemmF32 g{reinterpret_cast<const float*>(Hc), s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
-                  reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 1};
+                  reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 0};
         launch_gemm_f32(g, cus, st);
         launch_row_stats_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, s.V, y, cv, lse_c, logp_all,
                              lse_all, st);
@@ -666,10 +666,10 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         } else {
             const float* Gf = reinterpret_cast<const float*>(G);
             GemmF32 gh{Gf, p.Vp, 0, reinterpret_cast<const float*>(W), s.D, 1, cv.n_c, s.D, s.V, reinterpret_cast<float*>(oh.C),
-                       oh.ldc, 0, oh.row_map, p.f32_parts > 1 ? reinterpret_cast<float*>(wc + p.o_fpart) : nullptr, p.f32_parts};
+                       oh.ldc, 0, oh.row_map, p.f32_parts > 1 ? reinterpret_cast<float*>(wc + p.o_fpart) : nullptr, (int64_t)p.f32_parts * p.n_cp * s.D};
             launch_gemm_f32(gh, cus, st);
             GemmF32 gw{Gf, p.Vp, 1, reinterpret_cast<const float*>(wc + p.o_hc), s.D, 1, s.V, s.D, cv.n_c,
-                       reinterpret_cast<float*>(ow.C), ow.ldc, ow.accumulate, nullptr, nullptr, 1};
+                       reinterpret_cast<float*>(ow.C), ow.ldc, ow.accumulate, nullptr, nullptr, 0};
             launch_gemm_f32(gw, cus, st);
         }
         return DPPO_OK;

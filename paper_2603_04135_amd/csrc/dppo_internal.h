@@ -139,15 +139,15 @@ struct StoreSpec {
 };
 // fp32 GEMM of any size (gemm_f32.hip): A is [M, K] with pitch lda, or [K, M] if a_km; B likewise [N, K] or [K, N].
 // A k-major A goes with a k-major B (dW): the other pairing has no instance.
-// Output row m is row row_map[m] of C if row_map is not NULL. With `partial` (scratch of max_parts * M * N floats)
-// the K dimension may be cut into up to max_parts parts whose sums are added up in a fixed order.
+// Output row m is row row_map[m] of C if row_map is not NULL. With `partial` (scratch of partial_floats floats) the K dimension
+// may be cut into as many parts as M x N sums fit it, which are added up in a fixed order.
 struct GemmF32 {
     const float* A; int64_t lda; int a_km;
     const float* B; int64_t ldb; int b_km;
     int32_t M, N, K;
     float* C; int64_t ldc; int accumulate;
     const int32_t* row_map;
-    float* partial; int max_parts;
+    float* partial; int64_t partial_floats;
 };
 int gemm_f32_max_parts(int64_t K);
 void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st);

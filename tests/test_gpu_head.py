@@ -136,7 +136,7 @@ def test_vocab_and_token_tails(lib):
     _run_case(lib, case, TOL["f32"])
 
 
-# (workload, loss tokens, D, V): every tile of the fp32 GEMM (32, 64, 128) with remainders in all dimensions, a
+# (workload, loss tokens, D, V): every tile of the fp32 GEMM (32, 64, 128 wide) with remainders in all dimensions, a
 # single column, unaligned rows, K slices with a tail, and dH cut along the vocabulary
 @pytest.mark.parametrize("name,tokens,D,V", [("tiny", 1, 1, 2), ("tiny", None, 33, 3001), ("tiny", 33, 300, 65),
                                              ("small", 700, 130, 1100), ("small", 1100, 257, 4099)])
@@ -147,6 +147,45 @@ def test_fp32_tiles_and_splits(lib, name, tokens, D, V):
     lib.dppo_loss_fwd_bwd(case.H, case.W, case.ids, case.loss_pos, case.loss_cu, case.seq_adv, case.seq_coef,
                           case.logp_old, case.logp_ref, dW=acc, accumulate_dW=True)
     assert torch.equal(acc, 2.0 * out["dW"])
+
+
+# one size for each kind of tile of the fp32 GEMM (32, 64 and 128 wide)
+@pytest.mark.parametrize("tokens,D,V", [(40, 100, 500), (300, 200, 3001), (1100, 203, 9000)])
+def test_fp32_values_beyond_the_bf16_split(lib, tokens, D, V):
+    """Values of 2^60 and more, and infinities, do not go through the split into bf16 parts: a column scaled by 2^80 in H and by
+    2^-80 in W leaves the logits as they are and scales that column of dW and dH; a weight at minus infinity against
+    positive hidden states is a logit at minus infinity."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), device=DEV, generator=g)
+    W = 0.1 * torch.randn((V, D), device=DEV, generator=g)
+    H[:, 5] = H[:, 5].abs() + 0.1
+    ids = torch.randint(0, V - 1, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    cu, one = torch.tensor([0, tokens], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    lp = torch.zeros(tokens, device=DEV) - 5.0
+
+    def run(H, W):
+        return lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, lp, lp)
+
+    col = torch.ones(D, device=DEV)
+    col[3] = 2.0 ** 80
+    col[D - 1] = 2.0 ** -80
+    plain, scaled = run(H, W), run(H * col, W / col)
+    # any order of D fp32 products and sums, and of V exponentials in two levels
+    z = H.double() @ W.double().T
+    tol = D * 2.0 ** -24 * float((H.abs().double() @ W.abs().double().T).max()) + 32 * 2.0 ** -24 * 20
+    want = torch.log_softmax(z, 1).gather(1, ids.long()[:, None])[:, 0]
+    for out in (plain, scaled):
+        assert (out["logp"].double() - want).abs().max() <= tol
+    for name, scale in (("dH", 1 / col), ("dW", col)):
+        a, b = plain[name].double(), scaled[name].double() / scale.double()
+        err = (a - b).norm(dim=0) / a.norm(dim=0)
+        assert float(err.max()) <= 2 * tol, (name, float(err.max()))     # entries of G off by tol, sums of positive and negative ones
+
+    W[V - 1, 5] = -float("inf")
+    logp, lse = lib.dppo_token_logprob(H, W, ids, None)
+    want = torch.log_softmax(z[:, :V - 1], 1).gather(1, ids.long()[:, None])[:, 0]
+    assert (logp.double() - want).abs().max() <= tol
 
 
 @pytest.mark.parametrize("tokens", [3072, 3073])
