@@ -476,15 +476,17 @@ __global__ __launch_bounds__(256) void seq_ratio_kernel(const int32_t* __restric
     }
 }
 
-// One thread per prompt group: coef * G / (completion tokens of the whole group).
-__global__ void token_norm_coef_kernel(int32_t Q, int32_t G, const int32_t* __restrict__ comp_len,
-                                       const float* coef, float* coef_out) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per prompt group: coef * G / (completion tokens of the whole group). Bound by latency: 256 groups of 16, one
+// thread per group with a chain of loads and stores, 6.5 us; 2.6 us.
+__global__ __launch_bounds__(256) void token_norm_coef_kernel(int32_t Q, int32_t G, const int32_t* __restrict__ comp_len,
+                                                              const float* coef, float* coef_out) {
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= Q) return;
     int64_t tot = 0;
-    for (int i = 0; i < G; ++i) tot += comp_len[(size_t)q * G + i];
+    for (int i = lane; i < G; i += 64) tot += comp_len[(size_t)q * G + i];
+    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
     const float f = tot > 0 ? (float)((double)G / (double)tot) : 0.0f;
-    for (int i = 0; i < G; ++i) coef_out[(size_t)q * G + i] = coef[(size_t)q * G + i] * f;
+    for (int i = lane; i < G; i += 64) coef_out[(size_t)q * G + i] = coef[(size_t)q * G + i] * f;
 }
 
 // ------------------------------------------------------------------------------------
@@ -642,7 +644,7 @@ void launch_seq_ratio(const int32_t* loss_cu, int32_t S, const float* logp, cons
 
 void launch_token_norm_coef(int32_t Q, int32_t G, const int32_t* comp_len, const float* coef, float* coef_out,
                             hipStream_t st) {
-    token_norm_coef_kernel<<<(unsigned)ceil_div(Q, 64), 64, 0, st>>>(Q, G, comp_len, coef, coef_out);
+    token_norm_coef_kernel<<<(unsigned)ceil_div(Q, 4), 256, 0, st>>>(Q, G, comp_len, coef, coef_out);
 }
 
 void launch_grad_logits_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const float* lse, const float* c,

@@ -85,6 +85,19 @@ def test_fixed_count_select_matches_oracle(lib, name):
         _cmp_select(lib, rb.rewards, rb.hist, np.round(rb.u_prompt, 1).astype(np.float32), u_tied, r, r, fixed=True)
 
 
+# both sides of the sizes up to which one launch does the selection (512 prompts), groups that do not fill
+# a workgroup, a last workgroup with one group
+@pytest.mark.parametrize("Q,G", [(1, 1024), (3, 341), (2, 342), (5, 100), (513, 3), (512, 3), (257, 2), (129, 85), (5, 1024), (3, 513)])
+@pytest.mark.parametrize("fixed", [False, True])
+def test_select_on_both_sides_of_its_sizes(lib, Q, G, fixed):
+    rng = np.random.default_rng(Q * 1000 + G)
+    r = (rng.random((Q, G)) < rng.random((Q, 1))).astype(np.float32)
+    hist = np.round(rng.random(Q), 2).astype(np.float32)
+    up, uc = np.round(rng.random(Q), 2).astype(np.float32), np.round(rng.random((Q, G)), 3).astype(np.float32)
+    _cmp_select(lib, r, hist, up, uc, 0.5, 0.4, fixed=fixed)
+    _cmp_select(lib, rng.normal(size=(Q, G)).astype(np.float32), None, None, uc, 0.5, 0.4, ddof=0, fixed=fixed)
+
+
 def test_history_update_matches_oracle(lib):
     rng = np.random.default_rng(3)
     table = rng.random(1000).astype(np.float32)
