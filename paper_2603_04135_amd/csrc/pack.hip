@@ -8,9 +8,12 @@
 // 6 cycles, and reading the pool from memory costs 600 to 2000 cycles. The placing wavefront therefore keeps
 // the pool in registers, oldest item in the lowest lane: a ballot finds the oldest item that fits (first-fit
 // reading) or a DPP max the longest one (best-fit), and no memory is touched between two placements.
-// Measured (8 500 prompts, pool of 32, 2 440 rows): first-fit 0.62 ms instead of 3.07 with the pool in
-// global memory and one wavefront for everything, best-fit 1.28 ms; per row 590 cycles, per best-fit placement
-// 350. Compaction and offsets, spread over 16 wavefronts: 18 us.
+// An instruction of a wavefront alone on its compute unit takes about 7 cycles, and a taken branch or a VALU result that the
+// scalar unit waits for several more, so first-fit's loop over rows is straight-line code with one look (at the slots, the
+// stream and the row ends together) per row.
+// Measured (8 500 prompts, pool of 32, 2 900 rows): first-fit 0.51 ms (3.07 with the pool in global memory and one wavefront for
+// everything; 0.75 with a branch for each of those looks, in every row and around every search), best-fit 1.28 ms.
+// Compaction and offsets, spread over 16 wavefronts: 18 us.
 #include "dppo_internal.h"
 
 namespace dppo {
@@ -69,6 +72,8 @@ __device__ __forceinline__ int bits_below(uint64_t m) {
 }
 
 __device__ __forceinline__ uint64_t mask_below(int n) { return n >= 64 ? ~0ull : (1ull << n) - 1ull; }
+// Mask of the lanes below n (any integer), by one compare.
+__device__ __forceinline__ uint64_t lanes_below(int n) { return __ballot((int)(threadIdx.x & (WAVE - 1)) < n); }
 
 // Window-based greedy placement by one wavefront, pool of n_win <= 64 R - 32 items in registers.
 // The pool occupies the slots 0, 1, ... (slot = 64 r + lane) in arrival order; a placed item leaves a
@@ -135,81 +140,116 @@ __device__ __forceinline__ int place_pool(int S, int capacity, int n_win, const 
 
     int row_end = 0;                     // lane i: items placed up to the end of row 64 k + i, written out 64 rows at a time
     if (lane == 0) row_ptr[0] = 0;
-    while (pos < S) {
-        uint32_t rem = capacity;
-        uint32_t want = 0;               // best-fit: the longest length that fits
-        int hit = 0;                     // lowest register with a slot that can be placed next
-        auto next_slots = [&]() -> uint64_t {
-            uint64_t ok[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) ok[r] = fetched_slots(r) & __ballot(len[r] <= rem);
-            if (BEST) {
-                uint32_t v = 0;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const uint32_t l = __builtin_amdgcn_inverse_ballot_w64(ok[r]) ? len[r] : 0;
-                    v = l > v ? l : v;
-                }
-                want = wave_max_dpp(v);
-#pragma unroll
-                for (int r = 0; r < R; ++r) ok[r] &= __ballot(len[r] == want);
-            }
-            uint64_t mm = ok[R - 1];
-            hit = R - 1;
-#pragma unroll
-            for (int r = R - 2; r >= 0; --r)
-                if (ok[r] != 0) { mm = ok[r]; hit = r; }
-            return mm;
-        };
-        // first-fit: the run of oldest items (all slots before it are placed; its own refills follow in turn)
-        while (!BEST) {
-            const uint32_t top = base + rem;      // both below 2^31
-            int k = 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint64_t in = __ballot(sum[r] <= top);      // sum[] never falls from slot to slot
-                const uint64_t run = in & open[r];
-                at[r] = __builtin_amdgcn_inverse_ballot_w64(run) ? pos + bits_below(run) : at[r];
-                open[r] &= ~run;
-                pos += __popcll(run);
-                limit += __popcll(run);
-                const int n = __popcll(in);
-                if (n > 0) base = __builtin_amdgcn_readlane(sum[r], n - 1);
-                k += n;
-            }
-            rem = top - base;
-            if (k < SLOTS) break;
-            close_up();                           // the whole window is placed
-            if (pos >= S) break;
-        }
-        while (true) {
-            for (uint64_t mm = next_slots(); mm != 0; mm = next_slots()) {
-                const int f = __builtin_ctzll(mm);
-                uint32_t l = want;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (R > 1 && r != hit) continue;
-                    if (!BEST) l = __builtin_amdgcn_readlane(len[r], f);
-                    at[r] = lane == f ? pos : at[r];
-                    open[r] &= ~(1ull << f);
-                    if (!BEST) sum[r] -= lane >= f ? l : 0;
-                }
-#pragma unroll
-                for (int r = 1; r < R; ++r)
-                    if (!BEST && r > hit) sum[r] -= l;
-                rem -= l;
-                pos += 1;
-                limit += 1;
-                if (BEST && limit > SLOTS) close_up();
-            }
-            // first-fit may have run past the last slot: the items it could not fetch are the newest, which
-            // the scan of this row reaches last anyway
-            if (BEST || pos - pos0 < SLOTS - n_win) break;
-            close_up();
-        }
+    auto end_row = [&]() __attribute__((always_inline)) {
         row_end = lane == (rows & (WAVE - 1)) ? pos : row_end;
         rows += 1;
+    };
+    auto write_rows = [&]() __attribute__((always_inline)) {
         if ((rows & (WAVE - 1)) == 0) row_ptr[rows - WAVE + 1 + lane] = row_end;
+    };
+    while (BEST && pos < S) {
+        uint32_t rem = capacity;
+        while (true) {
+            uint64_t ok[R];
+            uint32_t v = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                ok[r] = fetched_slots(r) & __ballot(len[r] <= rem);
+                const uint32_t l = __builtin_amdgcn_inverse_ballot_w64(ok[r]) ? len[r] : 0;
+                v = l > v ? l : v;
+            }
+            const uint32_t want = wave_max_dpp(v);       // the longest length that fits
+            bool placed = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint64_t mm = ok[r] & __ballot(len[r] == want);
+                if (placed || mm == 0) continue;
+                const int f = __builtin_ctzll(mm);
+                at[r] = lane == f ? pos : at[r];
+                open[r] &= ~(1ull << f);
+                placed = true;
+            }
+            if (!placed) break;
+            rem -= want;
+            pos += 1;
+            limit += 1;
+            if (limit > SLOTS) close_up();
+        }
+        end_row();
+        write_rows();
+    }
+    // first-fit: places the run of oldest items (all slots before it are placed; its own refills follow in turn)
+    uint32_t rem = 0;
+    auto run_step = [&](bool may_be_empty) __attribute__((always_inline)) {
+        const uint32_t top = base + rem;              // both below 2^31
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t in = __ballot(sum[r] <= top);              // sum[] never falls from slot to slot
+            const uint64_t run = in & open[r];
+            at[r] = __builtin_amdgcn_inverse_ballot_w64(run) ? bits_below(run) + (pos + n) : at[r];
+            open[r] &= ~in;
+            n += __popcll(run);
+            const int here = __popcll(in);
+            if ((r == 0 && !may_be_empty) || here > 0) base = __builtin_amdgcn_readlane(sum[r], here - 1);
+        }
+        pos += n;
+        limit += n;
+        rem = top - base;
+    };
+    // and the later items that still fit, oldest first
+    auto later_items = [&]() __attribute__((always_inline)) {
+        auto next_slots = [&](uint64_t (&ok)[R]) __attribute__((always_inline)) -> uint64_t {
+            uint64_t any = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                ok[r] = __ballot(len[r] <= rem) & open[r] & lanes_below(limit - r * WAVE);
+                any |= ok[r];
+            }
+            return any;
+        };
+        uint64_t ok[R];
+        for (uint64_t any = next_slots(ok); any != 0; any = next_slots(ok)) {
+            uint32_t l = 0;
+            bool placed = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (placed) {                         // behind the placed item's register
+                    sum[r] -= l;
+                } else if (r == R - 1 || ok[r] != 0) {
+                    const int f = __builtin_ctzll(ok[r]);
+                    l = __builtin_amdgcn_readlane(len[r], f);
+                    at[r] = lane == f ? pos : at[r];
+                    open[r] &= ~(1ull << f);
+                    sum[r] -= lane >= f ? l : 0;
+                    placed = true;
+                }
+            }
+            rem -= l;
+            pos += 1;
+            limit += 1;
+        }
+    };
+    // Rows are ended one after the other, without a look at anything else, as long as neither the slots, nor the stream, nor
+    // the 64 row ends of the register run out.
+    while (!BEST && pos < S) {
+        const int stop = S < pos0 + (SLOTS - n_win) ? S : pos0 + (SLOTS - n_win), last_row = rows | (WAVE - 1);
+        while (true) {
+            rem = capacity;
+            run_step(false);                          // (a row begins with the oldest item, which fits)
+            later_items();
+            if (((pos - stop) & (rows - last_row)) >= 0) break;
+            end_row();
+        }
+        // the search may have run past the last slot: the items it could not fetch are the newest, which the scan of this row
+        // reaches last anyway
+        while (pos < S && pos - pos0 >= SLOTS - n_win) {
+            close_up();
+            run_step(true);
+            later_items();
+        }
+        end_row();
+        write_rows();
     }
     write_order();
     if (lane < (rows & (WAVE - 1))) row_ptr[(rows & ~(WAVE - 1)) + 1 + lane] = row_end;
