@@ -220,10 +220,11 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // Forward statistics of one chunk: Hc, targets, log-probs, lse. `ws` is the base of the set of
 // per-chunk regions to use (the workspace itself for set 0); no per-call region is touched. With keep_z the chunk's logits
+// (float32 with logits_only: just the logits, whose statistics launch_loss_rows_f32 makes in the backward)
 // stay in the workspace for the backward pass: as float32 logits (float32 path), or as bf16 exponentials against the per-token reference left in the bref region (bf16 path).
 int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, const void* H, const void* W,
                    const int32_t* ids, const int32_t* loss_pos, ChunkView cv, bool keep_z,
-                   float* logp_all, float* lse_all, int32_t* status, hipStream_t st) {
+                   float* logp_all, float* lse_all, int32_t* status, hipStream_t st, bool logits_only = false) {
     void* Hc = ws + p.o_hc;
     int32_t* y = reinterpret_cast<int32_t*>(ws + p.o_y);
     float* zy = reinterpret_cast<float*>(ws + p.o_zy);
@@ -267,8 +268,9 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, 
         GemmF32 g{reinterpret_cast<const float*>(Hc), s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
                   reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 0};
         launch_gemm_f32(g, cus, st);
-        launch_row_stats_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, s.V, y, cv, lse_c, logp_all,
-                             lse_all, st);
+        if (!logits_only)
+            launch_row_stats_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, s.V, y, cv, lse_c, logp_all,
+                                 lse_all, st);
     }
     return DPPO_OK;
 }
@@ -587,11 +589,14 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         launch_seq_ratio(loss_cu, S, logp_all, logp_old, seq_ratio, 0, s.N, nullptr, st);
     }
 
+    // float32 with a token-level ratio: nothing but the token's own log-prob stands between its logits and its gradients
+    const bool fused_rows = s.dtype == 0 && !seq_level;
     // forward of chunk c: statistics and log-probs, and what the backward needs of its logits;
     // with the forward running ahead, also the ratios of the sequences that end in it
     auto forward = [&](int64_t c) -> int {
         const ChunkView cv = view(c);
-        if (int rc2 = chunk_forward(s, p, cus, regions(c), H, W, ids, loss_pos, cv, s.dtype == 0 || !recompute, logp_all, nullptr, status, st))
+        if (int rc2 = chunk_forward(s, p, cus, regions(c), H, W, ids, loss_pos, cv, s.dtype == 0 || !recompute, logp_all, nullptr, status, st,
+                                    fused_rows))
             return rc2;
         if (ahead) launch_seq_ratio(loss_cu, S, logp_all, logp_old, seq_ratio, cv.n0, cv.n0 + cv.n_c, status, st);
         return DPPO_OK;
@@ -607,7 +612,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         ta.ratio_level = lp->ratio_level; ta.aggregation = lp->aggregation; ta.seq_ratio = seq_ratio;
         ta.c_chunk = reinterpret_cast<float*>(wc + p.o_c);
         ta.ell = ell; ta.kl = kl; ta.clipped = clipf;
-        {
+        if (!fused_rows) {
             StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
             launch_token_loss(ta, cv, st);
         }
@@ -619,7 +624,10 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         // serves both GEMMs. float32: row-major G, which the GEMMs read along either dimension.
         void* G = wc + p.o_zg;
         const float* row_scale = nullptr;
-        if (s.dtype == 0) {
+        if (fused_rows) {
+            StageTimer tm(DPPO_STAGE_GRAD_LOGITS, st);
+            launch_loss_rows_f32(reinterpret_cast<float*>(G), s.V, p.Vp, y, ta, logp_all, cv, st);
+        } else if (s.dtype == 0) {
             StageTimer tm(DPPO_STAGE_GRAD_LOGITS, st);
             launch_grad_logits_f32(reinterpret_cast<float*>(G), s.V, p.Vp, y, lse_c, ta.c_chunk, cv.n_c, st);
         } else if (recompute) {

@@ -119,6 +119,11 @@ void launch_token_norm_coef(int32_t Q, int32_t G, const int32_t* comp_len, const
 void launch_grad_logits_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const float* lse, const float* c,
                             int32_t n_c, hipStream_t st);
 
+// float32 path, token-level ratio: row statistics, log-prob, token terms and gradient entries of a chunk in one pass over the
+// stored logits (launch_row_stats_f32, launch_token_loss and launch_grad_logits_f32 of its n_c tokens).
+void launch_loss_rows_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const TokenLossArgs& a, float* logp, ChunkView cv,
+                          hipStream_t st);
+
 struct SeqReduceArgs {
     const int32_t* loss_cu; int32_t S; int64_t N;
     const float* seq_coef;

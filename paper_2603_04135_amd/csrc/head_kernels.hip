@@ -391,21 +391,19 @@ __global__ __launch_bounds__(ROW_THREADS) void row_stats_kernel(const float* __r
 // ------------------------------------------------------------------------------------
 // Per-token terms of Eq. 1 and d(loss)/d(logp), weighted by seq_coef / C_s (token-sum aggregation:
 // by seq_coef). With a sequence-level ratio every token of a sequence uses the same rho.
-__global__ void token_loss_kernel(TokenLossArgs a, int64_t n0, int32_t n_c, int32_t n_cp) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= n_cp) return;
-    if (n >= n_c) { a.c_chunk[n] = 0.0f; return; }
-    const int64_t gi = n0 + n;
+__device__ __forceinline__ int packed_sequence(const TokenLossArgs& a, int64_t gi) {
     int lo = 0, hi = a.S;          // largest s with loss_cu[s] <= gi
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if ((int64_t)a.loss_cu[mid] <= gi) lo = mid; else hi = mid;
     }
-    const int s = lo;
+    return lo;
+}
+// Terms of loss token gi of sequence s with log-prob lp; returns d(loss)/d(logp).
+__device__ __forceinline__ float token_terms(const TokenLossArgs& a, int64_t gi, int s, float lp) {
     const float A = a.seq_adv[s];
     const float w = a.aggregation == DPPO_AGG_TOKEN_SUM ? a.seq_coef[s]
                                                        : a.seq_coef[s] / (float)(a.loss_cu[s + 1] - a.loss_cu[s]);
-    const float lp = a.logp[gi];
     const float d_old = lp - a.logp_old[gi];
     const float d_ref = a.logp_ref[gi] - lp;
     const float rho = a.ratio_level == DPPO_RATIO_SEQUENCE ? a.seq_ratio[s] : expf(d_old);
@@ -419,7 +417,14 @@ __global__ void token_loss_kernel(TokenLossArgs a, int64_t n0, int32_t n_c, int3
     a.ell[gi] = -sur + a.beta * kl;
     a.kl[gi] = kl;
     a.clipped[gi] = away ? 1.0f : 0.0f;
-    a.c_chunk[n] = w * g;
+    return w * g;
+}
+__global__ void token_loss_kernel(TokenLossArgs a, int64_t n0, int32_t n_c, int32_t n_cp) {
+    const int n = blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= n_cp) return;
+    if (n >= n_c) { a.c_chunk[n] = 0.0f; return; }
+    const int64_t gi = n0 + n;
+    a.c_chunk[n] = token_terms(a, gi, packed_sequence(a, gi), a.logp[gi]);
 }
 
 // ------------------------------------------------------------------------------------
@@ -443,6 +448,85 @@ __global__ __launch_bounds__(256) void grad_logits_kernel(float* __restrict__ ZG
             g[q] = v < V ? gv : 0.0f;
         }
         row[i] = make_float4(g[0], g[1], g[2], g[3]);
+    }
+}
+
+// float32 path with a token-level ratio: everything between the logits GEMM and the backward GEMMs, one workgroup per loss
+// token: row statistics as in row_stats_kernel, log-prob, the token's terms of Eq. 1, and the row's logits turned into
+// softmax-gradient entries in place. Up to THREADS * NV vectors the row stays in registers in between; a longer one (LONG) is
+// read again, from the L2 (128 KB and more). Bound by HBM: 8 bytes per logit instead of 12, and one launch instead of three:
+// 2400 tokens of V = 32000 92 + 70 + 5 us -> 124 us (5.0 TB/s); 100 tokens of V = 512, whole step 41.6 -> 33.5 us.
+template <int THREADS, int NV, bool LONG>
+__global__ __launch_bounds__(THREADS) void loss_rows_kernel(float* __restrict__ ZG, int32_t V, int32_t Vp,
+                                                            const int32_t* __restrict__ y, TokenLossArgs a, float* __restrict__ logp,
+                                                            int64_t n0) {
+    __shared__ float2 red[THREADS / 64];
+    __shared__ float s_c;
+    const int n = blockIdx.x;
+    const int64_t gi = n0 + n;
+    float* z = ZG + (size_t)n * Vp;
+    const int yt = y[n];
+    const float NONE = -__builtin_inff();
+    const int vectors = (V + 3) / 4;
+    float p[NV][4];
+    auto load = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int i = i0 + u * THREADS;
+            float4 x = make_float4(NONE, NONE, NONE, NONE);
+            if (i < vectors) x = reinterpret_cast<const float4*>(z)[i];
+            const float xx[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[u][q] = i * 4 + q < V ? xx[q] : NONE;
+        }
+    };
+    float2 r = make_float2(NONE, 0.0f);
+    const float zy = z[yt];
+    for (int i0 = threadIdx.x; i0 < (LONG ? vectors : THREADS); i0 += THREADS * NV) {
+        load(i0);
+        float m = NONE, s = 0.0f;
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m = fmaxf(m, p[u][q]);
+        const float ref = m == NONE ? 0.0f : m;
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s += expf(p[u][q] - ref);
+        r = join_row(r, make_float2(m, s));
+    }
+    const int sequence = packed_sequence(a, gi);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) r = join_row(r, make_float2(__shfl_xor(r.x, off, 64), __shfl_xor(r.y, off, 64)));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = r;
+    __syncthreads();
+    r = red[0];
+#pragma unroll
+    for (int w = 1; w < THREADS / 64; ++w) r = join_row(r, red[w]);
+    const float lse = r.x + logf(r.x == NONE ? __builtin_nanf("") : r.y);
+    if (threadIdx.x == 0) {
+        const float lp = zy - lse, c = token_terms(a, gi, sequence, lp);
+        logp[gi] = lp;
+        s_c = c;
+    }
+    __syncthreads();                              // (zy has been read by every thread before the row is overwritten)
+    const float c = s_c;
+    for (int i0 = threadIdx.x; i0 < (LONG ? Vp / 4 : THREADS); i0 += THREADS * NV) {
+        if (LONG) load(i0);
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int i = i0 + u * THREADS;
+            if (i >= Vp / 4) break;
+            float g[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int v = i * 4 + q;
+                const float gv = c * ((v == yt ? 1.0f : 0.0f) - expf(p[u][q] - lse));
+                g[q] = v < V ? gv : 0.0f;
+            }
+            reinterpret_cast<float4*>(z)[i] = make_float4(g[0], g[1], g[2], g[3]);
+        }
     }
 }
 
@@ -652,6 +736,15 @@ void launch_grad_logits_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, 
     const int64_t per_row = ceil_div(Vp / 4, 256);
     dim3 grid((unsigned)n_c, (unsigned)(per_row < 64 ? per_row : 64));
     grad_logits_kernel<<<grid, 256, 0, st>>>(ZG, V, Vp, y, lse, c);
+}
+
+void launch_loss_rows_f32(float* ZG, int32_t V, int32_t Vp, const int32_t* y, const TokenLossArgs& a, float* logp, ChunkView cv,
+                          hipStream_t st) {
+    const unsigned rows = (unsigned)cv.n_c;
+    if (Vp <= 4 * 256 * 4) loss_rows_kernel<256, 4, false><<<rows, 256, 0, st>>>(ZG, V, Vp, y, a, logp, cv.n0);
+    else if (Vp <= 4 * 512 * 8) loss_rows_kernel<512, 8, false><<<rows, 512, 0, st>>>(ZG, V, Vp, y, a, logp, cv.n0);
+    else if (Vp <= 4 * 512 * 16) loss_rows_kernel<512, 16, false><<<rows, 512, 0, st>>>(ZG, V, Vp, y, a, logp, cv.n0);
+    else loss_rows_kernel<512, 8, true><<<rows, 512, 0, st>>>(ZG, V, Vp, y, a, logp, cv.n0);
 }
 
 void launch_seq_reduce(const SeqReduceArgs& a, hipStream_t st) {

@@ -149,6 +149,13 @@ def test_fp32_tiles_and_splits(lib, name, tokens, D, V):
     assert torch.equal(acc, 2.0 * out["dW"])
 
 
+# both sides of the row lengths (padded to 256) that the kernel between the fp32 GEMMs keeps in registers: 4, 8 and 16
+# vectors a thread, longer ones read twice
+@pytest.mark.parametrize("V", [1, 4096, 4097, 16384, 16385, 32768, 32769])
+def test_fp32_rows_between_the_gemms(lib, V):
+    _run_case(lib, _case("tiny", 11, dtype="f32", D=12, V=V), TOL["f32"])
+
+
 # one size for each kind of tile of the fp32 GEMM (32, 64 and 128 wide)
 @pytest.mark.parametrize("tokens,D,V", [(40, 100, 500), (300, 200, 3001), (1100, 203, 9000)])
 def test_fp32_values_beyond_the_bf16_split(lib, tokens, D, V):
