@@ -663,8 +663,12 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         if (s.dtype == 1) {
             {
                 StageTimer tm(DPPO_STAGE_DH_GEMM, st);
-                launch_mfma_dh(cus, G, p.Vp, p.direct_w ? nullptr : w + p.o_wt, W, s.V, cv.n_c, s.D, row_scale, oh,
-                               reinterpret_cast<float*>(w + p.o_dwpart), st);
+                // partial tiles of dH: where dW is overwritten just behind, its memory holds more of them than the workspace
+                float* partial = reinterpret_cast<float*>(w + p.o_dwpart);
+                int64_t floats = (int64_t)(mfma_dw_partial_bytes() / 4);
+                if (!ow.accumulate && (int64_t)s.V * s.D > floats) { partial = dW; floats = (int64_t)s.V * s.D; }
+                launch_mfma_dh(cus, G, p.Vp, p.direct_w ? nullptr : w + p.o_wt, W, s.V, cv.n_c, s.D, row_scale, oh, partial,
+                               floats, st);
             }
             {
                 StageTimer tm(DPPO_STAGE_DW_GEMM, st);

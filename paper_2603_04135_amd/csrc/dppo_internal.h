@@ -188,10 +188,10 @@ int launch_mfma_logits_grad(const void* W, int32_t V, int32_t D, const void* Hc,
                             const int32_t* y, const float* lse, const float* c, const float* zy, void* G, int64_t ldg,
                             int32_t Vp, hipStream_t st);
 // dH rows of a chunk: C[n_c, D] = diag(row_scale) G[n_c, Vp] W[V, D] with G in the blocked chunk layout (pitch Vp)
-// and W read from WT, its transpose in the blocked B-operand layout, or as it lies if WT is NULL; row_scale may be NULL (= 1). `partial`: as for
-// launch_mfma_dw.
+// and W read from WT, its transpose in the blocked B-operand layout, or as it lies if WT is NULL; row_scale may be NULL (= 1). `partial` (or NULL): scratch of
+// partial_floats floats, at least mfma_dw_partial_bytes() bytes, for the partial tiles of a last round that is cut along K.
 void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, const void* W, int32_t V, int32_t n_c, int32_t D,
-                    const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st);
+                    const float* row_scale, const StoreSpec& out, float* partial, int64_t partial_floats, hipStream_t st);
 // dW of a chunk: C[V, D] (+)= G^T HcT^T = sum_n G[n, v] HcT[d, n] (HcT in the blocked B-operand layout, K = n_cp),
 // G read k-major from the same blocks.
 // `partial` is scratch of mfma_dw_partial_bytes() bytes (or NULL): with it, the tiles of a

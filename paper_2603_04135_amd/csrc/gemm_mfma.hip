@@ -212,14 +212,34 @@ static int tail_split(int cus, int tiles, int k_slices, const float* partial, in
 }
 
 namespace {
+// Parts along K for the `tail` tiles of dH's last round where the scratch holds `room` partial tiles. With room for one per
+// compute unit only whole sets of parts fit beside each other (and a round that is more than half full stays whole). With more,
+// several rounds of parts: what is least of rounds / parts of a tile's time and a fifth of a slice's time for every partial tile
+// (512 KB to write and read, and dW's stores behind it find its memory dirty). A round that is partly full is not that much
+// longer than its share, as the chip runs at its power limit: 140, 220 and 250 tiles 3.13, 3.43 and 3.66 ms. V = 151936, D = 2560,
+// dH and dW, whole / split: 3800 tokens (150 tiles) 5.40 / 4.76 ms, 4900 (200) 6.26 / 6.13, 5400 (220) 6.71 / 6.88, 10500 (420)
+// 12.22 / 12.00; D = 4096, V = 100000 2300 tokens (144) 3.57 / 3.22.
+int dh_tail_parts(int cus, int tail, int k_slices, int64_t room) {
+    if (cus <= 0 || tail <= 0) return 1;
+    if (room <= cus) return mfma_tail_parts(cus, tail, k_slices);
+    auto rounds = [&](int items) { return items / cus + (items % cus ? 0.7 + 0.3 * (items % cus) / cus : 0.0); };
+    int best = 1;
+    double best_t = 0.95 * rounds(tail);
+    for (int p = 2; p <= k_slices / 16 && (int64_t)tail * p <= room && tail * p <= 8 * cus; ++p) {
+        const double t = rounds(tail * p) / p + (0.2 * tail * p + 5.0) / k_slices;
+        if (t < best_t) { best_t = t; best = p; }
+    }
+    return best;
+}
+
 template <int BL>
 void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, int b_rows, int32_t n_c, int32_t D,
-               const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st) {
+               const float* row_scale, const StoreSpec& out, float* partial, int64_t partial_floats, hipStream_t st) {
     EpiStoreDH e{nullptr, reinterpret_cast<uint16_t*>(out.C), out.ldc, 0, out.row_map, row_scale, nullptr};
     const int tiles_m = (int)ceil_div(n_c, CfgGrad::BM), tiles_n = (int)ceil_div(D, CfgGrad::BN);
     const int tiles = tiles_m * tiles_n;
-    int tail;
-    const int parts = tail_split(cus, tiles, Vp / CfgGrad::BK, partial, tail);
+    const int tail = cus > 0 ? tiles % cus : 0;
+    const int parts = partial ? dh_tail_parts(cus, tail, Vp / CfgGrad::BK, partial_floats / (CfgGrad::BM * CfgGrad::BN)) : 1;
     if (parts == 1) {
         launch<CfgGrad, A_BLK_ROWS, WG_RANGES, BL>(G, Vp, B, ldb, n_c, D, Vp, e, st, 0, -1, 1, PHASE_DH, b_rows);
         return;
@@ -235,9 +255,9 @@ void launch_dh(int cus, const void* G, int32_t Vp, const void* B, int64_t ldb, i
 }  // namespace
 
 void launch_mfma_dh(int cus, const void* G, int32_t Vp, const void* WT, const void* W, int32_t V, int32_t n_c, int32_t D,
-                    const float* row_scale, const StoreSpec& out, float* partial, hipStream_t st) {
-    if (WT) launch_dh<B_BLK>(cus, G, Vp, WT, 0, 0, n_c, D, row_scale, out, partial, st);
-    else launch_dh<B_KM>(cus, G, Vp, W, D, V, n_c, D, row_scale, out, partial, st);
+                    const float* row_scale, const StoreSpec& out, float* partial, int64_t partial_floats, hipStream_t st) {
+    if (WT) launch_dh<B_BLK>(cus, G, Vp, WT, 0, 0, n_c, D, row_scale, out, partial, partial_floats, st);
+    else launch_dh<B_KM>(cus, G, Vp, W, D, V, n_c, D, row_scale, out, partial, partial_floats, st);
 }
 
 // Whether dW's tiles are walked by resident workgroups, one per compute unit, that load a tile's first slices while the one

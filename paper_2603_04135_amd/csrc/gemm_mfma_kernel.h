@@ -53,7 +53,7 @@ struct TileCtx {
     int m0, n0;        // first row / column of this wavefront's sub-tile
     int bm0, bn0;      // first row / column of the workgroup tile
     int wave_m, wave_n, lane, tid;
-    int item;          // work item of the launch (= tile when the launch does not split K)
+    int slot;          // partial tile of the launch: k_parts consecutive ones for each of its tiles
     char* smem;
 };
 
@@ -176,9 +176,11 @@ __host__ __device__ __forceinline__ void tile_coords(int tile, int tiles_m, int 
     }
 }
 
-// A launch covers gridDim.x work items: item i is part i % k_parts of tile tile0 + i / k_parts,
+// A launch covers n_items work items: with n_tiles = n_items / k_parts, item i is part i / n_tiles of tile tile0 + i % n_tiles,
 // and part p of a tile computes the k-slices [p KT / k_parts, (p + 1) KT / k_parts) of it
-// (k_parts = 1: whole tiles).
+// (k_parts = 1: whole tiles). Neighbouring items are neighbouring tiles at the same k-slices, which share operand panels in
+// L2; with the parts of a tile side by side instead, dH of 650 tokens of D = 4096 (48 tiles in 5
+// parts) fetched 4.9 GB instead of 2.9 (732 against 702 us; 1500 tokens of D = 512, V = 50000 109 against 82).
 enum { WG_ROUNDS = 0, WG_RANGES = 1 };
 template <class Cfg, class Epi, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS>
 __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps LDS targets in SGPRs
     const int wave_m = wave % Cfg::WGM, wave_n = wave / Cfg::WGM;
-    int tm, tn, bm0, bn0, kt_lo, KT;
+    int tm, tn, bm0, bn0, kt_lo, KT, slot;
 
     constexpr int B_KM_CPR = Cfg::BN / 8;                       // B_KM: 16-byte chunks per k-row of the slice
     // One pointer per load (A loads first, then B loads). A_BLK_KM with B_BLK: every load of a tile is at a lane offset that holds for all tiles from a wave-uniform address
@@ -252,9 +254,11 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     auto locate = [&](int item) __attribute__((always_inline)) {
         kt_lo = 0;
         int kt_hi = K / Cfg::BK, item_tile = item;
+        slot = item;
         if (k_parts != 1) {                          // whole tiles (the common case) skip these divisions
-            item_tile = item / k_parts;
-            const int k_part = item - item_tile * k_parts;
+            const int n_tiles = n_items / k_parts, k_part = item / n_tiles;
+            item_tile = item - k_part * n_tiles;
+            slot = item_tile * k_parts + k_part;
             kt_lo = (int)((int64_t)k_part * (K / Cfg::BK) / k_parts);
             kt_hi = (int)((int64_t)(k_part + 1) * (K / Cfg::BK) / k_parts);
         }
@@ -522,7 +526,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         c.M = M; c.N = N; c.tm = tm; c.tn = tn;
         c.bm0 = bm0; c.bn0 = bn0;
         c.m0 = bm0 + wave_m * Cfg::WTM; c.n0 = bn0 + wave_n * Cfg::WTN;
-        c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.item = logical; c.smem = smem;
+        c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.slot = slot; c.smem = smem;
         const bool more = PERSIST && logical + item_step < item_end;
         if (more) {
             logical += item_step;
@@ -569,8 +573,8 @@ template <int KIND>
 struct EpiStore {
     float* Cf; uint16_t* Cb; int64_t ldc; int accumulate; const int32_t* row_map;
     const float* row_scale;   // KIND 1: output row m is multiplied by row_scale[m] if not NULL
-    float* partial;           // if not NULL, work item i stores its whole BM x BN fp32 tile, row-major, at
-                              // partial + i * BM * BN instead (launches that split K; summed up by a second kernel)
+    float* partial;           // if not NULL, the whole BM x BN fp32 tile goes, row-major, to partial + slot * BM * BN instead
+                              // (launches that split K; summed up by a second kernel)
 
     template <class Cfg>
     __device__ __forceinline__ void run(f32x4 (&acc)[Cfg::MI][Cfg::NI], const TileCtx& c) const {
@@ -578,7 +582,7 @@ struct EpiStore {
             // accumulator lane: vocabulary row lane % 16, columns 4 (lane / 16) .. + 3 of each block
             typedef float f32x4v __attribute__((ext_vector_type(4)));
             const int64_t ld = partial ? Cfg::BN : ldc;
-            float* base = partial ? partial + (size_t)c.item * (Cfg::BM * Cfg::BN) : Cf + (size_t)c.bm0 * ldc + c.bn0;
+            float* base = partial ? partial + (size_t)c.slot * (Cfg::BM * Cfg::BN) : Cf + (size_t)c.bm0 * ldc + c.bn0;
             const int rows = partial ? Cfg::BM : c.M - c.bm0, cols = partial ? Cfg::BN : c.N - c.bn0;
             const int r0 = c.wave_m * Cfg::WTM + (c.lane & 15), c0 = c.wave_n * Cfg::WTN + 4 * (c.lane >> 4);
             float* p = base + (size_t)r0 * ld + c0;
@@ -636,7 +640,7 @@ struct EpiStore {
             return;
         }
         if (partial) {       // K-split launch: the raw fp32 tile, row-major, to this work item's slot
-            float* dst = partial + (size_t)c.item * (Cfg::BM * Cfg::BN);
+            float* dst = partial + (size_t)c.slot * (Cfg::BM * Cfg::BN);
 #pragma unroll
             for (int mi = 0; mi < Cfg::MI; ++mi)
 #pragma unroll

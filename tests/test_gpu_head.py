@@ -338,6 +338,28 @@ def test_logits_that_are_not_finite(lib, dtype, tokens, V, kind):
         assert (g[far] < -1e30).all()
 
 
+# 143 and 300 tiles of dH (a last round of 143 and of 44), both operand layouts, against 1188 slices of the vocabulary
+@pytest.mark.parametrize("tokens,D", [(2810, 3328), (7500, 2560)])
+def test_dh_parts_in_the_memory_of_dw(lib, tokens, D):
+    """A call that overwrites dW keeps partial tiles of dH there first, one that adds to it may not: the same dW, and dH the
+    same but for the rounding of another order of the fp32 sums to bf16."""
+    V = 76000
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), device=DEV, generator=g).bfloat16()
+    W = (0.02 * torch.randn((V, D), device=DEV, generator=g)).bfloat16()
+    ids = torch.randint(0, V, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    cu, one = torch.tensor([0, tokens], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    lp = torch.full((tokens,), -11.0, device=DEV)
+    args = (H, W, ids, None, cu, one, one, lp, lp)
+    over = lib.dppo_loss_fwd_bwd(*args)
+    added = lib.dppo_loss_fwd_bwd(*args, dW=torch.zeros((V, D), device=DEV), accumulate_dW=True)
+    assert torch.equal(over["dW"], added["dW"])
+    a, b = over["dH"].float(), added["dH"].float()
+    assert float((a - b).norm() / b.norm()) <= 2.0 ** -9       # each value within a rounding (2^-9) of the same sum, few differ
+    assert torch.isfinite(a).all()
+
+
 @pytest.mark.parametrize("tokens", [40, 300, 700])
 @pytest.mark.parametrize("D,V", [(1088, 33000), (512, 70000)])
 def test_dw_tiles_walked_by_resident_workgroups(lib, tokens, D, V):
