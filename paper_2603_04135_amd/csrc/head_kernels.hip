@@ -60,16 +60,30 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t 
         constexpr int PER = 16 / (int)sizeof(E);
         const uint4* h = reinterpret_cast<const uint4*>(src);
         const uint4* w = reinterpret_cast<const uint4*>(reinterpret_cast<const E*>(a.W) + (size_t)t * a.D);
-        for (int c = lane; c < a.D / PER; c += 64) {
-            const uint4 x = valid ? h[c] : make_uint4(0, 0, 0, 0);
-            reinterpret_cast<uint4*>(dst)[c] = x;
-            if (sizeof(E) == 2) {
-                const uint4 b = w[c];
-                const uint32_t aw[4] = {x.x, x.y, x.z, x.w}, bw[4] = {b.x, b.y, b.z, b.w};
+        // all loads of up to 8 vectors first: one by one, few tokens wait for memory D / 512 times over (33 tokens of D = 2560
+        // 8.2 -> 5.0 us, 333 of D = 4096 12.4 -> 6.6, 8600 of D = 2560 30 -> 25.5)
+        constexpr int U = 8;
+        const int vectors = a.D / PER;
+        for (int c0 = lane; c0 < vectors; c0 += 64 * U) {
+            uint4 x[U], b[U];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    s = fmaf(__uint_as_float(aw[k] << 16), __uint_as_float(bw[k] << 16), s);
-                    s = fmaf(__uint_as_float(aw[k] & 0xffff0000u), __uint_as_float(bw[k] & 0xffff0000u), s);
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * 64;
+                x[u] = valid && c < vectors ? h[c] : make_uint4(0, 0, 0, 0);
+                if (sizeof(E) == 2) b[u] = c < vectors ? w[c] : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * 64;
+                if (c >= vectors) break;
+                reinterpret_cast<uint4*>(dst)[c] = x[u];
+                if (sizeof(E) == 2) {
+                    const uint32_t aw[4] = {x[u].x, x[u].y, x[u].z, x[u].w}, bw[4] = {b[u].x, b[u].y, b[u].z, b[u].w};
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        s = fmaf(__uint_as_float(aw[k] << 16), __uint_as_float(bw[k] << 16), s);
+                        s = fmaf(__uint_as_float(aw[k] & 0xffff0000u), __uint_as_float(bw[k] & 0xffff0000u), s);
+                    }
                 }
             }
         }
