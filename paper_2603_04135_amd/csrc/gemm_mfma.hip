@@ -221,14 +221,16 @@ namespace {
 // 12.22 / 12.00; D = 4096, V = 100000 2300 tokens (144) 3.57 / 3.22.
 int dh_tail_parts(int cus, int tail, int k_slices, int64_t room) {
     if (cus <= 0 || tail <= 0) return 1;
-    if (room <= cus) return mfma_tail_parts(cus, tail, k_slices);
-    auto rounds = [&](int items) { return items / cus + (items % cus ? 0.7 + 0.3 * (items % cus) / cus : 0.0); };
-    int best = 1;
-    double best_t = 0.95 * rounds(tail);
-    for (int p = 2; p <= k_slices / 16 && (int64_t)tail * p <= room && tail * p <= 8 * cus; ++p) {
-        const double t = rounds(tail * p) / p + (0.2 * tail * p + 5.0) / k_slices;
-        if (t < best_t) { best_t = t; best = p; }
-    }
+    int best = mfma_tail_parts(cus, tail, k_slices);
+    if (room <= cus) return best;
+    auto time = [&](int p) {
+        const int items = tail * p;
+        const double rounds = items / cus + (items % cus ? 0.7 + 0.3 * (items % cus) / cus : 0.0);
+        return rounds / p + (p > 1 ? (0.2 * items + 5.0) / k_slices : 0.0);
+    };
+    double best_t = 0.98 * time(best);
+    for (int p = best + 1; p <= k_slices / 16 && (int64_t)tail * p <= room && tail * p <= 8 * cus; ++p)
+        if (time(p) < best_t) { best_t = time(p); best = p; }
     return best;
 }
 
