@@ -224,12 +224,16 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // stay in the workspace for the backward pass: as float32 logits (float32 path), or as bf16 exponentials against the per-token reference left in the bref region (bf16 path).
 int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, const void* H, const void* W,
                    const int32_t* ids, const int32_t* loss_pos, ChunkView cv, bool keep_z,
-                   float* logp_all, float* lse_all, int32_t* status, hipStream_t st, bool logits_only = false) {
+                   float* logp_all, float* lse_all, int32_t* status, hipStream_t st, bool logits_only = false, bool score_only = false) {
     void* Hc = ws + p.o_hc;
     int32_t* y = reinterpret_cast<int32_t*>(ws + p.o_y);
     float* zy = reinterpret_cast<float*>(ws + p.o_zy);
     float* lse_c = reinterpret_cast<float*>(ws + p.o_lse);
-    {
+    const TokenArgs tokens{H, W, ids, loss_pos, s.T, s.D, s.V, status};
+    // Nothing but the log-probs is wanted (no backward follows): the logits GEMM reads the tokens' rows of H where they are, the
+    // statistics kernel looks up the targets.
+    const bool gathered = !score_only || (s.dtype == 1 && !mfma_logits_reads_tokens(cv.n_c));
+    if (gathered) {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         const bool exp_ref = s.dtype == 1 && keep_z;
         GatherArgs ga{H, W, ids, loss_pos, s.T, s.D, s.V, Hc, y, reinterpret_cast<int32_t*>(ws + p.o_rowc), status, zy,
@@ -260,15 +264,20 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, 
         LogitsPart lp;
         {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
-            lp = launch_mfma_logits(W, s.V, s.D, Hc, cv.n_c, cv.n_cp, part, st);
+            lp = launch_mfma_logits(W, s.V, s.D, Hc, tokens, cv, part, zy, st);
         }
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         launch_combine_logprob(part, lp, zy, cv, lse_c, logp_all, lse_all, st);
     } else {
-        GemmF32 g{reinterpret_cast<const float*>(Hc), s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
-                  reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 0};
+        const float* A = gathered ? reinterpret_cast<const float*>(Hc)
+                                  : reinterpret_cast<const float*>(H) + (loss_pos ? 0 : (size_t)cv.n0 * s.D);
+        GemmF32 g{A, s.D, 0, reinterpret_cast<const float*>(W), s.D, 0, cv.n_c, s.V, s.D,
+                  reinterpret_cast<float*>(ws + p.o_zg), p.Vp, 0, nullptr, nullptr, 0,
+                  gathered || !loss_pos ? nullptr : loss_pos + cv.n0, (int32_t)s.T};
         launch_gemm_f32(g, cus, st);
-        if (!logits_only)
+        if (!gathered)
+            launch_score_rows_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, tokens, cv, logp_all, lse_all, st);
+        else if (!logits_only)
             launch_row_stats_f32(reinterpret_cast<const float*>(ws + p.o_zg), p.Vp, s.V, y, cv, lse_c, logp_all,
                                  lse_all, st);
     }
@@ -483,7 +492,7 @@ int dppo_token_logprob(const dppo_head_shape* shape, const void* H, const void* 
         cv.n0 = n0;
         cv.n_c = (int32_t)((s.N - n0) < p.n_cp ? (s.N - n0) : p.n_cp);
         cv.n_cp = round_up32(cv.n_c, CHUNK_ALIGN);
-        if (int rc = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, cv, false, logp, lse, status, st)) return rc;
+        if (int rc = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, cv, false, logp, lse, status, st, false, true)) return rc;
     }
     return check_launch("dppo_token_logprob");
 }
@@ -585,7 +594,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
 
     if (seq_level && !ahead) {
         for (int64_t c = 0; c < p.n_chunks; ++c)
-            if (int rc2 = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, view(c), false, logp_all, nullptr, status, st)) return rc2;
+            if (int rc2 = chunk_forward(s, p, cus, w, H, W, ids, loss_pos, view(c), false, logp_all, nullptr, status, st, false, true)) return rc2;
         launch_seq_ratio(loss_cu, S, logp_all, logp_old, seq_ratio, 0, s.N, nullptr, st);
     }
 
@@ -678,10 +687,10 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
         } else {
             const float* Gf = reinterpret_cast<const float*>(G);
             GemmF32 gh{Gf, p.Vp, 0, reinterpret_cast<const float*>(W), s.D, 1, cv.n_c, s.D, s.V, reinterpret_cast<float*>(oh.C),
-                       oh.ldc, 0, oh.row_map, p.f32_parts > 1 ? reinterpret_cast<float*>(wc + p.o_fpart) : nullptr, (int64_t)p.f32_parts * p.n_cp * s.D};
+                       oh.ldc, 0, oh.row_map, p.f32_parts > 1 ? reinterpret_cast<float*>(wc + p.o_fpart) : nullptr, (int64_t)p.f32_parts * p.n_cp * s.D, nullptr, 0};
             launch_gemm_f32(gh, cus, st);
             GemmF32 gw{Gf, p.Vp, 1, reinterpret_cast<const float*>(wc + p.o_hc), s.D, 1, s.V, s.D, cv.n_c,
-                       reinterpret_cast<float*>(ow.C), ow.ldc, ow.accumulate, nullptr, nullptr, 0};
+                       reinterpret_cast<float*>(ow.C), ow.ldc, ow.accumulate, nullptr, nullptr, 0, nullptr, 0};
             launch_gemm_f32(gw, cus, st);
         }
         return DPPO_OK;

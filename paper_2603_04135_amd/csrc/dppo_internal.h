@@ -35,6 +35,13 @@ void launch_gather_f32(int64_t n, const int32_t* idx, const float* src, float* d
 
 // ---- layout / elementwise kernels (head_kernels.hip) -------------------------
 // E = element type of H and W (float or bf16 stored as uint16_t).
+// What a loss token is: its row of H and its target (clamped into range, reported in *status as DPPO_HEAD_BAD_*).
+struct TokenArgs {
+    const void* H; const void* W; const int32_t* ids; const int32_t* loss_pos;
+    int64_t T; int32_t D, V;
+    int32_t* status;
+};
+
 struct ChunkView {
     int64_t n0;    // first loss token of the chunk
     int32_t n_c;   // loss tokens in the chunk
@@ -93,6 +100,9 @@ void launch_scale_transpose_bf16(const void* Hc, const float* scale, int32_t n_c
 // fp32 path: row statistics straight from stored logits Z[n_cp, ldz].
 void launch_row_stats_f32(const float* Z, int64_t ldz, int32_t V, const int32_t* y, ChunkView cv,
                           float* lse_chunk, float* logp_out, float* lse_out, hipStream_t st);
+// The same for tokens that were not gathered.
+void launch_score_rows_f32(const float* Z, int64_t ldz, const TokenArgs& a, ChunkView cv, float* logp_out, float* lse_out,
+                           hipStream_t st);
 
 struct TokenLossArgs {
     const int32_t* loss_cu; int32_t S;
@@ -153,6 +163,7 @@ struct GemmF32 {
     float* C; int64_t ldc; int accumulate;
     const int32_t* row_map;
     float* partial; int64_t partial_floats;
+    const int32_t* a_map; int32_t a_rows;      // K-contiguous A: row m is row a_map[m] of a_rows (clamped) if a_map is not NULL
 };
 int gemm_f32_max_parts(int64_t K);
 void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st);
@@ -173,8 +184,11 @@ int mfma_tail_parts(int cus, int tail, int k_slices);
 int mfma_dh_slices(int32_t V);
 int32_t mfma_vocab_tile();
 constexpr int32_t LOGITS_FEW_TOKENS = 128;
-LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_c, int32_t n_cp, float2* part,
-                              hipStream_t st);
+// Columns of up to 192 tokens read the tokens' rows from H themselves: where mfma_logits_reads_tokens says so, nothing needs to be
+// gathered, and the launch also looks the tokens up (status word) and writes their target logits to zy.
+bool mfma_logits_reads_tokens(int32_t n_c);
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, ChunkView cv, float2* part,
+                              float* zy, hipStream_t st);
 // Same GEMM; stores E[n, v] = exp(z[n, v] - bref[n]) as bf16 (0 for V <= v < Vp) to E, a [n_cp, lde]
 // matrix in the blocked chunk layout (blocks of 64 tokens x 256 vocabulary entries, each
 // contiguous; block (i, j) at element i * 64 * lde + j * 16384); lde = Vp must be a multiple of

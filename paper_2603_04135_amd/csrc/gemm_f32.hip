@@ -43,8 +43,20 @@ struct F32Args {
     int tiles_n, k_parts, slices_per_part;
     float* C; int64_t ldc; int accumulate;
     const int32_t* row_map;      // output row = row_map[m] if not NULL
+    const int32_t* a_map;        // K-contiguous A: row m of it is row a_map[m] (clamped to the a_rows there are) if not NULL
+    int a_rows;
     float* partial;              // k_parts > 1: part p of the sums goes to partial + p * M * N, row-major
 };
+
+// Row r of an operand of `rows` rows (beyond them: the last one, for outputs that are not stored), through its map.
+__device__ __forceinline__ int operand_row(int r, int rows, const int32_t* map, int map_rows) {
+    r = r < rows ? r : rows - 1;
+    if (map) {
+        r = map[r];
+        r = r < 0 ? 0 : r < map_rows ? r : map_rows - 1;
+    }
+    return r;
+}
 
 // x = h + m + l, element pairs packed into 32-bit words.
 __device__ __forceinline__ uint32_t pack_bf16(f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }
@@ -99,11 +111,11 @@ struct Operand {
 
     // Start of the thread's chunks in a whole slice at k = 0 of the tile at row0. Rows are clamped: those beyond the matrix only
     // reach outputs that are not stored.
-    static __device__ __forceinline__ void source(const float* (&x)[UNITS], const float* X, int64_t ld, int row0, int rows, int t) {
+    static __device__ __forceinline__ void source(const float* (&x)[UNITS], const float* X, int64_t ld, int row0, int rows, int t,
+                                                  const int32_t* map, int map_rows) {
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
-            int r = row0 + row_of(g, t);
-            r = r < rows ? r : rows - 1;
+            const int r = operand_row(row0 + row_of(g, t), rows, map, map_rows);
             const int k = chunk_of(g, t) * 8;
             x[g] = KM ? X + (size_t)k * ld + r : X + (size_t)r * ld + k;
         }
@@ -130,13 +142,12 @@ struct Operand {
     }
     // The same element by element, with k-values beyond K read as zero.
     static __device__ __forceinline__ void load_tail(float (&v)[UNITS][8], const float* __restrict__ X, int64_t ld, int row0, int rows,
-                                                     int k0, int K, int tid, int first) {
+                                                     int k0, int K, int tid, int first, const int32_t* map, int map_rows) {
         asm volatile("" : "+v"(tid));   // this one slice's addresses are formed here, not kept in registers over the K loop
         const int t = tid - first;
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) {
-            int r = row0 + unit_row(u, t);
-            r = r < rows ? r : rows - 1;
+            const int r = operand_row(row0 + unit_row(u, t), rows, map, map_rows);
             const int k = k0 + unit_chunk(u, t) * 8;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -198,15 +209,16 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
     char* s_x = for_a ? s_a : s_b;
     const float* src[UNITS];
     int at[UNITS];
-    if (ALIKE || for_a) { OA::source(src, X, ld, row0, rows, t); OA::places(at, t); }
-    else { OB::source(src, X, ld, row0, rows, t); OB::places(at, t); }
+    const int32_t* map = !A_KM && for_a ? g.a_map : nullptr;
+    if (ALIKE || for_a) { OA::source(src, X, ld, row0, rows, t, map, g.a_rows); OA::places(at, t); }
+    else { OB::source(src, X, ld, row0, rows, t, nullptr, 0); OB::places(at, t); }
     auto load = [&](int k0) __attribute__((always_inline)) {
         if (ALIKE || for_a) {
             if (OA::safe(ld, row0, rows, k0, g.K)) OA::load(v, src, ld, k0);
-            else OA::load_tail(v, X, ld, row0, rows, k0, g.K, tid, first);
+            else OA::load_tail(v, X, ld, row0, rows, k0, g.K, tid, first, map, g.a_rows);
         } else {
             if (OB::safe(ld, row0, rows, k0, g.K)) OB::load(v, src, ld, k0);
-            else OB::load_tail(v, X, ld, row0, rows, k0, g.K, tid, first);
+            else OB::load_tail(v, X, ld, row0, rows, k0, g.K, tid, first, nullptr, 0);
         }
     };
     if (tid == 0) s_big = -1;
@@ -348,12 +360,12 @@ template <bool KM>
 struct Direct {
     typedef float Vec2 __attribute__((ext_vector_type(2), aligned(4)));
     typedef float Vec4 __attribute__((ext_vector_type(4), aligned(4)));
-    static __device__ __forceinline__ void load(float (&v)[2][8], const float* __restrict__ X, int64_t ld, int row0, int rows, int k0,
-                                                int K, int lane) {
-        const int r0 = row0 + 2 * (lane & 15), k = k0 + 8 * (lane >> 4);
+    static __device__ __forceinline__ void load(float (&v)[2][8], const float* __restrict__ X, int64_t ld, int row0, int rows,
+                                                const int (&r)[2], int k0, int K, int lane) {
+        const int k = k0 + 8 * (lane >> 4);
         const bool whole = k0 + 32 <= K;
         if (KM && whole && (row0 + 32 <= rows || (int64_t)(K - k0 - 32) * ld >= 1)) {     // (as in Operand::safe)
-            const float* x = X + (size_t)k * ld + (r0 < rows ? r0 : rows - 1);
+            const float* x = X + (size_t)k * ld + r[0];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const Vec2 a = *reinterpret_cast<const Vec2*>(x + (size_t)j * ld);
@@ -363,7 +375,7 @@ struct Direct {
         } else if (!KM && whole) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const float* x = X + (size_t)(r0 + i < rows ? r0 + i : rows - 1) * ld + k;
+                const float* x = X + (size_t)r[i] * ld + k;
                 const Vec4 a = *reinterpret_cast<const Vec4*>(x), b = *reinterpret_cast<const Vec4*>(x + 4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { v[i][j] = a[j]; v[i][4 + j] = b[j]; }
@@ -371,11 +383,10 @@ struct Direct {
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const int r = r0 + i < rows ? r0 + i : rows - 1;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int kc = k + j < K ? k + j : K - 1;
-                    const float x = KM ? X[(size_t)kc * ld + r] : X[(size_t)r * ld + kc];
+                    const float x = KM ? X[(size_t)kc * ld + r[i]] : X[(size_t)r[i] * ld + kc];
                     v[i][j] = k + j < K ? x : 0.0f;
                 }
             }
@@ -397,9 +408,15 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i / 2][i % 2] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float a[DEPTH][2][8], b[DEPTH][2][8];
+    int ra[2], rb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        ra[i] = operand_row(m0 + 2 * (lane & 15) + i, g.M, A_KM ? nullptr : g.a_map, g.a_rows);
+        rb[i] = operand_row(n0 + 2 * (lane & 15) + i, g.N, nullptr, 0);
+    }
     auto load = [&](int d, int k0) __attribute__((always_inline)) {
-        Direct<A_KM>::load(a[d], g.A, g.lda, m0, g.M, k0, g.K, lane);
-        Direct<B_KM>::load(b[d], g.B, g.ldb, n0, g.N, k0, g.K, lane);
+        Direct<A_KM>::load(a[d], g.A, g.lda, m0, g.M, ra, k0, g.K, lane);
+        Direct<B_KM>::load(b[d], g.B, g.ldb, n0, g.N, rb, k0, g.K, lane);
     };
     auto products = [&](int d) __attribute__((always_inline)) {
         float top = 0.0f;
@@ -491,6 +508,7 @@ F32Args args_of(const GemmF32& p, int edge, int bk, int parts) {
     g.k_parts = parts;
     g.slices_per_part = (int)ceil_div(ceil_div(p.K, bk), parts);
     g.C = p.C; g.ldc = p.ldc; g.accumulate = p.accumulate; g.row_map = p.row_map; g.partial = p.partial;
+    g.a_map = p.a_map; g.a_rows = p.a_rows;
     return g;
 }
 

@@ -47,16 +47,16 @@ enum { PHASE_LOGITS = 0, PHASE_DH = 1, PHASE_DW = 2 };
 template <class Cfg, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B_ROWS, class Epi>
 void launch(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N, int K, const Epi& epi,
             hipStream_t st, int tile0 = 0, int n_tiles = -1, int k_parts = 1, int phase_stage = -1, int b_rows = 0,
-            int max_workgroups = 0) {
+            int max_workgroups = 0, const int32_t* b_map = nullptr, int extra_workgroups = 0) {
     const int tiles_m = (int)ceil_div(M, Cfg::BM), tiles_n = (int)ceil_div(N, Cfg::BN);
     if (n_tiles < 0) n_tiles = tiles_m * tiles_n - tile0;
     if (n_tiles <= 0) return;
     unsigned long long* phase = phase_stage >= 0 && k_parts == 1 ? g_phase_counters.load() : nullptr;
     if (phase) phase += 4 * phase_stage;
     const int items = n_tiles * k_parts, workgroups = max_workgroups > 0 && items > max_workgroups ? max_workgroups : items;
-    gemm_nt_kernel<Cfg, Epi, AM, MAP, BL><<<dim3(workgroups), dim3(Cfg::NT), lds_request<Cfg, Epi>(), st>>>(
+    gemm_nt_kernel<Cfg, Epi, AM, MAP, BL><<<dim3(workgroups + extra_workgroups), dim3(Cfg::NT), lds_request<Cfg, Epi>(), st>>>(
         reinterpret_cast<const uint16_t*>(A), lda, reinterpret_cast<const uint16_t*>(B), ldb, b_rows, M, N, K, tiles_m,
-        tiles_n, tile0, k_parts, items, epi, phase);
+        tiles_n, tile0, k_parts, items, epi, phase, b_map);
 }
 
 // Sums the k_parts partial tiles of each of the n_tiles tiles from tile0 on, in part order, into
@@ -128,9 +128,9 @@ int mfma_setup(int* compute_units) {
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_BLK>();
         if (e == hipSuccess) e = allow_lds<CfgGrad, EpiStoreDH, A_BLK_ROWS, WG_RANGES, B_KM>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogits>();
-        if (e == hipSuccess) e = allow_lds<CfgBig192, EpiLogits>();
-        if (e == hipSuccess) e = allow_lds<CfgFew<96>, EpiLogits>();
-        if (e == hipSuccess) e = allow_lds<CfgFew<128>, EpiLogits>();
+        if (e == hipSuccess) e = allow_lds<CfgBig192, EpiScore, A_ROWS, WG_ROUNDS, B_MAP>();
+        if (e == hipSuccess) e = allow_lds<CfgFew<96>, EpiScore, A_ROWS, WG_ROUNDS, B_MAP>();
+        if (e == hipSuccess) e = allow_lds<CfgFew<128>, EpiScore, A_ROWS, WG_ROUNDS, B_MAP>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsExp>();
         if (e == hipSuccess) e = allow_lds<CfgBig, EpiLogitsGrad>();
         d.status = e == hipSuccess ? (int)DPPO_OK
@@ -147,21 +147,32 @@ void mfma_set_phase_counters(unsigned long long* counters) { g_phase_counters.st
 int32_t mfma_logits_row_tiles(int32_t V) { return (int32_t)ceil_div(V, CfgBig::BM); }
 int32_t mfma_vocab_tile() { return CfgBig::BM; }
 
-LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_c, int32_t n_cp, float2* part,
-                              hipStream_t st) {
-    LogitsPart lp{mfma_logits_row_tiles(V), n_cp};
+// Columns of 192 tokens where they cover the chunk with as many tiles as columns of 256.
+static bool narrow_columns(int32_t n_c) { return n_c <= (int32_t)ceil_div(n_c, CfgBig::BN) * CfgBig192::BN; }
+bool mfma_logits_reads_tokens(int32_t n_c) { return narrow_columns(n_c); }
+
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, ChunkView cv, float2* part,
+                              float* zy, hipStream_t st) {
+    const int32_t n_c = cv.n_c;
+    LogitsPart lp{mfma_logits_row_tiles(V), cv.n_cp};
+    const int32_t* map = tokens.loss_pos ? tokens.loss_pos + cv.n0 : nullptr;
+    const uint16_t* rows = reinterpret_cast<const uint16_t*>(tokens.H) + (map ? 0 : (size_t)cv.n0 * D);
+    auto narrow = [&](auto cfg, int64_t pitch) {
+        typedef decltype(cfg) Cfg;
+        EpiScore e{{part, pitch}, tokens, cv.n0, n_c, zy};
+        launch<Cfg, A_ROWS, WG_ROUNDS, B_MAP>(W, D, rows, D, V, n_c, D, e, st, 0, -1, 1, -1, (int)tokens.T, 0, map,
+                                              (int)ceil_div(n_c, Cfg::NW));
+    };
     if (n_c <= LOGITS_FEW_TOKENS) {
         // as many pairs in all as with 256-row tiles: twice the row tiles, half the pitch
         lp = LogitsPart{(int32_t)ceil_div(V, CfgFew<128>::BM), LOGITS_FEW_TOKENS};
-        EpiLogits e{part, lp.pitch};
-        if (n_c <= 96) launch<CfgFew<96>>(W, D, Hc, D, V, 96, D, e, st);
-        else launch<CfgFew<128>>(W, D, Hc, D, V, 128, D, e, st);
-        return lp;
+        if (n_c <= 96) narrow(CfgFew<96>{}, lp.pitch);
+        else narrow(CfgFew<128>{}, lp.pitch);
+    } else if (narrow_columns(n_c)) {
+        narrow(CfgBig192{}, cv.n_cp);
+    } else {
+        launch<CfgBig>(W, D, Hc, D, V, cv.n_cp, D, EpiLogits{part, cv.n_cp}, st, 0, -1, 1, PHASE_LOGITS);
     }
-    EpiLogits e{part, n_cp};
-    const int32_t columns = (int32_t)ceil_div(n_c, CfgBig::BN);
-    if (n_c <= columns * CfgBig192::BN) launch<CfgBig192>(W, D, Hc, D, V, columns * CfgBig192::BN, D, e, st);
-    else launch<CfgBig>(W, D, Hc, D, V, n_cp, D, e, st, 0, -1, 1, PHASE_LOGITS);
     return lp;
 }
 

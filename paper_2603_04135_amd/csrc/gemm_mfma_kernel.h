@@ -32,7 +32,7 @@
 #pragma once
 #include <type_traits>
 
-#include "dppo_internal.h"
+#include "token_rows.h"
 
 namespace dppo {
 namespace mfma {
@@ -153,7 +153,8 @@ enum { A_ROWS = 0, A_BLK_ROWS = 1, A_BLK_KM = 2 };
 //           cycles and 2.5 % of dW's). N is padded to whole blocks; ldb is not used.
 //   B_KM    B is [K, N] row-major, ldb = row pitch, with b_rows <= K rows in memory (the last one is read in place of
 //           those beyond: the A operand is zero there); operands are gathered by transposing reads as for A_BLK_KM.
-enum { B_ROWS = 0, B_BLK = 1, B_KM = 2 };
+//   B_MAP   B_ROWS whose row n is row b_map[n] (clamped to the b_rows there are), or n where b_map is NULL.
+enum { B_ROWS = 0, B_BLK = 1, B_KM = 2, B_MAP = 3 };
 constexpr int BLK_R = 64, BLK_C = 256;
 __host__ __device__ __forceinline__ size_t blk_offset(int64_t r, int64_t c, int64_t ld) {
     return (size_t)(r / BLK_R) * BLK_R * ld + (size_t)(c / BLK_C) * (BLK_R * BLK_C) + (r % BLK_R) * BLK_C + c % BLK_C;
@@ -186,12 +187,20 @@ template <class Cfg, class Epi, int AM = A_ROWS, int MAP = WG_ROUNDS, int BL = B
 __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                              const uint16_t* __restrict__ B, int64_t ldb, int b_rows, int M,
                                                              int N, int K, int tiles_m, int tiles_n, int tile0,
-                                                             int k_parts, int n_items, Epi epi, unsigned long long* phase) {
+                                                             int k_parts, int n_items, Epi epi, unsigned long long* phase,
+                                                             const int32_t* __restrict__ b_map) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // phase (benchmark aid, normally NULL): 4 counters that every workgroup adds to: shader cycles from
     // its start to the first slice in LDS, in the main loop, in the epilogue, and 1. A resident workgroup adds once per
     // tile: from the second one on, the first of them is the wait for slices that were loaded under the epilogue before.
     unsigned long long pt0 = 0, pt1 = 0, pt2 = 0;
+    if constexpr (BL == B_MAP) {
+        // workgroups behind the items look up tokens, one per wavefront, beside the last tiles
+        if ((int)blockIdx.x >= n_items) {
+            epi.look_up(((int)blockIdx.x - n_items) * Cfg::NW + (int)(threadIdx.x >> 6), threadIdx.x & 63);
+            return;
+        }
+    }
     if (phase) pt0 = clock64();
     constexpr bool A_KM = AM == A_BLK_KM;
     constexpr int MI = Cfg::MI, NI = Cfg::NI, KK = Cfg::KK, LPS = Cfg::LPS;
@@ -289,6 +298,10 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
             int r = (isA ? bm0 : bn0) + row;
             const int lim = isA ? M : N;
             r = r < lim ? r : lim - 1;
+            if (BL == B_MAP && !isA && b_map) {
+                r = b_map[r];
+                r = r < 0 ? 0 : r < b_rows ? r : b_rows - 1;
+            }
             if (AM == A_BLK_ROWS && isA) {
                 static_assert(AM != A_BLK_ROWS || BLK_C % Cfg::BK == 0, "a slice stays inside one block column");
                 pl[i] = A + blk_offset(r, kc * 8, lda);
@@ -783,6 +796,23 @@ struct EpiLogits {
     template <class Cfg>
     static constexpr int lds_bytes() { return Cfg::WGM * Cfg::BN * 8; }
     static constexpr bool SWAP = false;
+};
+
+// The same where the tokens were not gathered (B_MAP): their target logits, formed as gather_rows_kernel forms them, and the
+// status word come from extra workgroups of the launch. Scoring is then two launches, and the lookup costs no time of its own
+// (33 tokens of D = 2560, V = 151936 171 -> 162 us; with the lookup in the combining kernel 165).
+struct EpiScore : EpiLogits {
+    TokenArgs tokens; int64_t n0; int n_c; float* zy;
+    __device__ __forceinline__ void look_up(int n, int lane) const {
+        if (n >= n_c) return;
+        int64_t row;
+        int32_t t;
+        const int flags = locate_token(tokens.ids, tokens.loss_pos, tokens.T, tokens.V, n0 + n, row, t);
+        if (flags != 0 && tokens.status != nullptr && lane == 0) atomicOr(tokens.status, flags);
+        const float z = dot_bf16_rows(reinterpret_cast<const uint16_t*>(tokens.H) + (size_t)row * tokens.D,
+                                      reinterpret_cast<const uint16_t*>(tokens.W) + (size_t)t * tokens.D, tokens.D, lane);
+        if (lane == 0) zy[n] = z;
+    }
 };
 
 // Rows = vocabulary entries, columns = tokens. What the backward pass needs of the logits is the

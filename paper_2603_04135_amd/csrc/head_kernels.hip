@@ -7,7 +7,7 @@
 // transposes go through padded LDS tiles.
 #include <type_traits>
 
-#include "dppo_internal.h"
+#include "token_rows.h"
 
 namespace dppo {
 namespace {
@@ -38,15 +38,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t 
     int32_t t = 0;
     const bool valid = n < n_c;
     if (valid) {
-        int flags = 0;
-        row = a.loss_pos ? (int64_t)a.loss_pos[n0 + n] : n0 + n;
-        int64_t pos = a.loss_pos ? row + 1 : row;
-        if (row < 0 || pos >= a.T) flags |= DPPO_HEAD_BAD_POSITION;
-        row = row < 0 ? 0 : (row >= a.T ? a.T - 1 : row);
-        pos = pos < 0 ? 0 : (pos >= a.T ? a.T - 1 : pos);
-        t = a.ids[pos];
-        if (t < 0 || t >= a.V) flags |= DPPO_HEAD_BAD_TARGET;
-        t = t < 0 ? 0 : (t >= a.V ? a.V - 1 : t);
+        const int flags = locate_token(a.ids, a.loss_pos, a.T, a.V, n0 + n, row, t);
         if (flags != 0 && a.status != nullptr && lane == 0) atomicOr(a.status, flags);
     }
     if (lane == 0) {
@@ -77,14 +69,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a, int64_t 
                 const int c = c0 + u * 64;
                 if (c >= vectors) break;
                 reinterpret_cast<uint4*>(dst)[c] = x[u];
-                if (sizeof(E) == 2) {
-                    const uint32_t aw[4] = {x[u].x, x[u].y, x[u].z, x[u].w}, bw[4] = {b[u].x, b[u].y, b[u].z, b[u].w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        s = fmaf(__uint_as_float(aw[k] << 16), __uint_as_float(bw[k] << 16), s);
-                        s = fmaf(__uint_as_float(aw[k] & 0xffff0000u), __uint_as_float(bw[k] & 0xffff0000u), s);
-                    }
-                }
+                if (sizeof(E) == 2) s = dot_bf16x8(x[u], b[u], s);
             }
         }
     } else {
@@ -356,13 +341,21 @@ __device__ __forceinline__ float2 join_row(float2 a, float2 b) {
     return make_float2(m, a.y * expf(a.x - ref) + b.y * expf(b.x - ref));
 }
 __global__ __launch_bounds__(ROW_THREADS) void row_stats_kernel(const float* __restrict__ Z, int64_t ldz, int32_t V,
-                                                                const int32_t* __restrict__ y, int64_t n0, int32_t n_c,
+                                                                const int32_t* __restrict__ y, TokenArgs a, int64_t n0, int32_t n_c,
                                                                 float* __restrict__ lse_chunk, float* __restrict__ logp_out,
                                                                 float* __restrict__ lse_out) {
     __shared__ float2 red[ROW_THREADS / 64];
     const int n = blockIdx.x;
     if (n >= n_c) { if (threadIdx.x == 0) lse_chunk[n] = 0.0f; return; }
     const float* z = Z + (size_t)n * ldz;
+    int32_t target;                               // (y NULL: the token was not gathered)
+    if (y != nullptr) {
+        target = y[n];
+    } else {
+        int64_t row;
+        const int flags = locate_token(a.ids, a.loss_pos, a.T, a.V, n0 + n, row, target);
+        if (flags != 0 && a.status != nullptr && threadIdx.x == 0) atomicOr(a.status, flags);
+    }
     const float NONE = -__builtin_inff();
     float2 r = make_float2(NONE, 0.0f);
     const int vectors = (V + 3) / 4;
@@ -396,8 +389,8 @@ __global__ __launch_bounds__(ROW_THREADS) void row_stats_kernel(const float* __r
     if (threadIdx.x == 0) {
         for (int w = 1; w < ROW_THREADS / 64; ++w) r = join_row(r, red[w]);
         const float lse = r.x + logf(r.x == NONE ? __builtin_nanf("") : r.y);
-        lse_chunk[n] = lse;
-        logp_out[n0 + n] = z[y[n]] - lse;
+        if (lse_chunk) lse_chunk[n] = lse;
+        logp_out[n0 + n] = z[target] - lse;
         if (lse_out) lse_out[n0 + n] = lse;
     }
 }
@@ -726,7 +719,12 @@ void launch_combine_logprob(const float2* part, LogitsPart lp, const float* zy, 
 
 void launch_row_stats_f32(const float* Z, int64_t ldz, int32_t V, const int32_t* y, ChunkView cv, float* lse_chunk,
                           float* logp_out, float* lse_out, hipStream_t st) {
-    row_stats_kernel<<<(unsigned)cv.n_cp, ROW_THREADS, 0, st>>>(Z, ldz, V, y, cv.n0, cv.n_c, lse_chunk, logp_out, lse_out);
+    row_stats_kernel<<<(unsigned)cv.n_cp, ROW_THREADS, 0, st>>>(Z, ldz, V, y, TokenArgs{}, cv.n0, cv.n_c, lse_chunk, logp_out, lse_out);
+}
+
+void launch_score_rows_f32(const float* Z, int64_t ldz, const TokenArgs& a, ChunkView cv, float* logp_out, float* lse_out,
+                           hipStream_t st) {
+    row_stats_kernel<<<(unsigned)cv.n_c, ROW_THREADS, 0, st>>>(Z, ldz, a.V, nullptr, a, cv.n0, cv.n_c, nullptr, logp_out, lse_out);
 }
 
 void launch_token_loss(const TokenLossArgs& a, ChunkView cv, hipStream_t st) {

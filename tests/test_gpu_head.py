@@ -338,6 +338,40 @@ def test_logits_that_are_not_finite(lib, dtype, tokens, V, kind):
         assert (g[far] < -1e30).all()
 
 
+# columns of 96, 128 and 192 tokens read the rows of H where they lie (bfloat16), columns of 256 a gathered copy
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [1, 96, 97, 128, 129, 192, 193, 257, 384, 385, 576, 577])
+def test_scoring_tokens_where_they_lie(lib, dtype, n):
+    """Positions in any order, repeated, out of range (clamped and reported), and without a list of positions."""
+    T, D, V = 700, 192, 3001
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    H = torch.randn((T, D), device=DEV, generator=g).to(dtype)
+    W = (0.1 * torch.randn((V, D), device=DEV, generator=g)).to(dtype)
+    ids = torch.randint(0, V, (T,), device=DEV, dtype=torch.int32, generator=g)
+    all_logp = torch.log_softmax(H.double() @ W.double().T, 1)
+    tol = D * 2.0 ** -24 * float((H.abs().double() @ W.abs().double().T).max()) + 32 * 2.0 ** -24 * 20   # any order of the fp32 sums
+
+    def check(pos, ids, want_flags):
+        status = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+        h = H if pos is not None else H[:n]
+        logp, lse = lib.dppo_token_logprob(h, W, ids[:len(h)], pos, status=status)
+        row = pos.long() if pos is not None else torch.arange(n, device=DEV)
+        target = ids.long()[(row + (pos is not None)).clamp(0, len(h) - 1)].clamp(0, V - 1)
+        want = all_logp[row.clamp(0, len(h) - 1), target]
+        assert (logp.double() - want).abs().max() <= tol
+        assert int(status) == want_flags
+
+    pos = torch.randint(0, T - 1, (n,), device=DEV, dtype=torch.int32, generator=g)
+    check(pos, ids, 0)
+    check(None, ids, 0)
+    pos[0] = -5 if n % 2 else T + 7
+    check(pos, ids, lib.HEAD_BAD_POSITION)
+    ids = ids.clone()
+    ids[:n] = V + 3
+    check(None, ids, lib.HEAD_BAD_TARGET)
+
+
 # 143 and 300 tiles of dH (a last round of 143 and of 44), both operand layouts, against 1188 slices of the vocabulary
 @pytest.mark.parametrize("tokens,D", [(2810, 3328), (7500, 2560)])
 def test_dh_parts_in_the_memory_of_dw(lib, tokens, D):
