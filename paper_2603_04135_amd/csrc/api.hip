@@ -90,6 +90,7 @@ struct WsPlan {
     // region offsets
     size_t o_wt, o_logp, o_ell, o_kl, o_clip, o_seq, o_sratio, o_hc, o_hct, o_part, o_zg, o_fpart, o_y, o_rowc, o_zy, o_lse, o_c;
     size_t o_bref, o_mx, o_scale, o_redo_list, o_redo_sum, o_redo_count, o_dwpart;   // bf16 backward only
+    size_t o_done;
     bool direct_w;                 // bf16 backward: the dH GEMM reads W as it lies, no transposed copy is written or reserved
     int f32_parts;                 // float32: sums of all rows of a chunk that the scratch of a dH GEMM cut along K holds
     size_t total;
@@ -138,7 +139,9 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
     p.o_scale = take(per_tok);
     p.o_redo_list = take(per_tok);
     p.o_redo_sum = take(per_tok);
-    p.o_redo_count = take(per_tok ? 4 : 0);
+    p.o_redo_count = take(per_tok ? 8 : 0);
+    // bfloat16: the word behind the redo count (regions are 256-byte aligned); float32: the first target logit, which stays unused
+    p.o_done = per_tok ? p.o_redo_count + 4 : p.o_zy;
     p.chunk_bytes = off - p.fixed_bytes;
     p.sets = sets;
     p.total = p.fixed_bytes + (size_t)sets * p.chunk_bytes;
@@ -572,10 +575,12 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     float* clipf = reinterpret_cast<float*>(w + p.o_clip);
     float* seq_tmp = reinterpret_cast<float*>(w + p.o_seq);
 
+    // workgroups of the final reduction that have finished: a word of the per-chunk regions that nothing else uses
+    int32_t* done = reinterpret_cast<int32_t*>(w + p.o_done);
     const bool recompute = lp->recompute_logits != 0;
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
-        launch_fill_zero(dH, (size_t)s.T * s.D * p.es, status, st);
+        launch_fill_zero(dH, (size_t)s.T * s.D * p.es, status, st, done);
         if (!lp->accumulate_dW && s.N == 0) launch_fill_zero(dW, (size_t)s.V * s.D * 4, nullptr, st);
         if (s.N > 0 && s.dtype == 1 && !p.direct_w) launch_transpose_w(W, s.V, s.D, p.Vp, w + p.o_wt, st);
     }
@@ -716,6 +721,7 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
     ra.ell = ell; ra.kl = kl; ra.clipped = clipf;
     ra.seq_mean = seq_tmp; ra.seq_kl = seq_tmp + s.N; ra.seq_clip = seq_tmp + 2 * s.N;
     ra.seq_loss_out = seq_loss; ra.loss_out = loss; ra.stats_out = stats;
+    ra.done = done;
     {
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         launch_seq_reduce(ra, st);

@@ -48,8 +48,8 @@ struct ChunkView {
     int32_t n_cp;  // padded chunk rows (multiple of 256)
 };
 
-// Clears p, and *word too if it is not NULL.
-void launch_fill_zero(void* p, size_t bytes, int32_t* word, hipStream_t st);
+// Clears p, and *word and *word2 too if they are not NULL.
+void launch_fill_zero(void* p, size_t bytes, int32_t* word, hipStream_t st, int32_t* word2 = nullptr);
 // y[n] = target id of loss token n0+n and rowc[n] = its row of H, both clamped into range (a clamp
 // that changed something is OR-ed into *status, see DPPO_HEAD_BAD_*; status may be NULL);
 // Hc[n_cp, D] = H[rowc[n]] (zero rows beyond n_c). bfloat16: also zy[n] = H[rowc[n]] . W[y[n]] in fp32 (0 beyond
@@ -142,6 +142,7 @@ struct SeqReduceArgs {
     float* seq_mean; float* seq_kl; float* seq_clip;   // [S] scratch
     float* seq_loss_out;                                // [S] or NULL
     float* loss_out; float* stats_out;                  // [1], [4] or NULL
+    int32_t* done;                                      // workgroups that have finished, cleared beforehand
 };
 void launch_seq_reduce(const SeqReduceArgs& a, hipStream_t st);
 

@@ -373,6 +373,28 @@ def test_scoring_tokens_where_they_lie(lib, dtype, n):
 
 
 # 143 and 300 tiles of dH (a last round of 143 and of 44), both operand layouts, against 1188 slices of the vocabulary
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("S", [1, 2, 300, 4096, 4097, 9000])
+def test_totals_of_many_sequences(lib, dtype, S):
+    """The loss is the fp64 sum over the sequences rounded once (2^-24, and 2^-40 of the terms for the order of the fp64 sums),
+    in every call into the same workspace: more sequences than workgroups, and one alone."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S)
+    D, V = 64, 257
+    H = torch.randn((S, D), device=DEV, generator=g).to(dtype)
+    W = (0.1 * torch.randn((V, D), device=DEV, generator=g)).to(dtype)
+    ids = torch.randint(0, V, (S,), device=DEV, dtype=torch.int32, generator=g)
+    cu = torch.arange(S + 1, device=DEV, dtype=torch.int32)
+    adv, coef = torch.randn(S, device=DEV, generator=g), torch.rand(S, device=DEV, generator=g)
+    lp = torch.full((S,), -5.5, device=DEV)
+    ws = lib.alloc_workspace(lib.dppo_workspace_bytes(S, S, D, V, 1 if dtype == torch.bfloat16 else 0, True), H.device)
+    for _ in range(3):
+        out = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, adv, coef, lp, lp, ws=ws)
+        terms = coef.double() * out["seq_loss"].double()
+        assert abs(float(out["loss"]) - float(terms.sum())) <= 2.0 ** -24 * abs(float(terms.sum())) + 2.0 ** -40 * float(terms.abs().sum())
+        assert float(out["stats"][2]) == S
+
+
 @pytest.mark.parametrize("tokens,D", [(2810, 3328), (7500, 2560)])
 def test_dh_parts_in_the_memory_of_dw(lib, tokens, D):
     """A call that overwrites dW keeps partial tiles of dH there first, one that adds to it may not: the same dW, and dH the
