@@ -238,7 +238,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps LDS targets in SGPRs
     const int wave_m = wave % Cfg::WGM, wave_n = wave / Cfg::WGM;
-    int tm, tn, bm0, bn0, kt_lo, KT, slot;
+    int tm, tn, bm0, bn0, kt_lo, KT;
 
     constexpr int B_KM_CPR = Cfg::BN / 8;                       // B_KM: 16-byte chunks per k-row of the slice
     // One pointer per load (A loads first, then B loads). A_BLK_KM with B_BLK: every load of a tile is at a lane offset that holds for all tiles from a wave-uniform address
@@ -263,11 +263,9 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
     auto locate = [&](int item) __attribute__((always_inline)) {
         kt_lo = 0;
         int kt_hi = K / Cfg::BK, item_tile = item;
-        slot = item;
         if (k_parts != 1) {                          // whole tiles (the common case) skip these divisions
             const int n_tiles = n_items / k_parts, k_part = item / n_tiles;
             item_tile = item - k_part * n_tiles;
-            slot = item_tile * k_parts + k_part;
             kt_lo = (int)((int64_t)k_part * (K / Cfg::BK) / k_parts);
             kt_hi = (int)((int64_t)(k_part + 1) * (K / Cfg::BK) / k_parts);
         }
@@ -310,6 +308,12 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
             pl[i] = (isA ? A : B) + (size_t)r * (isA ? lda : ldb) + kc * 8;
         }
     };
+    // Formed behind the main loop: kept over it, dH's main loop was scheduled 1.7 % slower.
+    auto item_slot = [&](int item) __attribute__((always_inline)) {
+        if (k_parts == 1) return item;
+        const int n_tiles = n_items / k_parts;
+        return item % n_tiles * k_parts + item / n_tiles;
+    };
     locate(logical);
     // Load i of slice kt: i < B_LD is a B load into B-ring buffer bufb, the others are A loads
     // into A-ring buffer bufa. B goes first, so that at the next barrier "all but the newest A_LD
@@ -320,10 +324,14 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         return smem + (isA ? bufa * Cfg::A_BYTES : Cfg::B_RING + bufb * Cfg::B_BYTES) + (ii * Cfg::NW + wave) * 1024;
     };
     auto load_src = [&](int kt_rel, int i) __attribute__((always_inline)) -> const void* {
-        const int64_t kt = kt_lo + kt_rel;
+        // Every scalar instruction of a slice takes issue slots from the MFMAs: formed with signed 64-bit arithmetic (a division
+        // by blocks with its roundings), dH's offsets cost 2 % of its main loop (32234 tokens, D = 2560, V = 151936 5.32 -> 5.20 M
+        // cycles per tile, 16.82 -> 16.71 ms), the vocabulary GEMM's 1.3 % (90.5 -> 89.3 K).
+        const uint32_t kt = (uint32_t)(kt_lo + kt_rel);
         const size_t koff = (size_t)kt * Cfg::BK;
-        const size_t koff_a = A_KM ? blk_offset(kt * Cfg::BK, 0, lda)
-                              : AM == A_BLK_ROWS ? blk_offset(0, kt * Cfg::BK, lda) : koff;
+        constexpr uint32_t SPB = BLK_C / Cfg::BK;                 // A_BLK_ROWS: slices per block column
+        const size_t koff_a = A_KM ? blk_offset((int64_t)kt * Cfg::BK, 0, lda)
+                              : AM == A_BLK_ROWS ? ((size_t)((uint32_t)kt / SPB) * (BLK_R * BLK_C) | (size_t)((uint32_t)kt % SPB * Cfg::BK)) : koff;
         const bool isA = i >= Cfg::B_LD;
         const int ii = isA ? i - Cfg::B_LD : i;
         size_t koff_b = BL == B_BLK ? koff * Cfg::BN : koff;
@@ -539,7 +547,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_nt_kernel(const uint16_t* __r
         c.M = M; c.N = N; c.tm = tm; c.tn = tn;
         c.bm0 = bm0; c.bn0 = bn0;
         c.m0 = bm0 + wave_m * Cfg::WTM; c.n0 = bn0 + wave_n * Cfg::WTN;
-        c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.slot = slot; c.smem = smem;
+        c.wave_m = wave_m; c.wave_n = wave_n; c.lane = lane; c.tid = tid; c.slot = item_slot(logical); c.smem = smem;
         const bool more = PERSIST && logical + item_step < item_end;
         if (more) {
             logical += item_step;
