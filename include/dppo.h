@@ -226,7 +226,8 @@ int dppo_token_logprob_noalloc(const dppo_head_shape* shape,
  *   + beta (rho_hat - log rho_hat - 1),  rho_hat = exp(logp_ref - logp),  A = seq_adv[s]
  * (Eq. 1; the weight multiplies surrogate and KL alike), and its gradients
  *   dH[T,D] (dtype of H; rows not in loss_pos are zero) and dW[V,D] (float32; added to
- *   the buffer's contents if accumulate_dW != 0, otherwise overwritten).
+ *   the buffer's contents if accumulate_dW != 0, otherwise overwritten, and used for partial
+ *   sums of dH before that).
  * Optional outputs: logp[N]; seq_loss[S] (token-mean loss of each sequence);
  * stats[4] = {mean KL over loss tokens, fraction of tokens whose surrogate gradient is
  * clipped away, N, 0}. loss is one float on the device.

@@ -4,12 +4,11 @@
 // and validate the kept items, one wavefront places them, and all 16 turn the order into offsets.
 // Integer work only; the result is a bit-exact function of the inputs.
 //
-// What bounds it is the latency of one placement: a single wavefront issues an instruction about every
-// 6 cycles, and reading the pool from memory costs 600 to 2000 cycles. The placing wavefront therefore keeps
+// What bounds it is the latency of one placement: a wavefront alone on its compute unit issues an
+// instruction about every 7 cycles, and reading the pool from memory costs 600 to 2000 cycles. The placing wavefront therefore keeps
 // the pool in registers, oldest item in the lowest lane: a ballot finds the oldest item that fits (first-fit
 // reading) or a DPP max the longest one (best-fit), and no memory is touched between two placements.
-// An instruction of a wavefront alone on its compute unit takes about 7 cycles, and a taken branch or a VALU result that the
-// scalar unit waits for several more, so first-fit's loop over rows is straight-line code with one look (at the slots, the
+// A taken branch, or a VALU result that the scalar unit waits for, costs several instructions more, so first-fit's loop over rows is straight-line code with one look (at the slots, the
 // stream and the row ends together) per row.
 // Measured (8 500 prompts, pool of 32, 2 900 rows): first-fit 0.51 ms (3.07 with the pool in global memory and one wavefront for
 // everything; 0.75 with a branch for each of those looks, in every row and around every search), best-fit 1.28 ms.
@@ -82,8 +81,8 @@ __device__ __forceinline__ uint64_t lanes_below(int n) { return __ballot((int)(t
 // count as fetched. Once the slots run out, the order is written and the pool closed up again (at least
 // 32 placements later). order[] receives stream indices.
 // First-fit begins a row with the run of oldest items whose lengths add up to at most the capacity; the
-// prefix sums for that are kept up to date, so the whole run is one step (about 100 cycles, as much as one
-// placement costs in the search for later items that still fit).
+// prefix sums for that are kept up to date, so the whole run is one step, as dear as one
+// placement in the search for later items that still fit.
 // lens: stream lengths (LDS or global); moved: 64 R ints of LDS. Returns the number of rows.
 template <int R, bool BEST>
 __device__ __forceinline__ int place_pool(int S, int capacity, int n_win, const int32_t* lens, int32_t* moved, int32_t* order,
