@@ -39,9 +39,9 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E peak
 # gives). Keyed by (workload, kernel, recompute); an entry is deleted when that kernel changes, until
 # the counters are taken again.
 MEASURED_TRAFFIC_BYTES = {
-    ("qwen3_4b", "logits_gemm", False): 2.0 * 19084425 * 1024 + 9734956 * 1024,
-    ("qwen3_4b", "dh_gemm", False): 2.0 * 21404815 * 1024 + 161247 * 1024,
-    ("qwen3_4b", "dw_gemm", False): 2.0 * 21985449 * 1024 + 1561953 * 1024,   # both dispatches
+    ("qwen3_4b", "logits_gemm", False): 2.0 * 19076973 * 1024 + 9736444 * 1024,
+    ("qwen3_4b", "dh_gemm", False): 2.0 * 21725421 * 1024 + 161247 * 1024,
+    ("qwen3_4b", "dw_gemm", False): 2.0 * 21761298 * 1024 + 1561921 * 1024,   # both dispatches
 }
 
 
