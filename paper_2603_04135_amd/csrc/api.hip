@@ -646,8 +646,8 @@ int dppo_loss_fwd_bwd(const dppo_head_shape* shape, const dppo_loss_params* lp, 
             launch_grad_logits_f32(reinterpret_cast<float*>(G), s.V, p.Vp, y, lse_c, ta.c_chunk, cv.n_c, st);
         } else if (recompute) {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
-            const int rc2 = launch_mfma_logits_grad(W, s.V, s.D, wc + p.o_hc, cv.n_cp, y, lse_c, ta.c_chunk,
-                                                    reinterpret_cast<const float*>(wc + p.o_zy), G, p.Vp, p.Vp, st);
+            const int rc2 = launch_mfma_logits_grad(W, s.V, s.D, wc + p.o_hc, cv.n_cp, y, lse_c, ta.c_chunk, G, p.Vp,
+                                                    p.Vp, st);
             if (rc2 != DPPO_OK) return rc2;
         } else {
             StageTimer tm(DPPO_STAGE_GRAD_LOGITS, st);

@@ -198,9 +198,9 @@ LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* H
 int launch_mfma_logits_exp(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp, float2* part,
                            const float* bref, void* E, int64_t lde, int32_t Vp, hipStream_t st);
 // Same GEMM, but the epilogue turns logits straight into gradient entries
-// G[n,v] = c[n] (1[v==y[n]] - exp(z - lse[n])) written as bf16 to the blocked chunk G (pitch ldg = Vp); zy = target logits.
+// G[n,v] = c[n] (1[v==y[n]] - exp(z - lse[n])) written as bf16 to the blocked chunk G (pitch ldg = Vp).
 int launch_mfma_logits_grad(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp,
-                            const int32_t* y, const float* lse, const float* c, const float* zy, void* G, int64_t ldg,
+                            const int32_t* y, const float* lse, const float* c, void* G, int64_t ldg,
                             int32_t Vp, hipStream_t st);
 // dH rows of a chunk: C[n_c, D] = diag(row_scale) G[n_c, Vp] W[V, D] with G in the blocked chunk layout (pitch Vp)
 // and W read from WT, its transpose in the blocked B-operand layout, or as it lies if WT is NULL; row_scale may be NULL (= 1). `partial` (or NULL): scratch of

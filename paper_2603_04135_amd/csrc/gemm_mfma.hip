@@ -188,12 +188,12 @@ int launch_mfma_logits_exp(const void* W, int32_t V, int32_t D, const void* Hc, 
 }
 
 int launch_mfma_logits_grad(const void* W, int32_t V, int32_t D, const void* Hc, int32_t n_cp,
-                            const int32_t* y, const float* lse, const float* c, const float* zy, void* G, int64_t ldg,
+                            const int32_t* y, const float* lse, const float* c, void* G, int64_t ldg,
                             int32_t Vp, hipStream_t st) {
     if (Vp % CfgBig::BM != 0 || ldg != Vp || Vp < V)
         return fail(DPPO_ERR_UNSUPPORTED, "gradient-logits buffer not padded to whole vocabulary tiles (Vp %d, pitch %lld)",
                     Vp, (long long)ldg);
-    EpiLogitsGrad e{y, lse, c, zy, reinterpret_cast<uint16_t*>(G), ldg, n_cp, V};
+    EpiLogitsGrad e{y, lse, c, reinterpret_cast<uint16_t*>(G), ldg, n_cp, V};
     launch<CfgBig>(W, D, Hc, D, V, n_cp, D, e, st);
     return DPPO_OK;
 }

@@ -937,9 +937,11 @@ struct EpiLogitsExp {
 
 // Rows = vocabulary entries, columns = tokens: softmax-gradient entries straight from the logits,
 // staged through LDS as [token][vocabulary row] and stored to the blocked chunk like the logits.
-// The target's entry c (1 - p), with p from the target logit zy, is put in its place in LDS.
+// The target's entry c (1 - p) takes p from the same accumulator as the others: lse holds the very rounding errors of these
+// logits, and where p is near 1 they cancel (a target logit summed in another order leaves its difference in 1 - p, 2^-20
+// and more of a logit of 16, where 1 - p may be 2^-14). Few wavefronts hold a target, so each looks once per 16 tokens.
 struct EpiLogitsGrad {
-    const int32_t* y; const float* lse; const float* cvec; const float* zy;
+    const int32_t* y; const float* lse; const float* cvec;
     uint16_t* G; int64_t ldg; int64_t n_cp; int V;
 
     template <class Cfg>
@@ -952,33 +954,38 @@ struct EpiLogitsGrad {
                 const int tok = c.wave_n * Cfg::WTN + ni * MB + acc_col(c.lane);
                 const int64_t col = c.bn0 + tok;
                 const bool col_ok = col < n_cp;
+                const int at = col_ok ? y[col] - (c.bm0 + c.wave_m * Cfg::WTM) : -1;    // target among the wavefront's rows
                 const float l = col_ok ? lse[col] : 0.0f;
                 const float cn = col_ok ? cvec[col] : 0.0f;
+                auto softmax = [&](int mi, int q) __attribute__((always_inline)) {
+                    return __builtin_amdgcn_exp2f((acc[mi][ni][q] - l) * LOG2E);
+                };
 #pragma unroll
                 for (int mi = 0; mi < Cfg::MI; ++mi) {
                     const int vloc = c.wave_m * Cfg::WTM + mi * MB + acc_row(c.lane, 0);
                     bf16x4 h;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        float gv = -cn * __builtin_amdgcn_exp2f((acc[mi][ni][q] - l) * LOG2E);
+                        float gv = -cn * softmax(mi, q);
                         if (!FULL) gv = c.bm0 + vloc + q < V ? gv : 0.0f;
                         const __bf16 b = (__bf16)gv;   // scalar copy: reading h[q] back right after writing it miscompiles
                         h[q] = b;
                     }
                     *reinterpret_cast<bf16x4*>(c.smem + tok * ZPITCH + vloc * 2) = h;
                 }
+                if (!__any(at >= 0 && at < Cfg::WTM)) continue;
+#pragma unroll
+                for (int mi = 0; mi < Cfg::MI; ++mi)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (at != mi * MB + acc_row(c.lane, q)) continue;
+                        const __bf16 b = (__bf16)(cn * (1.0f - softmax(mi, q)));
+                        *reinterpret_cast<__bf16*>(c.smem + tok * ZPITCH + (c.wave_m * Cfg::WTM + at) * 2) = b;
+                    }
             }
         };
         if (c.bm0 + Cfg::BM <= V) body(std::true_type{});
         else body(std::false_type{});
-        __syncthreads();
-        for (int t = c.tid; t < Cfg::BN; t += Cfg::NT) {
-            const int64_t col = c.bn0 + t;
-            const int v = col < n_cp ? y[col] - c.bm0 : -1;
-            if (v < 0 || v >= Cfg::BM) continue;
-            const __bf16 b = (__bf16)(cvec[col] * (1.0f - __builtin_amdgcn_exp2f((zy[col] - lse[col]) * LOG2E)));
-            *reinterpret_cast<uint16_t*>(c.smem + t * ZPITCH + v * 2) = __builtin_bit_cast(uint16_t, b);
-        }
         __syncthreads();
         const StagedStore<Cfg> staged(c, G, ldg);
 #pragma unroll

@@ -245,6 +245,33 @@ def test_token_columns_of_the_forward(lib, tokens, D, V):
         _run_case(lib, case, TOL["bf16"], recompute_logits=True)
 
 
+# the forward in columns of 192 tokens and of 256
+@pytest.mark.parametrize("tokens", [150, 250])
+def test_recomputed_gradient_of_likely_targets(lib, tokens):
+    """Targets of probability 1 - 4e-5: 1 - p is formed from the very logit that entered lse, so that its rounding errors
+    cancel. What remains is the rounding of lse (2^-20, as it lies between 16 and 32), of the exponential (2^-22), of the 32
+    exponentials of 4e-8 that a thread adds to the target's 1 (2^-24 each) and of the entry to bf16 (2^-9): 8 %, seen 5 %.
+    A target logit summed over D = 4096 in another order is off by 2^-18 and more: 37 %."""
+    D, V, z_target = 4096, 1000, 17.0
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), device=DEV, generator=g).bfloat16()
+    ids = torch.randperm(V, device=DEV, generator=g)[:tokens].int()
+    W = torch.zeros((V, D), device=DEV, dtype=torch.bfloat16)
+    W[ids.long()] = (H.float() * (z_target / H.float().square().sum(1, keepdim=True))).bfloat16()
+    logp, _ = lib.dppo_token_logprob(H, W, ids, None)
+    cu, one = torch.tensor([0, tokens], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    out = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, logp, logp, recompute_logits=True)
+    p = torch.softmax(H.double() @ W.double().T, 1)                  # ratio 1, no KL: d loss / d logp = -1 / tokens
+    hot = torch.zeros_like(p).scatter_(1, ids.long()[:, None], 1.0)
+    miss = 1.0 - p.gather(1, ids.long()[:, None])[:, 0]
+    assert float(miss.min()) > 3e-5 and float(miss.max()) < 6e-5
+    want = (((hot - p).T @ H.double()) * (-1.0 / tokens))[ids.long()]
+    err = (out["dW"][ids.long()].double() - want).norm(dim=1) / want.norm(dim=1)
+    worst = float(err.max())
+    assert worst <= (2.0 ** -20 + 2.0 ** -22 + 32 * 2.0 ** -24) / float(miss.min()) + 2.0 ** -8
+
+
 @pytest.mark.parametrize("tokens,D", [(40, 64), (256, 320), (257, 64)])
 def test_dh_of_few_tiles_in_many_parts(lib, tokens, D):
     # 313 slices of the vocabulary against one or two tiles of dH: cut into 19 parts of 16 and 17 slices
