@@ -5,10 +5,15 @@
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate, so every operand element is split on its way
 // into LDS into three bf16 values, x = h + m + l (each the rounded remainder of the ones before: 8 + 8 + 8 significand
 // bits, the sum is x exactly), and a product takes six bf16 MFMAs into the fp32 accumulators:
-//     x y = m m' + h m' + h l' + h h' + m h' + l h',      dropped: m l' + l m' + l l' <= 2^-25 |x y|,
-// less than half the rounding of one fp32 product. K = 32 costs 96 matrix cycles per 16 x 16 block instead of 256, and
-// the accumulator is rounded 6 times instead of 8. Slices that hold a value of BIG or more (where an infinity times a part of
-// the other factor would be a NaN, or a part's product could overflow) are multiplied in fp32 by v_mfma_f32_16x16x4_f32.
+//     x y = l h' + m h' + m m' + h m' + h l' + h h',      dropped: m l' + l m' + l l' <= 2^-24 |x y| (2^-26.5 rms),
+// at most the rounding of one fp32 product. K = 32 costs 96 matrix cycles per 16 x 16 block instead of 256, and the
+// accumulator is rounded 6 times instead of 8. The instruction cuts off the bits of an accumulator that lie below the new
+// product's last place (-1 to +1/2 ulp, 0.39 ulp rms, measured; fp32 rounding 0.29), so the order matters where few products make up
+// the sum: with h h' last only its addition errs at full magnitude. Error of a sum of K products of normally distributed factors
+// (2-norm; in brackets the fp32 instruction's): K = 1 3.4e-8 (2.5e-8; at worst 2^-22.7, 2^-24), 2 3.30e-8 (3.13e-8), 3 3.31e-8 (3.55e-8),
+// 32 3.8e-8 (1.0e-7), 1024 4.8e-7 (5.7e-7), 8192 1.44e-6 (1.64e-6); with h h' fourth K = 1 to 4 4.8e-8. Below FEW_K products, where
+// storing the result takes longer, the fp32 instruction (v_mfma_f32_16x16x4_f32) makes the sums. Slices that hold a value of BIG or
+// more (where an infinity times a part of the other factor would be a NaN, or a part's product could overflow) are multiplied by it, too.
 // Measured against those instructions throughout (2400 tokens, D = 1024, V = 32000): logits 1493 -> 801 us (196 TFLOP/s),
 // dH 1504 -> 851, dW 1463 -> 774; relative error of the logits 5.7e-7 -> 4.9e-7, of dH 1.0e-6 -> 0.8e-6. What bounds it: the
 // matrix pipes are busy half of the time at 2.1 GHz, the splitting (13 VALU instructions per pair) takes most of the rest,
@@ -26,6 +31,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float BIG = 1152921504606846976.0f;    // 2^60
+constexpr int FEW_K = 3;
 
 template <int BM_, int BN_, int BK_, int WGM_, int WGN_>
 struct F32Cfg {
@@ -224,8 +230,9 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
     if (tid == 0) s_big = -1;
     const int lane = tid & 63, ra = wave_m * (MI * 16) + (lane & 15), rb = wave_n * (NI * 16) + (lane & 15), kq = lane >> 4;
     int k0 = k_lo;
-    if (k_lo < k_end) load(k_lo);
-    for (; k0 < k_end; k0 += BK) {
+    const bool few = g.K < FEW_K;
+    if (!few && k_lo < k_end) load(k_lo);
+    for (; !few && k0 < k_end; k0 += BK) {
         __syncthreads();                         // the slice before has been read
         float top = 0.0f;                        // largest magnitude (a NaN is left out: it spoils all six products)
 #pragma unroll
@@ -247,7 +254,7 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
         if (k0 + BK < k_end) load(k0 + BK);
         // Six products of one plane of A with one of B, row by row or column by column of blocks. A plane is replaced in its
         // registers by the next one as the product before is done with it, so that two planes are live and three
-        // workgroups fit a compute unit: one's splitting falls into the others' products.
+        // workgroups fit a compute unit: one's splitting falls into the others' products. h h' comes last (see above).
 #pragma unroll
         for (int kk = 0; kk < BK / 32; ++kk) {
             const int chunk = kk * 4 + kq;
@@ -274,19 +281,19 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
             };
             constexpr int H = 0, M = 1, L = 2;
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) y[ni] = OB::read(s_b, rb, chunk, M, ni);
+            for (int ni = 0; ni < NI; ++ni) y[ni] = OB::read(s_b, rb, chunk, H, ni);
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) x[mi] = OA::read(s_a, ra, chunk, M, mi);
+            for (int mi = 0; mi < MI; ++mi) x[mi] = OA::read(s_a, ra, chunk, L, mi);
             __builtin_amdgcn_sched_barrier(0);
+            by_rows(M);            // l h'
+            by_columns(M);         // m h'
             by_rows(H);            // m m'
             by_columns(L);         // h m'
             by_columns(H);         // h l'
-            by_rows(M);            // h h'
-            by_rows(L);            // m h'
-            by_columns(-1);        // l h'
+            by_columns(-1);        // h h'
         }
     }
-    // From the first slice with a BIG value on: fp32 products of the values themselves. (A loop of its own: as a branch of the one
+    // From the first slice with a BIG value on, or for few products: fp32 products of the values themselves. (A loop of its own: as a branch of the one
     // above it costs that one the accumulators' registers a second time.)
     for (; k0 < k_end; k0 += BK) {
         constexpr int PITCH = BK + 1;
@@ -424,7 +431,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 8; ++j) top = fmaxf(top, fmaxf(__builtin_fabsf(a[d][i][j]), __builtin_fabsf(b[d][i][j])));
-        if (__any(top >= BIG)) {
+        if (g.K < FEW_K || __any(top >= BIG)) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll

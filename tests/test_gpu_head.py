@@ -195,6 +195,52 @@ def test_fp32_values_beyond_the_bf16_split(lib, tokens, D, V):
     assert (logp.double() - want).abs().max() <= tol
 
 
+# dW by wavefront tiles, 64- and 128-wide ones
+FP32_DW_TILES = [(64, 4000), (300, 20001), (1001, 16001)]
+
+
+@pytest.mark.parametrize("tokens", [1, 2, 3])
+@pytest.mark.parametrize("D,V", FP32_DW_TILES)
+def test_fp32_gradient_of_few_tokens(lib, tokens, D, V):
+    """dW of n tokens is a sum of n products of float32 numbers, each product and sum rounded to 24 bits once: off by n 2^-24 of the
+    sum of magnitudes at most. The first n columns of H pick the gradient entries out."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), device=DEV, generator=g)
+    H[:, :tokens] = torch.eye(tokens, device=DEV)
+    W = 0.02 * torch.randn((V, D), device=DEV, generator=g)
+    ids = torch.randint(0, V, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    cu, one = torch.tensor([0, tokens], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    lp, _ = lib.dppo_token_logprob(H, W, ids, None)
+    dW = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, lp, lp)["dW"].double()
+    G = dW[:, :tokens]
+    err = (dW - G @ H.double()).abs() / (G.abs() @ H.double().abs()).clamp_min(2.0 ** -120)
+    worst = float(err.max())
+    assert worst <= tokens * 2.0 ** -24
+
+
+@pytest.mark.parametrize("D,V", FP32_DW_TILES)
+def test_fp32_gradient_of_one_token_among_zeros(lib, D, V):
+    """39 tokens without advantage and one with: dW is one product per entry, of bf16 parts here. Adding h h' last errs by 0.39 units
+    of the last place in rms, -1 to +1/2 at worst, the products left out by 2^-26.5: 3.5e-8 of the entry (4.8e-8 with an
+    order that adds smaller products behind h h')."""
+    tokens, at = 40, 17
+    g = torch.Generator(device=DEV)
+    g.manual_seed(V)
+    H = torch.randn((tokens, D), device=DEV, generator=g)
+    H[:, 0] = 1.0
+    W = 0.02 * torch.randn((V, D), device=DEV, generator=g)
+    ids = torch.randint(0, V, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    cu = torch.tensor([0, at, at + 1, tokens], dtype=torch.int32, device=DEV)
+    adv, coef = torch.tensor([0.0, 1.0, 0.0], device=DEV), torch.ones(3, device=DEV)
+    lp, _ = lib.dppo_token_logprob(H, W, ids, None)
+    dW = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, adv, coef, lp, lp, beta=0.0)["dW"].double()
+    want = dW[:, :1] * H[at].double()
+    err = ((dW - want) / want)[:, 1:]
+    rms, worst = float(err.square().mean().sqrt()), float(err.abs().max())
+    assert rms <= 4e-8 and worst <= 2.0 ** -22, (rms, worst)
+
+
 @pytest.mark.parametrize("tokens", [3072, 3073])
 @pytest.mark.parametrize("D,V", [(320, 777), (64, 257)])
 def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
