@@ -4,7 +4,7 @@
 //
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate, so every operand element is split on its way
 // into LDS into three bf16 values, x = h + m + l (each the rounded remainder of the ones before: 8 + 8 + 8 significand
-// bits, the sum is x exactly), and a product takes six bf16 MFMAs into the fp32 accumulators:
+// bits, the sum is x exactly; all are scaled by 2^24, see SCALE), and a product takes six bf16 MFMAs into the fp32 accumulators:
 //     x y = l h' + m h' + m m' + h m' + h l' + h h',      dropped: m l' + l m' + l l' <= 2^-24 |x y| (2^-26.5 rms),
 // at most the rounding of one fp32 product. K = 32 costs 96 matrix cycles per 16 x 16 block instead of 256, and the
 // accumulator is rounded 6 times instead of 8. The instruction cuts off the bits of an accumulator that lie below the new
@@ -30,7 +30,12 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr float BIG = 1152921504606846976.0f;    // 2^60
+// Elements are split as 2^24 x, so that every part of any float32 value, subnormals among them, is a normal bf16 number or zero (a
+// multiple of 2^-125) and no part of a product that reaches the result underflows; the accumulators are scaled back by 2^-48.
+// Unscaled, a gradient entry below 2^-110 (a token suppressed by e^-76) lost its low parts: 1.5e-2 of a row of dW at e^-80. Two
+// instructions more per pair: 1.6 % of a loss step (2400 tokens, D = 1024, V = 32000: 2.70 -> 2.74 ms).
+// Values below BIG keep the sum of 2^31 products finite: (2^48)^2 2^31 = 2^127.
+constexpr float SCALE = 16777216.0f, UNSCALE = 1.0f / 281474976710656.0f, BIG = 16777216.0f;
 constexpr int FEW_K = 3;
 
 template <int BM_, int BN_, int BK_, int WGM_, int WGN_>
@@ -64,12 +69,13 @@ __device__ __forceinline__ int operand_row(int r, int rows, const int32_t* map, 
     return r;
 }
 
-// x = h + m + l, element pairs packed into 32-bit words.
+// 2^24 x = h + m + l, element pairs packed into 32-bit words.
 __device__ __forceinline__ uint32_t pack_bf16(f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }
 __device__ __forceinline__ f32x2 unpack_bf16(uint32_t w) {
     return f32x2{__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u)};
 }
 __device__ __forceinline__ void split_pair(f32x2 x, uint32_t& h, uint32_t& m, uint32_t& l) {
+    x *= SCALE;
     h = pack_bf16(x);
     f32x2 r = x - unpack_bf16(h);
     m = pack_bf16(r);
@@ -293,6 +299,10 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
             by_columns(-1);        // h h'
         }
     }
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) acc[mi][ni] *= UNSCALE;
     // From the first slice with a BIG value on, or for few products: fp32 products of the values themselves. (A loop of its own: as a branch of the one
     // above it costs that one the accumulators' registers a second time.)
     for (; k0 < k_end; k0 += BK) {
@@ -425,13 +435,22 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
         Direct<A_KM>::load(a[d], g.A, g.lda, m0, g.M, ra, k0, g.K, lane);
         Direct<B_KM>::load(b[d], g.B, g.ldb, n0, g.N, rb, k0, g.K, lane);
     };
+    bool split = g.K >= FEW_K;                   // (until the wavefront's first slice with a BIG value)
+    auto unscale = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i / 2][i % 2] *= UNSCALE;
+    };
     auto products = [&](int d) __attribute__((always_inline)) {
         float top = 0.0f;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 8; ++j) top = fmaxf(top, fmaxf(__builtin_fabsf(a[d][i][j]), __builtin_fabsf(b[d][i][j])));
-        if (g.K < FEW_K || __any(top >= BIG)) {
+        if (split && __any(top >= BIG)) {
+            split = false;
+            unscale();
+        }
+        if (!split) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -440,7 +459,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
             return;
         }
         bf16x8 x[2][3], y[2][3];
-        auto split = [&](const float (&v)[8], bf16x8 (&p)[3]) __attribute__((always_inline)) {
+        auto parts_of = [&](const float (&v)[8], bf16x8 (&p)[3]) __attribute__((always_inline)) {
             uint32_t w[3][4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) split_pair(f32x2{v[2 * j], v[2 * j + 1]}, w[0][j], w[1][j], w[2][j]);
@@ -448,7 +467,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
             for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, u32x4{w[q][0], w[q][1], w[q][2], w[q][3]});
         };
 #pragma unroll
-        for (int i = 0; i < 2; ++i) { split(a[d][i], x[i]); split(b[d][i], y[i]); }
+        for (int i = 0; i < 2; ++i) { parts_of(a[d][i], x[i]); parts_of(b[d][i], y[i]); }
         constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
         for (int p = 0; p < 6; ++p)
@@ -470,6 +489,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
             k0 += NW * 32;
         }
     }
+    if (split) unscale();
     // element e = 8 mi + 2 j + ni of lane l: row m0 + 2 (4 (l / 16) + j) + mi, column n0 + 2 (l % 16) + ni
 #pragma unroll
     for (int e = 0; e < 16; ++e) s_acc[wave][e][lane] = acc[e / 8][e % 2][e / 2 % 4];

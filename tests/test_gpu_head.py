@@ -241,6 +241,30 @@ def test_fp32_gradient_of_one_token_among_zeros(lib, D, V):
     assert rms <= 4e-8 and worst <= 2.0 ** -22, (rms, worst)
 
 
+@pytest.mark.parametrize("drop", [60, 72, 78, 84])
+@pytest.mark.parametrize("D,V", FP32_DW_TILES)
+def test_fp32_gradient_of_suppressed_entries(lib, D, V, drop):
+    """The row of dW of a vocabulary entry of logit -drop, whose gradient entries lie between 2^-105 and the subnormals: as good as
+    those entries. Their exponent z - lse is rounded at 64 to 128 (2^-18) and lse and the exponential err by less than 2^-20
+    each; subnormal entries are off by half a unit of 2^-149 twice (the exponential, and its product with the token's factor)."""
+    tokens = 40
+    g = torch.Generator(device=DEV)
+    g.manual_seed(drop)
+    H = torch.randn((tokens, D), device=DEV, generator=g)
+    H[:, 0] = 1.0
+    W = 0.02 * torch.randn((V, D), device=DEV, generator=g)
+    W[7] = 0.0
+    W[7, 0] = -float(drop)
+    ids = torch.randint(8, V, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    cu, one = torch.tensor([0, tokens], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    lp, _ = lib.dppo_token_logprob(H, W, ids, None)
+    dW = lib.dppo_loss_fwd_bwd(H, W, ids, None, cu, one, one, lp, lp, beta=0.0)["dW"]
+    p = torch.exp(-float(drop) - torch.logsumexp(H.double() @ W.double().T, 1)) / tokens
+    want = p @ H.double()
+    bound = (2.0 ** -18 + 2.0 ** -19 + 2.0 ** -148 / p) * p @ H.double().abs() + 2.0 ** -149
+    assert bool(((dW[7].double() - want).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("tokens", [3072, 3073])
 @pytest.mark.parametrize("D,V", [(320, 777), (64, 257)])
 def test_operand_of_dh_on_both_sides_of_its_rule(lib, tokens, D, V):
