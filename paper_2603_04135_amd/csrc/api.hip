@@ -267,7 +267,7 @@ int chunk_forward(const dppo_head_shape& s, const WsPlan& p, int cus, char* ws, 
         LogitsPart lp;
         {
             StageTimer tm(DPPO_STAGE_LOGITS_GEMM, st);
-            lp = launch_mfma_logits(W, s.V, s.D, Hc, tokens, cv, part, zy, st);
+            lp = launch_mfma_logits(W, s.V, s.D, Hc, tokens, !gathered, cv, part, zy, st);
         }
         StageTimer tm(DPPO_STAGE_ELEMENTWISE, st);
         launch_combine_logprob(part, lp, zy, cv, lse_c, logp_all, lse_all, st);

@@ -186,9 +186,11 @@ int mfma_dh_slices(int32_t V);
 int32_t mfma_vocab_tile();
 constexpr int32_t LOGITS_FEW_TOKENS = 128;
 // Columns of up to 192 tokens read the tokens' rows from H themselves: where mfma_logits_reads_tokens says so, nothing needs to be
-// gathered, and the launch also looks the tokens up (status word) and writes their target logits to zy.
+// gathered, and with look_up the launch also looks the tokens up (status word) and writes their target logits to zy. (A recomputing
+// step gathers all the same, for dW, and needs no second lookup; read from the copy just written instead of from H, its logits
+// GEMM was slower: 96 tokens of D = 4096, V = 151936, whole step 1600 -> 1631 us.)
 bool mfma_logits_reads_tokens(int32_t n_c);
-LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, ChunkView cv, float2* part,
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, bool look_up, ChunkView cv, float2* part,
                               float* zy, hipStream_t st);
 // Same GEMM; stores E[n, v] = exp(z[n, v] - bref[n]) as bf16 (0 for V <= v < Vp) to E, a [n_cp, lde]
 // matrix in the blocked chunk layout (blocks of 64 tokens x 256 vocabulary entries, each

@@ -151,7 +151,7 @@ int32_t mfma_vocab_tile() { return CfgBig::BM; }
 static bool narrow_columns(int32_t n_c) { return n_c <= (int32_t)ceil_div(n_c, CfgBig::BN) * CfgBig192::BN; }
 bool mfma_logits_reads_tokens(int32_t n_c) { return narrow_columns(n_c); }
 
-LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, ChunkView cv, float2* part,
+LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* Hc, const TokenArgs& tokens, bool look_up, ChunkView cv, float2* part,
                               float* zy, hipStream_t st) {
     const int32_t n_c = cv.n_c;
     LogitsPart lp{mfma_logits_row_tiles(V), cv.n_cp};
@@ -161,7 +161,7 @@ LogitsPart launch_mfma_logits(const void* W, int32_t V, int32_t D, const void* H
         typedef decltype(cfg) Cfg;
         EpiScore e{{part, pitch}, tokens, cv.n0, n_c, zy};
         launch<Cfg, A_ROWS, WG_ROUNDS, B_MAP>(W, D, rows, D, V, n_c, D, e, st, 0, -1, 1, -1, (int)tokens.T, 0, map,
-                                              (int)ceil_div(n_c, Cfg::NW));
+                                              look_up ? (int)ceil_div(n_c, Cfg::NW) : 0);
     };
     if (n_c <= LOGITS_FEW_TOKENS) {
         // as many pairs in all as with 256-row tiles: twice the row tiles, half the pitch

@@ -342,6 +342,37 @@ def test_recomputed_gradient_of_likely_targets(lib, tokens):
     assert worst <= (2.0 ** -20 + 2.0 ** -22 + 32 * 2.0 ** -24) / float(miss.min()) + 2.0 ** -8
 
 
+# columns of 96, 128 and 192 tokens, whose forward reads H itself, and of 256
+@pytest.mark.parametrize("n", [40, 100, 150, 250])
+def test_recomputing_step_reports_and_clamps_tokens(lib, n):
+    """The gather alone looks the tokens up: positions and ids out of range are reported, and taken as the clamped ones."""
+    T, D, V = 300, 128, 1000
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    H = torch.randn((T, D), device=DEV, generator=g).bfloat16()
+    W = (0.1 * torch.randn((V, D), device=DEV, generator=g)).bfloat16()
+    ids = torch.randint(0, V, (T,), device=DEV, dtype=torch.int32, generator=g)
+    pos = torch.randperm(T - 2, device=DEV, generator=g)[:n].int() + 1
+    cu, one = torch.tensor([0, n], dtype=torch.int32, device=DEV), torch.ones(1, device=DEV)
+    lp = torch.full((n,), -7.0, device=DEV)
+
+    def run(pos, ids, want_flags):
+        status = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+        out = lib.dppo_loss_fwd_bwd(H, W, ids, pos, cu, one, one, lp, lp, recompute_logits=True, status=status)
+        assert int(status) == want_flags
+        return out
+
+    bad_pos, bad_ids, at = pos.clone(), ids.clone(), int(pos[3]) + 1
+    bad_pos[0], pos[0] = -5, 0
+    bad_ids[at], ids[at] = V + 3, V - 1
+    good = run(pos, ids, 0)
+    bad = run(pos, bad_ids, lib.HEAD_BAD_TARGET)
+    for name in ("logp", "dH", "dW", "loss"):
+        assert torch.equal(good[name], bad[name]), name
+    bad = run(bad_pos, ids, lib.HEAD_BAD_POSITION)
+    assert torch.equal(good["logp"][1:], bad["logp"][1:]) and torch.isfinite(bad["logp"]).all()
+
+
 @pytest.mark.parametrize("tokens,D", [(40, 64), (256, 320), (257, 64)])
 def test_dh_of_few_tiles_in_many_parts(lib, tokens, D):
     # 313 slices of the vocabulary against one or two tiles of dH: cut into 19 parts of 16 and 17 slices
