@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "dppo_internal.h"
+#include "gemm_f32_plan.h"
 
 namespace dppo {
 

@@ -166,7 +166,6 @@ struct GemmF32 {
     float* partial; int64_t partial_floats;
     const int32_t* a_map; int32_t a_rows;      // K-contiguous A: row m is row a_map[m] of a_rows (clamped) if a_map is not NULL
 };
-int gemm_f32_max_parts(int64_t K);
 void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st);
 
 // bf16 MFMA GEMMs (gemm_mfma.hip). K must be a multiple of 64; A and B rows may be read up

@@ -20,6 +20,7 @@
 // only partly under other wavefronts' products. Splitting the next slice between the products of the present one, with the
 // parts in registers and two workgroups per compute unit, was slower (928 / 999 / 880 us).
 #include "dppo_internal.h"
+#include "gemm_f32_plan.h"
 
 namespace dppo {
 namespace {
@@ -559,40 +560,16 @@ void launch_direct(const GemmF32& p, int parts, hipStream_t st) {
 
 }  // namespace
 
-// Parts that the scratch of a dH GEMM is laid out for.
-int gemm_f32_max_parts(int64_t K) {
-    const int64_t p = K / 256;
-    return (int)(p < 1 ? 1 : p > 16 ? 16 : p);
-}
-
-// Tile and K split (a power of two): the least estimated time. A launch takes a start plus its K steps, one after the other;
-// a step takes a latency, or, with many workgroups to a compute unit, their products' time; a split adds a launch that sums. The
-// constants (us) are fitted to 2700 measured combinations (all three GEMMs; 20 to 2400 tokens, D = 64 to 1024, V = 500 to 32000;
-// times within 13 % rms), and what is picked is on average 1.4 % slower than the fastest (20 % at worst, at 10 us).
 void launch_gemm_f32(const GemmF32& p, int cus, hipStream_t st) {
     if (p.M <= 0 || p.N <= 0) return;
-    static const struct { int edge, step_k; double start, latency, step; } option[4] = {
-        {F32Big::BM, F32Big::BK, 6.1, 2.0, 1.37},
-        {F32Mid::BM, F32Mid::BK, 4.3, 1.13, 0.51},
-        {DIRECT_EDGE, 32 * 4, 3.3, 1.18, 0.80},
-        {DIRECT_EDGE, 32 * 8, 2.7, 1.9, 1.9},
-    };
-    const double out_bytes = 4.0 * p.M * p.N;
-    const int64_t room = p.partial ? p.partial_floats / ((int64_t)p.M * p.N) : 1;
-    int best = 0, parts = 1;
-    double best_t = -1.0;
-    for (int c = 0; c < 4; ++c) {
-        const int64_t tiles = ceil_div(p.M, option[c].edge) * ceil_div(p.N, option[c].edge);
-        for (int q = 1; q == 1 || (q <= room && q <= 256 && 32 * (q / 2) < p.K); q *= 2) {
-            const double steps = (double)ceil_div(ceil_div(p.K, q), option[c].step_k), load = (double)ceil_div(tiles * q, cus) * option[c].step;
-            const double t = option[c].start + steps * (load > option[c].latency ? load : option[c].latency) +
-                             (q > 1 ? 3.2 + q * out_bytes / 3.1e6 : 0.0);
-            if (best_t < 0.0 || t < best_t) { best_t = t; best = c; parts = q; }
-        }
-    }
-    if (best == 0) launch_cfg<F32Big>(p, parts, st);
-    else if (best == 1) launch_cfg<F32Mid>(p, parts, st);
-    else if (best == 2) launch_direct<4>(p, parts, st);
+    static_assert(F32_EDGE[F32_BIG] == F32Big::BM && F32_EDGE[F32_MID] == F32Mid::BM && F32_EDGE[F32_DIRECT_4] == DIRECT_EDGE &&
+                  F32_EDGE[F32_DIRECT_8] == DIRECT_EDGE && F32_STEP_K[F32_BIG] == F32Big::BK && F32_STEP_K[F32_MID] == F32Mid::BK,
+                  "the plan knows the kernels' tiles");
+    const F32Plan plan = plan_gemm_f32(p.M, p.N, p.K, p.partial ? p.partial_floats / ((int64_t)p.M * p.N) : 1, cus);
+    const int parts = plan.parts;
+    if (plan.kernel == F32_BIG) launch_cfg<F32Big>(p, parts, st);
+    else if (plan.kernel == F32_MID) launch_cfg<F32Mid>(p, parts, st);
+    else if (plan.kernel == F32_DIRECT_4) launch_direct<4>(p, parts, st);
     else launch_direct<8>(p, parts, st);
     if (parts > 1)
         sum_parts_f32_kernel<<<(unsigned)ceil_div((int64_t)p.M * p.N, 256), 256, 0, st>>>(p.partial, parts, p.M, p.N, p.C,

@@ -136,8 +136,8 @@ def test_vocab_and_token_tails(lib):
     _run_case(lib, case, TOL["f32"])
 
 
-# (workload, loss tokens, D, V): every tile of the fp32 GEMM (32, 64, 128 wide) with remainders in all dimensions, a
-# single column, unaligned rows, K slices with a tail, and dH cut along the vocabulary
+# (workload, loss tokens, D, V): wavefront tiles of the fp32 GEMM, and 64-wide ones for the logits and dH of the largest, with remainders in
+# all dimensions, a single column, unaligned rows, K slices with a tail, and dH cut along the vocabulary
 @pytest.mark.parametrize("name,tokens,D,V", [("tiny", 1, 1, 2), ("tiny", None, 33, 3001), ("tiny", 33, 300, 65),
                                              ("small", 700, 130, 1100), ("small", 1100, 257, 4099)])
 def test_fp32_tiles_and_splits(lib, name, tokens, D, V):
@@ -156,10 +156,10 @@ def test_fp32_rows_between_the_gemms(lib, V):
     _run_case(lib, _case("tiny", 11, dtype="f32", D=12, V=V), TOL["f32"])
 
 
-# one size for each kind of tile of the fp32 GEMM (32, 64 and 128 wide)
-@pytest.mark.parametrize("tokens,D,V", [(40, 100, 500), (300, 200, 3001), (1100, 203, 9000)])
+# wavefront tiles, wavefront tiles with dH in parts, 128-wide logits with 64-wide gradients, and 128-wide tiles throughout
+@pytest.mark.parametrize("tokens,D,V", [(40, 100, 500), (300, 200, 3001), (1100, 203, 9000), (2111, 701, 9001)])
 def test_fp32_values_beyond_the_bf16_split(lib, tokens, D, V):
-    """Values of 2^60 and more, and infinities, do not go through the split into bf16 parts: a column scaled by 2^80 in H and by
+    """Values of 2^24 and more, and infinities, do not go through the split into bf16 parts: a column scaled by 2^80 in H and by
     2^-80 in W leaves the logits as they are and scales that column of dW and dH; a weight at minus infinity against
     positive hidden states is a logit at minus infinity."""
     g = torch.Generator(device=DEV)
@@ -193,6 +193,42 @@ def test_fp32_values_beyond_the_bf16_split(lib, tokens, D, V):
     logp, lse = lib.dppo_token_logprob(H, W, ids, None)
     want = torch.log_softmax(z[:, :V - 1], 1).gather(1, ids.long()[:, None])[:, 0]
     assert (logp.double() - want).abs().max() <= tol
+
+
+# (tokens, D, V): between them every kernel of the fp32 GEMM for the logits, dH and dW, and parts along K for each (test_f32_plan
+# holds that); remainders in all dimensions. The last one takes 128-wide tiles throughout.
+FP32_SIZES = [(33, 300, 65), (170, 33, 3001), (300, 200, 3001), (500, 333, 7001), (2111, 701, 9001)]
+
+
+@pytest.mark.parametrize("tokens,D,V", FP32_SIZES)
+def test_fp32_error_against_float64(lib, tokens, D, V):
+    """Tight enough to tell the split in three bf16 parts from one that loses the third part of one operand of one GEMM. Log-probs
+    (logits of deviation 2) are off by 0.3e-6 to 0.9e-6 in rms, gradients by 0.4e-6 to 1.1e-6 of their norm, growing with the lengths of the sums;
+    the loss of such a part adds 4.5e-6 and more, and 1.9e-6 and more (emulated on the CPU)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tokens)
+    H = torch.randn((tokens, D), device=DEV, generator=g)
+    W = torch.randn((V, D), device=DEV, generator=g) * (2.0 / D ** 0.5)
+    ids = torch.randint(0, V, (tokens,), device=DEV, dtype=torch.int32, generator=g)
+    S = 8
+    cu = torch.tensor([tokens * i // S for i in range(S + 1)], dtype=torch.int32, device=DEV)
+    adv, coef = torch.randn(S, device=DEV, generator=g), torch.rand(S, device=DEV, generator=g)
+    logp = torch.log_softmax(H.double() @ W.double().T, 1)
+    want = logp.gather(1, ids.long()[:, None])[:, 0]
+    lp = want.float()
+    args = (H, W, ids, None, cu, adv, coef, lp, lp)
+    out = lib.dppo_loss_fwd_bwd(*args, beta=0.0)           # ratio 1, no KL: d loss / d logp = -advantage x weight / length
+    length = (cu[1:] - cu[:-1]).double()
+    c = (-adv.double() * coef.double() / length).repeat_interleave(length.long())
+    G = (torch.zeros_like(logp).scatter_(1, ids.long()[:, None], 1.0) - logp.exp()) * c[:, None]
+    err = (out["logp"].double() - want).square().mean().sqrt().item()
+    dH, dW = G @ W.double(), G.T @ H.double()
+    err_dH, err_dW = [((a.double() - b).norm() / b.norm()).item() for a, b in ((out["dH"], dH), (out["dW"], dW))]
+    print("errors: logp %.3g dH %.3g dW %.3g" % (err, err_dH, err_dW))
+    assert err <= 2.5e-6 and err_dH <= 1.8e-6 and err_dW <= 1.8e-6, (err, err_dH, err_dW)
+    old = torch.randn((V, D), device=DEV, generator=g)
+    acc = lib.dppo_loss_fwd_bwd(*args, beta=0.0, dW=old.clone(), accumulate_dW=True)["dW"]
+    assert torch.equal(acc, old + out["dW"])
 
 
 # dW by wavefront tiles, 64- and 128-wide ones
