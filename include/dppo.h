@@ -227,7 +227,9 @@ int dppo_token_logprob_noalloc(const dppo_head_shape* shape,
  * (Eq. 1; the weight multiplies surrogate and KL alike), and its gradients
  *   dH[T,D] (dtype of H; rows not in loss_pos are zero) and dW[V,D] (float32; added to
  *   the buffer's contents if accumulate_dW != 0, otherwise overwritten, and used for partial
- *   sums of dH before that).
+ *   sums of dH before that). The order in which dH is summed depends on accumulate_dW as it does on
+ *   the workspace size: the same call gives the same bits, with the other value the last bits of
+ *   its float32 sums, and so single bfloat16 roundings, may differ.
  * Optional outputs: logp[N]; seq_loss[S] (token-mean loss of each sequence);
  * stats[4] = {mean KL over loss tokens, fraction of tokens whose surrogate gradient is
  * clipped away, N, 0}. loss is one float on the device.

@@ -536,7 +536,7 @@ def test_scoring_tokens_where_they_lie(lib, dtype, n):
     check(None, ids, lib.HEAD_BAD_TARGET)
 
 
-# 143 and 300 tiles of dH (a last round of 143 and of 44), both operand layouts, against 1188 slices of the vocabulary
+# more sequences than workgroups of the reduction (4096), and one alone
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("S", [1, 2, 300, 4096, 4097, 9000])
 def test_totals_of_many_sequences(lib, dtype, S):
@@ -559,10 +559,11 @@ def test_totals_of_many_sequences(lib, dtype, S):
         assert float(out["stats"][2]) == S
 
 
+# 143 and 300 tiles of dH (a last round of 143 and of 44), both operand layouts, against 1188 slices of the vocabulary
 @pytest.mark.parametrize("tokens,D", [(2810, 3328), (7500, 2560)])
 def test_dh_parts_in_the_memory_of_dw(lib, tokens, D):
     """A call that overwrites dW keeps partial tiles of dH there first, one that adds to it may not: the same dW, and dH the
-    same but for the rounding of another order of the fp32 sums to bf16."""
+    same but for the rounding of another order of the fp32 sums to bf16. Rows of every block of 256 tokens against float64."""
     V = 76000
     g = torch.Generator(device=DEV)
     g.manual_seed(tokens)
@@ -578,6 +579,18 @@ def test_dh_parts_in_the_memory_of_dw(lib, tokens, D):
     a, b = over["dH"].float(), added["dH"].float()
     assert float((a - b).norm() / b.norm()) <= 2.0 ** -9       # each value within a rounding (2^-9) of the same sum, few differ
     assert torch.isfinite(a).all()
+    rows = torch.arange(37, tokens, 251, device=DEV)
+    W64 = W.double()
+    logp64 = torch.log_softmax(H[rows].double() @ W64.T, 1)
+    t = ids.long()[rows]
+    l = logp64.gather(1, t[:, None])[:, 0]
+    rho = torch.exp(l + 11.0)                                  # advantage 1: clipped away above 1.2
+    c = (torch.where(rho > 1.2, 0.0, -rho) + 0.04 * (1.0 - 1.0 / rho)) / tokens
+    want = (W64[t] - logp64.exp() @ W64) * c[:, None]
+    for got in (a, b):
+        err = (got[rows].double() - want).norm(dim=1) / want.norm(dim=1)
+        worst = float(err.max())
+        assert worst <= TOL["bf16"]["grad"]
 
 
 @pytest.mark.parametrize("tokens", [40, 300, 700])
