@@ -154,7 +154,9 @@ void layout(const dppo_head_shape& s, bool bwd, int32_t n_cp, WsPlan& p, int set
 // rounds, plus the last one (the fraction that the launch cuts its tiles into along K = Vp if it is at most
 // half full; a second launch and the sums of the parts keep it from falling below an eighth: priced lower, 221500 tokens
 // of D = 2048, V = 50000 take 9 chunks instead of 7, 96.9 instead of 96.2 ms), plus what every chunk costs regardless of
-// its size (the dW read-modify-write, the small kernels, ramps).
+// its size (the dW read-modify-write, the small kernels, ramps). A chunk that overwrites dW may also cut a fuller last round, with
+// its parts in dW's memory; that is not priced. It is the first chunk only, and never the call's choice where one chunk holds all
+// tokens: a round more than half full, priced as whole, still costs less than the same tiles in two chunks or more.
 constexpr int DEFAULT_CUS = 256;          // MI355X; used where no device is at hand (size queries)
 constexpr double CHUNK_OVERHEAD_ROUNDS = 0.35;
 int32_t target_chunk(int64_t N, int32_t D, int32_t V, size_t es, int cus) {

@@ -33,8 +33,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Elements are split as 2^24 x, so that every part of any float32 value, subnormals among them, is a normal bf16 number or zero (a
 // multiple of 2^-125) and no part of a product that reaches the result underflows; the accumulators are scaled back by 2^-48.
-// Unscaled, a gradient entry below 2^-110 (a token suppressed by e^-76) lost its low parts: 1.5e-2 of a row of dW at e^-80. Two
-// instructions more per pair: 1.6 % of a loss step (2400 tokens, D = 1024, V = 32000: 2.70 -> 2.74 ms).
+// Unscaled, a gradient entry below 2^-110 (a token suppressed by e^-76) lost its low parts: 1.5e-2 of a row of dW at e^-80. The
+// two multiplications per pair cost nothing: the largest magnitude, taken of their results, needs no maximum that quiets
+// signalling NaNs (2400 tokens, D = 1024, V = 32000: 2.70 ms without the scale; 2.69 with it, 2.78 with the maximum of the unscaled values).
 // Values below BIG keep the sum of 2^31 products finite: (2^48)^2 2^31 = 2^127.
 constexpr float SCALE = 16777216.0f, UNSCALE = 1.0f / 281474976710656.0f, BIG = 16777216.0f;
 constexpr int FEW_K = 3;
@@ -70,13 +71,12 @@ __device__ __forceinline__ int operand_row(int r, int rows, const int32_t* map, 
     return r;
 }
 
-// 2^24 x = h + m + l, element pairs packed into 32-bit words.
+// x = h + m + l (x scaled), element pairs packed into 32-bit words.
 __device__ __forceinline__ uint32_t pack_bf16(f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }
 __device__ __forceinline__ f32x2 unpack_bf16(uint32_t w) {
     return f32x2{__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u)};
 }
 __device__ __forceinline__ void split_pair(f32x2 x, uint32_t& h, uint32_t& m, uint32_t& l) {
-    x *= SCALE;
     h = pack_bf16(x);
     f32x2 r = x - unpack_bf16(h);
     m = pack_bf16(r);
@@ -247,15 +247,15 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
             uint32_t h[4], m[4], l[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const f32x2 x = {v[u][2 * j], v[u][2 * j + 1]};
-                top = fmaxf(top, fmaxf(__builtin_fabsf(x[0]), __builtin_fabsf(x[1])));
+                const f32x2 x = f32x2{v[u][2 * j], v[u][2 * j + 1]} * SCALE;
+                top = fmaxf(fmaxf(top, __builtin_fabsf(x[0])), __builtin_fabsf(x[1]));
                 split_pair(x, h[j], m[j], l[j]);
             }
             *reinterpret_cast<u32x4*>(s_x + at[u]) = u32x4{h[0], h[1], h[2], h[3]};
             *reinterpret_cast<u32x4*>(s_x + at[u] + OA::PLANE) = u32x4{m[0], m[1], m[2], m[3]};
             *reinterpret_cast<u32x4*>(s_x + at[u] + 2 * OA::PLANE) = u32x4{l[0], l[1], l[2], l[3]};
         }
-        if (__any(top >= BIG)) s_big = k0;
+        if (__any(top >= SCALE * BIG)) s_big = k0;
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(s_big) == k0) break;
         if (k0 + BK < k_end) load(k0 + BK);
@@ -446,8 +446,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) top = fmaxf(top, fmaxf(__builtin_fabsf(a[d][i][j]), __builtin_fabsf(b[d][i][j])));
-        if (split && __any(top >= BIG)) {
+            for (int j = 0; j < 8; ++j) top = fmaxf(fmaxf(top, __builtin_fabsf(a[d][i][j] * SCALE)), __builtin_fabsf(b[d][i][j] * SCALE));
+        if (split && __any(top >= SCALE * BIG)) {
             split = false;
             unscale();
         }
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
         auto parts_of = [&](const float (&v)[8], bf16x8 (&p)[3]) __attribute__((always_inline)) {
             uint32_t w[3][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) split_pair(f32x2{v[2 * j], v[2 * j + 1]}, w[0][j], w[1][j], w[2][j]);
+            for (int j = 0; j < 4; ++j) split_pair(f32x2{v[2 * j], v[2 * j + 1]} * SCALE, w[0][j], w[1][j], w[2][j]);
 #pragma unroll
             for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, u32x4{w[q][0], w[q][1], w[q][2], w[q][3]});
         };

@@ -171,7 +171,11 @@ __global__ void select_weight_kernel(int Q, int G, int n_bottom, float r_q, floa
 // every prompt among all of them, from LDS). What bounds it is latency: the chains of a group's sums run in every thread of
 // the group at once, from LDS, in the order of the kernels above. 256 prompts x 16 completions: 17 + 13 + 13 us in three
 // launches (dependent loads from memory by one thread per group) -> 11 us; 4 x 4: 11 -> 4.4. With 256 threads a workgroup, one
-// prompt each, the ranks alone made it 14 us. They are Q^2 comparisons per workgroup: beyond 512 prompts they would be most of it.
+// prompt each, the ranks alone made it 14 us. They are Q^2 comparisons per workgroup, shared by 1024 / Q threads a prompt, so beyond 512
+// prompts each thread walks all of them and the lead shrinks. Three launches / one, Bernoulli and fixed count, us:
+//   G = 4   512 prompts 37 / 21, 97 / 47    513  43 / 35, 103 / 83    1024  77 / 69, 202 / 168
+//   G = 16  512 prompts 55 / 23, 161 / 49   513  60 / 37, 169 / 86    1024  94 / 73, 267 / 174
+// One launch is still ahead there; the line is where a prompt has two threads, and up to 1024 (one thread a prompt) it could be raised.
 constexpr int SELECT_THREADS = 1024, SELECT_PROMPTS = 512;
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(
     int Q, int G, int n_bottom, double eps, int ddof, float r_q, float r_o, int fixed_count, int realised_rate,
