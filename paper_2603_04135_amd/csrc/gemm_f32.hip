@@ -324,8 +324,9 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
                 raw[((for_a ? 0 : Cfg::BM) + row) * PITCH + c * 8 + j] = v[u][j];
             }
         __syncthreads();
+        const int k_top = g.K - k0 < BK ? g.K - k0 : BK;      // (zeros beyond: not multiplied where there are few products)
 #pragma unroll 1
-        for (int k = 0; k < BK; k += 4) {
+        for (int k = 0; k < k_top; k += 4) {
             float x[MI], y[NI];
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) x[mi] = raw[(wave_m * (MI * 16) + el * MI + mi) * PITCH + k + eq];
@@ -453,10 +454,12 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_direct_kernel(F32Args g) 
         }
         if (!split) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
+            for (int j = 0; j < 8; ++j) {
+                if (j >= g.K) break;             // (k-values 8 (lane / 16) + j: zeros where there are few products)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     acc[i / 2][i % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[d][i / 2][j], b[d][i % 2][j], acc[i / 2][i % 2], 0, 0, 0);
+            }
             return;
         }
         bf16x8 x[2][3], y[2][3];
