@@ -98,6 +98,31 @@ def test_select_on_both_sides_of_its_sizes(lib, Q, G, fixed):
     _cmp_select(lib, rng.normal(size=(Q, G)).astype(np.float32), None, None, uc, 0.5, 0.4, ddof=0, fixed=fixed)
 
 
+# Results share memory, but each is a tensor of its own: it takes in-place use with gradients, and writing one leaves what
+# autograd saved of another as it is.
+def test_results_are_tensors_of_their_own(lib):
+    rng = np.random.default_rng(4)
+    Q, G = 3, 5
+    u = lambda *shape: rng.random(shape, dtype=np.float32)
+    sel = lib.dppo_select(u(Q, G), u(Q), u(Q), u(Q, G), 0.5, 0.5, device=DEV)
+    pk = lib.dppo_pack(rng.integers(1, 9, Q * G), rng.integers(1, 9, Q * G), None, 20, 4, device=DEV)
+    for out in (sel, pk):
+        names = [k for k, t in out.items() if torch.is_tensor(t)]
+        spans = sorted((out[k].data_ptr(), out[k].data_ptr() + out[k].numel() * out[k].element_size()) for k in names)
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+        assert all(a % 16 == 0 for a, _ in spans)
+        for k in names:
+            versions = {j: out[j]._version for j in names if j != k}
+            out[k].mul_(1)
+            assert versions == {j: out[j]._version for j in names if j != k}, k
+    for k in ("adv", "coef", "gamma_o", "prune_o"):
+        w = torch.ones(Q, G, device=DEV, requires_grad=True)
+        kept = sel[k].clone()
+        sel[k].mul_(w)
+        sel[k].sum().backward()
+        assert torch.equal(w.grad, kept)
+
+
 def test_history_update_matches_oracle(lib):
     rng = np.random.default_rng(3)
     table = rng.random(1000).astype(np.float32)
