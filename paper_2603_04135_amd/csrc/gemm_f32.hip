@@ -238,7 +238,7 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
     const int lane = tid & 63, ra = wave_m * (MI * 16) + (lane & 15), rb = wave_n * (NI * 16) + (lane & 15), kq = lane >> 4;
     int k0 = k_lo;
     const bool few = g.K < FEW_K;
-    if (!few && k_lo < k_end) load(k_lo);
+    if (k_lo < k_end) load(k_lo);
     for (; !few && k0 < k_end; k0 += BK) {
         __syncthreads();                         // the slice before has been read
         float top = 0.0f;                        // largest magnitude (a NaN is left out: it spoils all six products)
@@ -304,8 +304,11 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) acc[mi][ni] *= UNSCALE;
-    // From the first slice with a BIG value on, or for few products: fp32 products of the values themselves. (A loop of its own: as a branch of the one
-    // above it costs that one the accumulators' registers a second time.)
+    // From the first slice with a BIG value on, or for few products: fp32 products of the values themselves; v holds the slice
+    // at k0. (A loop of its own: as a branch of the one above it costs that one the accumulators' registers a second time.) Bound by the
+    // instruction: 2400 tokens, D = 1024, V = 32000 with a BIG value in an early slice of every row 1.46 to 1.53 ms for the scoring (without the
+    // next slice's loads under the products 1.53 to 1.55; all slices through the instruction, without a split, 1.48) and 3.76 to
+    // 3.87 ms for the loss (4.55), of which one to three GEMMs meet such values.
     for (; k0 < k_end; k0 += BK) {
         constexpr int PITCH = BK + 1;
         static_assert((Cfg::BM + Cfg::BN) * PITCH * 4 <= OA::LDS_BYTES + OB::LDS_BYTES, "fp32 slices fit the planes' LDS");
@@ -314,8 +317,7 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
         asm volatile("" : "+v"(et));             // these addresses are formed here, not kept in registers over the loop above
         const int el = et & 15, eq = (et & 63) >> 4;
         et -= first;
-        load(k0);
-        __syncthreads();
+        __syncthreads();                         // the slice before has been read
 #pragma unroll
         for (int u = 0; u < UNITS; ++u)
 #pragma unroll
@@ -324,6 +326,7 @@ __global__ __launch_bounds__(Cfg::NT, 3) void gemm_f32_kernel(F32Args g) {
                 raw[((for_a ? 0 : Cfg::BM) + row) * PITCH + c * 8 + j] = v[u][j];
             }
         __syncthreads();
+        if (k0 + BK < k_end) load(k0 + BK);
         const int k_top = g.K - k0 < BK ? g.K - k0 : BK;      // (zeros beyond: not multiplied where there are few products)
 #pragma unroll 1
         for (int k = 0; k < k_top; k += 4) {
