@@ -250,7 +250,7 @@ def main() -> int:
     keep_flat = sel["keep_comp"].reshape(-1)
     other = {
         "dppo_select": stage(timed(lambda: P.dppo_select(rewards, hist, u_prompt, u_comp, wl.r_q, wl.r_o, device=dev), 10),
-                             sel_bytes, "one kernel of one workgroup, latency-bound"),
+                             sel_bytes, "one launch for up to 512 prompts, latency-bound"),
         "dppo_pack": stage(timed(lambda: P.dppo_pack(item_pl, item_cl, keep_flat, wl.capacity, wl.n_win,
                                                      loss_pos_capacity=lp_cap, device=dev), 10),
                            pack_bytes, "one workgroup (one of its wavefronts places, deterministic) + loss_pos fill; the "

@@ -14,11 +14,11 @@
 // 32 3.8e-8 (1.0e-7), 1024 4.8e-7 (5.7e-7), 8192 1.44e-6 (1.64e-6); with h h' fourth K = 1 to 4 4.8e-8. Below FEW_K products, where
 // storing the result takes longer, the fp32 instruction (v_mfma_f32_16x16x4_f32) makes the sums. Slices that hold a value of BIG or
 // more (where an infinity times a part of the other factor would be a NaN, or a part's product could overflow) are multiplied by it, too.
-// Measured against those instructions throughout (2400 tokens, D = 1024, V = 32000): logits 1493 -> 801 us (196 TFLOP/s),
-// dH 1504 -> 851, dW 1463 -> 774; relative error of the logits 5.7e-7 -> 4.9e-7, of dH 1.0e-6 -> 0.8e-6. What bounds it: the
+// Measured against those instructions throughout (2400 tokens, D = 1024, V = 32000, kernel trace): logits 1407 -> 774 us
+// (203 TFLOP/s), dH 1464 -> 912, dW 1476 -> 792; relative error of the logits 5.7e-7 -> 4.9e-7, of dH 1.0e-6 -> 0.8e-6. What bounds it: the
 // matrix pipes are busy half of the time at 2.1 GHz, the splitting (13 VALU instructions per pair) takes most of the rest,
 // only partly under other wavefronts' products. Splitting the next slice between the products of the present one, with the
-// parts in registers and two workgroups per compute unit, was slower (928 / 999 / 880 us).
+// parts in registers and two workgroups per compute unit, was slower (928 / 999 / 880 us against 801 / 851 / 774 in the same runs).
 #include "dppo_internal.h"
 #include "gemm_f32_plan.h"
 

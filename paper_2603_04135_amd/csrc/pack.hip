@@ -10,7 +10,7 @@
 // reading) or a DPP max the longest one (best-fit), and no memory is touched between two placements.
 // A taken branch, or a VALU result that the scalar unit waits for, costs several instructions more, so first-fit's loop over rows is straight-line code with one look (at the slots, the
 // stream and the row ends together) per row.
-// Measured (8 500 prompts, pool of 32, 2 900 rows): first-fit 0.51 ms (3.07 with the pool in global memory and one wavefront for
+// Measured (8 500 prompts, pool of 32, about 2 950 rows): first-fit 0.51 ms (3.07 with the pool in global memory and one wavefront for
 // everything; 0.75 with a branch for each of those looks, in every row and around every search), best-fit 1.28 ms.
 // Compaction and offsets, spread over 16 wavefronts: 18 us.
 #include "dppo_internal.h"
